@@ -99,17 +99,51 @@ inline bool sparse_final_ok(const sd2_matrix_t* m, int k_tok) {
     return sparse_strip_supported(mat_args(m), k_tok);
 }
 
-// The gate|up linear and the gated product in one launch (the bitmask kernel that adds the slabs up inside the workgroup).
-inline bool gated_ok(const sd2_matrix_t* m, int k_tok) {
-    return sparse_final_ok(m, k_tok) && sparse_strip_gated_supported(mat_args(m), k_tok);
+// What happens to a linear's results: final values for the caller (kFinal), or the next kernel of a stack adds the
+// partial results as it reads them (kStack; the stack's own workspace holds them for every format).
+enum LinUse { kFinal, kStack };
+
+// More than 16 tokens: the kernel that keeps the activations of all tokens in registers.  SD2_OPT_LINEAR_PARTIALS keeps
+// bitmask matrices on the kernel with one partial result per slab.
+bool wide_choice(const sd2_matrix_t* m, int k_tok, LinUse use, WidePlan* p) {
+    if (k_tok <= 16 || (m->kind == SD2_KIND_SPARSE && !is_nm24(m) && option(SD2_OPT_LINEAR_PARTIALS))) return false;
+    const int room = use == kStack ? kWideMaxSplit : n_partials(m);
+    return wide_plan(m->info.n_out, m->info.k_in, m->info.n_strips, k_tok, false, room, use == kStack, p);
+}
+bool wide_gated_choice(const sd2_matrix_t* m, int k_tok, WidePlan* p) {
+    if (k_tok <= 16 || (m->kind == SD2_KIND_SPARSE && !is_nm24(m) && option(SD2_OPT_LINEAR_PARTIALS))) return false;
+    return wide_plan(m->info.n_out, m->info.k_in, m->info.n_strips, k_tok, true, 1, false, p);
 }
 
-// Partial results run_linear leaves in `out` for this token count (1: final values).  Never more than n_partials(m),
-// which sizes the buffers.
-inline int n_splits(const sd2_matrix_t* m, int k_tok) { return sparse_final_ok(m, k_tok) ? 1 : n_partials(m); }
+// The gate|up linear and the gated product in one launch (the kernels that add the slabs up inside the workgroup).
+inline bool gated_ok(const sd2_matrix_t* m, int k_tok) {
+    WidePlan p;
+    if (k_tok > 16) return wide_gated_choice(m, k_tok, &p);
+    return sparse_final_ok(m, k_tok) && sparse_strip_gated_supported(mat_args(m), k_tok);
+}
+hipError_t run_gated(const sd2_matrix_t* m, const uint16_t* x, int k_tok, uint16_t* out, hipStream_t s) {
+    WidePlan p;
+    if (wide_gated_choice(m, k_tok, &p)) return launch_wide_linear(mat_args(m), is_nm24(m), x, k_tok, out, true, p, s);
+    return launch_sparse_strip_gated(mat_args(m), x, k_tok, out, s);
+}
 
-hipError_t run_linear(const sd2_matrix_t* m, const uint16_t* x, int k_tok, float* out, hipStream_t s, bool allow_final = true) {
+// Partial results run_linear leaves in `out` for this token count (1: final values).  Never more than n_partials(m) for
+// kFinal, which sizes the buffers.
+inline int n_splits(const sd2_matrix_t* m, int k_tok, LinUse use) {
+    WidePlan p;
+    if (wide_choice(m, k_tok, use, &p)) return p.n_split;
+    return sparse_final_ok(m, k_tok) ? 1 : n_partials(m);
+}
+
+// Bytes of the partial results of a linear inside a stack.
+size_t stack_partial_bytes(const sd2_matrix_t* m, int k_tok) {
+    return std::max(partial_bytes(m, k_tok), (size_t)n_splits(m, k_tok, kStack) * k_tok * m->info.n_out * sizeof(float));
+}
+
+hipError_t run_linear(const sd2_matrix_t* m, const uint16_t* x, int k_tok, float* out, hipStream_t s, LinUse use, bool allow_final = true) {
     MatArgs ma = mat_args(m);
+    WidePlan wp;
+    if (allow_final && wide_choice(m, k_tok, use, &wp)) return launch_wide_linear(ma, is_nm24(m), x, k_tok, out, false, wp, s);
     if (allow_final && sparse_final_ok(m, k_tok)) {
         LinArgs la{x, k_tok, out};
         return launch_sparse_strip_linear(ma, la, s);
@@ -123,8 +157,7 @@ hipError_t run_linear(const sd2_matrix_t* m, const uint16_t* x, int k_tok, float
         }
         return hipSuccess;
     }
-    if (is_dense_stream(m))  // one launch; 32 tokens per pass where two groups' activations fit the registers, else 16
-        return launch_dense_stream_linear(ma.w, x, ma.n_out, ma.k_in, k_tok, out, s);
+    if (is_dense_stream(m)) return launch_dense_stream_linear(ma.w, x, ma.n_out, ma.k_in, k_tok, out, s);
     LinArgs la{x, k_tok, out};
     if (m->kind == SD2_KIND_SPARSE && option(SD2_OPT_LINEAR_PARTIALS) == 2 && sparse_linear_valu_supported(ma, k_tok))
         return launch_sparse_linear_valu(ma, la, s);  // the measurement variant without matrix instructions
@@ -143,12 +176,12 @@ int linear_entry(const sd2_matrix_t* m, int kind, const uint16_t* x, int32_t k_t
         if (!ws) return SD2_ERR_NULL;
         if (!aligned16(ws) || ws_bytes < partial_bytes(m, k_tok)) return SD2_ERR_BUFFER;
     }
-    if (n_splits(m, k_tok) == 1) {
-        return run_linear(m, x, k_tok, y, s) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
+    if (n_splits(m, k_tok, kFinal) == 1) {
+        return run_linear(m, x, k_tok, y, s, kFinal) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
     }
     float* part = static_cast<float*>(ws);
-    if (run_linear(m, x, k_tok, part, s) != hipSuccess) return SD2_ERR_HIP;
-    if (launch_reduce_partials(part, n_partials(m), (size_t)k_tok * m->info.n_out, y, s) != hipSuccess)
+    if (run_linear(m, x, k_tok, part, s, kFinal) != hipSuccess) return SD2_ERR_HIP;
+    if (launch_reduce_partials(part, n_splits(m, k_tok, kFinal), (size_t)k_tok * m->info.n_out, y, s) != hipSuccess)
         return SD2_ERR_HIP;
     return SD2_OK;
 }
@@ -163,7 +196,7 @@ StackLayout stack_layout(const sd2_model* md, int k_tok) {
     const size_t widest = (size_t)std::max(std::max(sh.hidden, sh.q_out), sh.inter);
     L.act_off = 0;
     size_t part = 0;
-    for (const sd2_matrix_t& m : md->mats) part = std::max(part, partial_bytes(&m, k_tok));
+    for (const sd2_matrix_t& m : md->mats) part = std::max(part, stack_partial_bytes(&m, k_tok));
     L.act2_off = align256((size_t)k_tok * widest * sizeof(uint16_t));
     L.part_off = 2 * L.act2_off;
     L.ssq_off = L.part_off + align256(part);
@@ -324,7 +357,7 @@ int sd2_sparse_linear_partials(const sd2_matrix_t* m, const uint16_t* x, int32_t
     if (!x || !part) return SD2_ERR_NULL;
     if ((rc = check_tokens(k_tok)) != SD2_OK) return rc;
     if (!aligned16(x) || !aligned16(part) || part_bytes < partial_bytes(m, k_tok)) return SD2_ERR_BUFFER;
-    return run_linear(m, x, k_tok, part, static_cast<hipStream_t>(stream), /*allow_final=*/false) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
+    return run_linear(m, x, k_tok, part, static_cast<hipStream_t>(stream), kFinal, /*allow_final=*/false) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
 }
 
 int sd2_dense_linear(const sd2_matrix_t* m, const uint16_t* x, int32_t k_tok, float* y, void* ws, size_t ws_bytes,
@@ -364,14 +397,14 @@ int sd2_sparse_mlp_forward(const sd2_matrix_t* gu, const sd2_matrix_t* dn, const
     uint16_t* act = static_cast<uint16_t*>(ws);
     float* part = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + align256((size_t)k_tok * inter * sizeof(uint16_t)));
     if (gated_ok(gu, k_tok)) {
-        if (launch_sparse_strip_gated(mat_args(gu), x, k_tok, act, s) != hipSuccess) return SD2_ERR_HIP;
+        if (run_gated(gu, x, k_tok, act, s) != hipSuccess) return SD2_ERR_HIP;
     } else {
-        if (run_linear(gu, x, k_tok, part, s) != hipSuccess) return SD2_ERR_HIP;
-        if (launch_silu_mul(part, n_splits(gu, k_tok), k_tok, inter, act, s) != hipSuccess) return SD2_ERR_HIP;
+        if (run_linear(gu, x, k_tok, part, s, kFinal) != hipSuccess) return SD2_ERR_HIP;
+        if (launch_silu_mul(part, n_splits(gu, k_tok, kFinal), k_tok, inter, act, s) != hipSuccess) return SD2_ERR_HIP;
     }
-    if (n_splits(dn, k_tok) == 1) return run_linear(dn, act, k_tok, y, s) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
-    if (run_linear(dn, act, k_tok, part, s) != hipSuccess) return SD2_ERR_HIP;
-    if (launch_reduce_partials(part, n_splits(dn, k_tok), (size_t)k_tok * dn->info.n_out, y, s) != hipSuccess)
+    if (n_splits(dn, k_tok, kFinal) == 1) return run_linear(dn, act, k_tok, y, s, kFinal) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
+    if (run_linear(dn, act, k_tok, part, s, kFinal) != hipSuccess) return SD2_ERR_HIP;
+    if (launch_reduce_partials(part, n_splits(dn, k_tok, kFinal), (size_t)k_tok * dn->info.n_out, y, s) != hipSuccess)
         return SD2_ERR_HIP;
     return SD2_OK;
 }
@@ -544,25 +577,25 @@ static int forward_impl(const sd2_model_t* md, const uint16_t* h_in, int32_t k_t
         const sd2_matrix_t* gu = &md->mats[4 * l + 2];
         const sd2_matrix_t* dn = &md->mats[4 * l + 3];
         SD2_TRY(record(4 * l + 0, h, nullptr, 0, sh.hidden, sh.hidden));
-        SD2_TRY(run_linear(qkv, act, k_tok, part, s));
-        SD2_TRY(launch_inflight_attention(part, n_splits(qkv, k_tok), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv,
+        SD2_TRY(run_linear(qkv, act, k_tok, part, s, kStack));
+        SD2_TRY(launch_inflight_attention(part, n_splits(qkv, k_tok, kStack), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv,
                                           sh.head_dim, act, s));
-        SD2_TRY(record(4 * l + 1, nullptr, part, n_splits(qkv, k_tok), sh.q_out + 2 * sh.kv_out, sh.q_out));
-        SD2_TRY(run_linear(o, act, k_tok, part, s));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok), k_tok, sh.hidden, act, ssq, s));
+        SD2_TRY(record(4 * l + 1, nullptr, part, n_splits(qkv, k_tok, kStack), sh.q_out + 2 * sh.kv_out, sh.q_out));
+        SD2_TRY(run_linear(o, act, k_tok, part, s, kStack));
+        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok, kStack), k_tok, sh.hidden, act, ssq, s));
         SD2_TRY(record(4 * l + 2, h, nullptr, 0, sh.hidden, sh.hidden));
         if (!trace && gated_ok(gu, k_tok)) {
             // one launch: the gated product is written by the linear's own epilogue (act is read and written: the
             // kernel has taken its input columns into registers before the first result leaves)
-            SD2_TRY(launch_sparse_strip_gated(mat_args(gu), act, k_tok, act2, s));
+            SD2_TRY(run_gated(gu, act, k_tok, act2, s));
             std::swap(act, act2);
         } else {
-            SD2_TRY(run_linear(gu, act, k_tok, part, s));
-            SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok), k_tok, sh.inter, act, s));
+            SD2_TRY(run_linear(gu, act, k_tok, part, s, kStack));
+            SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok, kStack), k_tok, sh.inter, act, s));
         }
-        SD2_TRY(record(4 * l + 3, nullptr, part, n_splits(gu, k_tok), 2 * sh.inter, sh.inter));
-        SD2_TRY(run_linear(dn, act, k_tok, part, s));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok), k_tok, sh.hidden,
+        SD2_TRY(record(4 * l + 3, nullptr, part, n_splits(gu, k_tok, kStack), 2 * sh.inter, sh.inter));
+        SD2_TRY(run_linear(dn, act, k_tok, part, s, kStack));
+        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok, kStack), k_tok, sh.hidden,
                                         l + 1 < sh.layers ? act : nullptr, ssq, s));
     }
 #undef SD2_TRY
@@ -714,21 +747,21 @@ int sd2_sparse_drafter_decode(const sd2_model_t* md, const uint16_t* h_in, int32
         const sd2_matrix_t* dn = &md->mats[4 * l + 3];
         uint16_t* kc = k_cache + (size_t)l * layer_elems;
         uint16_t* vc = v_cache + (size_t)l * layer_elems;
-        SD2_TRY(run_linear(qkv, act, k_tok, part, s));
-        SD2_TRY(launch_rope_append(part, n_splits(qkv, k_tok), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv, sh.head_dim, table,
+        SD2_TRY(run_linear(qkv, act, k_tok, part, s, kStack));
+        SD2_TRY(launch_rope_append(part, n_splits(qkv, k_tok, kStack), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv, sh.head_dim, table,
                                    pos0, max_pos, q_rot, kc, vc, s));
         SD2_TRY(launch_cached_attention(q_rot, kc, vc, max_pos, pos0, k_tok, sh.q_out, sh.n_heads, sh.n_kv, sh.head_dim, act, s));
-        SD2_TRY(run_linear(o, act, k_tok, part, s));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok), k_tok, sh.hidden, act, ssq, s));
+        SD2_TRY(run_linear(o, act, k_tok, part, s, kStack));
+        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok, kStack), k_tok, sh.hidden, act, ssq, s));
         if (gated_ok(gu, k_tok)) {
-            SD2_TRY(launch_sparse_strip_gated(mat_args(gu), act, k_tok, act2, s));
+            SD2_TRY(run_gated(gu, act, k_tok, act2, s));
             std::swap(act, act2);
         } else {
-            SD2_TRY(run_linear(gu, act, k_tok, part, s));
-            SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok), k_tok, sh.inter, act, s));
+            SD2_TRY(run_linear(gu, act, k_tok, part, s, kStack));
+            SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok, kStack), k_tok, sh.inter, act, s));
         }
-        SD2_TRY(run_linear(dn, act, k_tok, part, s));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok), k_tok, sh.hidden,
+        SD2_TRY(run_linear(dn, act, k_tok, part, s, kStack));
+        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok, kStack), k_tok, sh.hidden,
                                         l + 1 < sh.layers ? act : nullptr, ssq, s));
     }
 #undef SD2_TRY

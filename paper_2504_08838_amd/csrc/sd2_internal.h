@@ -93,6 +93,18 @@ hipError_t launch_calibration_copy(void* dst, const void* src, size_t bytes, hip
 // pure read of src[0..bytes): one checksum word per workgroup goes to sink[0..2048)
 hipError_t launch_calibration_read(const void* src, size_t bytes, uint32_t* sink, hipStream_t s);
 
+// ---- linears on 17 to 64 tokens (bitmask, 2:4 and dense)
+constexpr int kWideMaxSplit = 16;
+struct WidePlan {
+    int n_split;        // partial results [n_split][k_tok][n_out] (1: final values)
+    int n_pass, waves, wk, sg, strips_per_wg, n_wg, n_units;
+};
+// max_split: partial results that the caller has room for; free_add: its next kernel adds them anyway.  gated: [gate; up]
+// rows in, bf16(silu(gate x) * (up x)) out (only with max_split 1).
+bool wide_plan(int n_out, int k_in, int n_strips, int k_tok, bool gated, int max_split, bool free_add, WidePlan* out);
+hipError_t launch_wide_linear(const MatArgs& m, bool nm24, const uint16_t* x, int k_tok, void* out, bool gated, const WidePlan& p,
+                              hipStream_t s);
+
 }  // namespace sd2
 
 namespace sd2 {
@@ -178,7 +190,5 @@ hipError_t launch_lm_head(const uint16_t* w, const float* h, int vocab, int hidd
 hipError_t launch_dense_stream_linear(const uint16_t* w, const uint16_t* x, int n_out, int k_in, int k_tok, float* y,
                                       hipStream_t s);
 inline bool dense_stream_ok(int k_in) { return k_in % 128 == 0 && k_in <= kLmMaxHidden; }
-// up to 4096 columns the kernel takes 32 tokens per pass
-inline bool dense_stream_pair_ok(int k_in) { return dense_stream_ok(k_in) && k_in <= 4096; }
 
 }  // namespace sd2

@@ -1,0 +1,67 @@
+"""The kernel for 17 to 64 tokens at the edges of its tiling -- ragged rows and columns, one strip, odd unit counts, halves of
+tiles denser than its staging, every token group -- on all three formats."""
+import numpy as np
+import pytest
+
+import sd2_workload as wl
+from oracle import linear as ol
+from oracle import stack as os_
+
+pytestmark = pytest.mark.gpu
+
+
+def _ints(a):
+    return wl.f32_to_bf16_bits(np.asarray(a, dtype=np.float32))
+
+
+def _matrix(rng, n, k, fmt):
+    w = rng.integers(-8, 9, size=(n, k))
+    if fmt == "2:4":
+        drop = rng.permuted(np.broadcast_to(np.array([True, True, False, False]), (n, k // 4, 4)), axis=2)
+        w[drop.reshape(n, k)] = 0
+    elif fmt == "bitmask":
+        w[rng.random((n, k)) < 0.5] = 0
+    elif fmt == "crowded":  # every tile's values in one half of it, far more than the staged part holds
+        w[:, (np.arange(k) // 128) % 2 == (1 if n % 2 else 0)] = 0
+    return w
+
+
+@pytest.mark.parametrize("fmt", ["bitmask", "crowded", "2:4", "dense"])
+@pytest.mark.parametrize("n,k,k_tok", [
+    (16, 64, 17),       # one strip, half a unit
+    (33, 192, 64),      # ragged rows, one unit and a half
+    (333, 320, 33),     # n_out not a multiple of 4: scalar stores
+    (4112, 1536, 32),   # more strips than one group per workgroup, ragged last block
+    (96, 8960, 49),     # a long contraction: split over workgroups or passes
+])
+def test_wide_linear_exact_integers(n, k, k_tok, fmt):
+    import gpu_util as gu
+    rng = np.random.default_rng([5, n, k, k_tok])
+    w = _matrix(rng, n, k, fmt)
+    x = rng.integers(-4, 5, size=(k_tok, k))
+    mat = gu.DenseMat(_ints(w)) if fmt == "dense" else gu.SparseMat(_ints(w), 3 if fmt == "2:4" else 1)
+    y = gu.run_linear(mat, _ints(x), sparse=fmt != "dense")
+    assert np.array_equal(y.astype(np.int64), x @ w.T)
+
+
+@pytest.mark.parametrize("fmt", ["2:4", "dense"])
+@pytest.mark.parametrize("hidden,inter,k_tok", [(192, 48, 17), (512, 1200, 64)])
+def test_wide_mlp_gated(hidden, inter, k_tok, fmt):
+    import torch
+    import paper_2504_08838_amd as sd2
+    import gpu_util as gu
+    pattern = dict(pattern="2:4") if fmt == "2:4" else {}
+    inter = (inter + 63) // 64 * 64
+    wg, wu, wd = (wl.gen_weight(2, 1, p, n, k, 50, **pattern) for p, n, k in (("gate", inter, hidden), ("up", inter, hidden), ("down", hidden, inter)))
+    x_bits = wl.gen_x(2, 1, "gate", k_tok, hidden)
+    ref, _ = os_.mlp_block(wg, wu, wd, x_bits)
+    mk = gu.DenseMat if fmt == "dense" else (lambda w: gu.SparseMat(w, 3))
+    g_u, dn = mk(np.concatenate([wg, wu], axis=0)), mk(wd)
+    x = gu.dev(x_bits)
+    y = torch.full((k_tok, hidden), float("nan"), dtype=torch.float32, device="cuda")
+    nb = sd2.mlp_workspace_size(g_u.m, dn.m, k_tok)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    sd2.sparse_mlp_forward(g_u.m, dn.m, x.data_ptr(), k_tok, y.data_ptr(), ws.data_ptr(), nb, gu.stream_ptr())
+    torch.cuda.synchronize()
+    assert ol.rel_l2(y.cpu().numpy(), ref) <= 2e-3
+
