@@ -59,6 +59,12 @@ hipError_t launch_residual_rmsnorm(float* h, const uint16_t* h_in, const float* 
 hipError_t launch_inflight_attention(const float* part, int n_splits, int k_tok, int q_out, int kv_out,
                                      int n_heads, int n_kv, int head_dim, uint16_t* ctx, hipStream_t s);
 
+// The two attention steps for head_dim 128 on the matrix cores, sixteen query rows at a time.
+hipError_t launch_inflight_attention_wide(const float* part, int n_splits, int k_tok, int q_out, int kv_out, int n_heads, int n_kv,
+                                          uint16_t* ctx, hipStream_t s);
+hipError_t launch_cached_attention_wide(const float* q_rot, const uint16_t* k_cache, const uint16_t* v_cache, int max_pos, int pos0, int k_tok,
+                                        int q_out, int n_heads, int n_kv, uint16_t* ctx, hipStream_t s);
+
 // m[t][j] = bf16( silu(g) * u ), g = sum_s part[s][t][j], u = sum_s part[s][t][inter + j]
 hipError_t launch_silu_mul(const float* part, int n_splits, int k_tok, int inter, uint16_t* m, hipStream_t s);
 

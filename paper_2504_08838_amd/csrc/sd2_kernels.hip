@@ -1032,6 +1032,7 @@ __global__ __launch_bounds__(128) void inflight_attention_kernel(const float* __
 hipError_t launch_inflight_attention(const float* part, int n_splits, int k_tok, int q_out, int kv_out, int n_heads,
                                      int n_kv, int head_dim, uint16_t* ctx, hipStream_t s) {
     if (k_tok < 1 || k_tok > 64 || head_dim < 8 || head_dim > 256 || head_dim % 8) return hipErrorInvalidValue;
+    if (head_dim == 128 && k_tok > 8) return launch_inflight_attention_wide(part, n_splits, k_tok, q_out, kv_out, n_heads, n_kv, ctx, s);
     hipLaunchKernelGGL(inflight_attention_kernel, dim3((unsigned)n_heads, (unsigned)k_tok), dim3(128), 0, s, part, n_splits, k_tok,
                        q_out, kv_out, n_heads, n_kv, head_dim, ctx);
     return hipGetLastError();
@@ -1265,6 +1266,7 @@ hipError_t launch_cached_attention(const float* q_rot, const uint16_t* k_cache, 
                                    int k_tok, int q_out, int n_heads, int n_kv, int head_dim, uint16_t* ctx, hipStream_t s) {
     if (!cached_attention_supported(n_heads, n_kv, head_dim, max_pos) || pos0 < 0 || pos0 + k_tok > max_pos)
         return hipErrorInvalidValue;
+    if (head_dim == 128) return launch_cached_attention_wide(q_rot, k_cache, v_cache, max_pos, pos0, k_tok, q_out, n_heads, n_kv, ctx, s);
     const int rep = n_heads / n_kv;
     // register arrays are sized for 4 or 8 query heads per key/value head
 #define SD2_ATT_CASE(L) \
@@ -1272,7 +1274,6 @@ hipError_t launch_cached_attention(const float* q_rot, const uint16_t* k_cache, 
         return rep <= 4 ? launch_cached_attention_t<L, 4>(q_rot, k_cache, v_cache, max_pos, pos0, k_tok, q_out, rep, n_kv, ctx, s) \
                         : launch_cached_attention_t<L, 8>(q_rot, k_cache, v_cache, max_pos, pos0, k_tok, q_out, rep, n_kv, ctx, s)
     SD2_ATT_CASE(8);
-    SD2_ATT_CASE(16);
     SD2_ATT_CASE(32);
 #undef SD2_ATT_CASE
     return hipErrorInvalidValue;

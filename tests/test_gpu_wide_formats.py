@@ -1,9 +1,12 @@
 """The kernel for 17 to 64 tokens at the edges of its tiling -- ragged rows and columns, one strip, odd unit counts, halves of
-tiles denser than its staging, every token group -- on all three formats."""
+tiles denser than its staging, every token group -- on all three formats, and the attention kernels behind it."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 
 import sd2_workload as wl
+from oracle import decode as od
 from oracle import linear as ol
 from oracle import stack as os_
 
@@ -65,3 +68,35 @@ def test_wide_mlp_gated(hidden, inter, k_tok, fmt):
     torch.cuda.synchronize()
     assert ol.rel_l2(y.cpu().numpy(), ref) <= 2e-3
 
+
+SHAPE = SimpleNamespace(layers=2, hidden=768, q_out=768, kv_out=128, inter=640, n_heads=6, n_kv=1, head_dim=128)
+
+
+@pytest.mark.parametrize("k_tok", [9, 16, 17, 33, 64])
+def test_wide_inflight_attention(k_tok):
+    import gpu_util as gu
+    from test_gpu_decode import _model
+    get, model = _model(SHAPE, 41)
+    h = wl.gen_x(41, 0, "q", k_tok, SHAPE.hidden)
+    assert ol.rel_l2(gu.run_forward(model, h, SHAPE.hidden), os_.drafter_forward(SHAPE, get, h)) <= 1e-3
+
+
+@pytest.mark.parametrize("k_tok,pos0", [(1, 0), (3, 31), (17, 255), (33, 256), (64, 1000)])
+def test_wide_cached_attention(k_tok, pos0, sd2_options):
+    """Histories around the tiles of 32 positions and the 256 of a workgroup's pass, six query heads per key/value head."""
+    import gpu_util as gu
+    from test_gpu_decode import _cache_close, _decode, _model, THETA
+    sd2_options.set("forward_multi", 1)
+    get, model = _model(SHAPE, 43)
+    max_pos = pos0 + k_tok + 5
+    rng = np.random.default_rng([43, k_tok, pos0])
+    kc, vc = (wl.f32_to_bf16_bits(rng.standard_normal((SHAPE.layers, SHAPE.n_kv, max_pos, 128)).astype(np.float32)) for _ in range(2))
+    h = wl.gen_x(43, 0, "q", k_tok, SHAPE.hidden)
+    kd, vd = gu.dev(kc), gu.dev(vc)
+    out = _decode(model, SHAPE, h, kd, vd, max_pos, pos0)
+    ref_k, ref_v = kc.copy(), vc.copy()
+    ref = od.drafter_decode(SHAPE, get, h, ref_k, ref_v, pos0, THETA)
+    assert ol.rel_l2(out, ref) <= 1e-3
+    # the first layer's rows: the second's inputs already differ by bf16 roundings that went the other way
+    _cache_close(kd.cpu().numpy().view(np.uint16)[:1], ref_k[:1])
+    _cache_close(vd.cpu().numpy().view(np.uint16)[:1], ref_v[:1])
