@@ -57,3 +57,21 @@ def test_zero_sparsity_changes_nothing_and_full_sparsity_clears_everything():
     dense = wl.gen_weight_dense(94, 0, "q", 32, 256)
     assert np.array_equal(_run(dense, g, False), np.where(ol.nonzero_mask(dense), g, 0))
     assert not _run(np.zeros((32, 256), dtype=np.uint16), g, False).any()
+
+
+@pytest.mark.parametrize("is_bf16", [False, True])
+@pytest.mark.parametrize("n,k", [(1, 64), (8, 256), (9, 192), (17, 448), (31, 1088), (40, 2304)])
+def test_edges_of_tiles_and_workgroups_bit_exact(n, k, is_bf16):
+    """Rows around half strips and strips, columns around slabs, one to nine slabs; neighbours of the buffer stay as they are."""
+    import torch
+    import paper_2504_08838_amd as sd2
+    import gpu_util as gu
+    w = wl.gen_weight(95, 0, "q", n, k, 50)
+    g = np.random.default_rng(95).standard_normal((n + 2, k)).astype(np.float32)
+    g = wl.f32_to_bf16_bits(g) if is_bf16 else g
+    mat, d = gu.SparseMat(w, 1), gu.dev(g)
+    sd2.mask_gradient(mat.m, d[1:].data_ptr(), is_bf16, gu.stream_ptr())
+    torch.cuda.synchronize()
+    out, ref = d.cpu().numpy().view(g.dtype), g.copy()
+    ref[1:-1] = np.where(ol.nonzero_mask(w), ref[1:-1], ref.dtype.type(0))
+    assert np.array_equal(out.view(np.uint8), ref.view(np.uint8))
