@@ -81,6 +81,19 @@ def test_wide_inflight_attention(k_tok):
     assert ol.rel_l2(gu.run_forward(model, h, SHAPE.hidden), os_.drafter_forward(SHAPE, get, h)) <= 1e-3
 
 
+@pytest.mark.parametrize("hidden", [64, 1088, 4096, 4160, 8256])
+@pytest.mark.parametrize("k_tok", [5, 20])
+def test_residual_norm_widths(hidden, k_tok, sd2_options):
+    """Less than a wavefront's columns, a ragged last wavefront, one to four pieces per thread; one and several partial results."""
+    import gpu_util as gu
+    from test_gpu_decode import _model
+    sd2_options.set("forward_multi", 1)
+    shape = SimpleNamespace(layers=1, hidden=hidden, q_out=256, kv_out=128, inter=1024, n_heads=2, n_kv=1, head_dim=128)
+    get, model = _model(shape, 47)
+    h = wl.gen_x(47, 0, "q", k_tok, hidden)
+    assert ol.rel_l2(gu.run_forward(model, h, hidden), os_.drafter_forward(shape, get, h)) <= 1e-3
+
+
 @pytest.mark.parametrize("k_tok,pos0", [(1, 0), (3, 31), (17, 255), (33, 256), (64, 1000)])
 def test_wide_cached_attention(k_tok, pos0, sd2_options):
     """Histories around the tiles of 32 positions and the 256 of a workgroup's pass, six query heads per key/value head."""
