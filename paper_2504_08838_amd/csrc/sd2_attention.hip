@@ -14,6 +14,14 @@ namespace sd2 {
 
 constexpr int kAttD = 128;
 
+// A row's weight for a position that it does not attend to is zero, and the matrix instruction multiplies it all the same:
+// an infinity or NaN in a value of a later token would reach the earlier ones.  So a wavefront whose sums are not all finite
+// adds them again on the vector ALU, attended positions only (nothing is paid for that while all is finite).
+__device__ __forceinline__ bool finite4(const f32x4& v) {
+    constexpr float kMax = 3.402823466e38f;
+    return fabsf(v[0]) <= kMax && fabsf(v[1]) <= kMax && fabsf(v[2]) <= kMax && fabsf(v[3]) <= kMax;
+}
+
 // ------------------------------------------------------------------ among the call's own tokens (up to 64)
 //
 // Workgroup (head, 16 queries): keys and values 0 .. last query as fp32 in LDS (summed from the split-K partials on the way),
@@ -114,6 +122,17 @@ __global__ __launch_bounds__(kInThreads) void inflight_attention_wide_kernel(con
         const float p = sc[n * 68 + j + g];
         o0 = __builtin_amdgcn_mfma_f32_16x16x4f32(p, vp[(j + g) * kInRow], o0, 0, 0, 0);
         o1 = __builtin_amdgcn_mfma_f32_16x16x4f32(p, vp[(j + g) * kInRow + 16], o1, 0, 0, 0);
+    }
+    if (__any(!finite4(o0) || !finite4(o1))) {
+        o0 = o1 = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < n_keys; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (j <= 16 * qt + 4 * g + v) {
+                    const float p = sc[(4 * g + v) * 68 + j];
+                    o0[v] += p * vp[j * kInRow];
+                    o1[v] += p * vp[j * kInRow + 16];
+                }
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -285,6 +304,45 @@ __global__ __launch_bounds__(64 * kCaWaves) void cached_attention_wide_kernel(co
         }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_wave_barrier();  // the next tile overwrites both buffers
+    }
+    bool finite = true;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) finite = finite && finite4(o[d]);
+    if (__any(!finite)) {  // maxima and sums stand: they come from attended scores only
+#pragma unroll
+        for (int d = 0; d < 8; ++d) o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int base = 32 * wave; base < n_pos; base += 32 * kCaWaves) {
+            const int n_here = min(32, n_pos - base);
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const uint16_t* src = kg + (size_t)min(base + 16 * b + n, n_pos - 1) * kAttD + 8 * g;
+                f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 2; k >= 0; --k)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        Frag kf;
+                        kf.q = *reinterpret_cast<const u32x4*>(src + 32 * i);
+                        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q[i][k].v, kf.v, s, 0, 0, 0);
+                    }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) pbuf[(4 * g + v) * kCaPRow + 16 * b + n] = expf(s[v] - m[v]);
+            }
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_wave_barrier();
+            for (int j = 0; j < n_here; ++j) {
+                const uint16_t* src = vg + (size_t)(base + j) * kAttD + n;
+#pragma unroll
+                for (int d = 0; d < 8; ++d) {
+                    const float x = __uint_as_float((uint32_t)src[16 * d] << 16);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (base + j <= last[v]) o[d][v] += pbuf[(4 * g + v) * kCaPRow + j] * x;
+                }
+            }
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_wave_barrier();
+        }
     }
     __syncthreads();
     float* om = reinterpret_cast<float*>(ca_smem);       // [waves][16][kCaORow]

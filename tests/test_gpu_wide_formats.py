@@ -113,3 +113,29 @@ def test_wide_cached_attention(k_tok, pos0, sd2_options):
     # the first layer's rows: the second's inputs already differ by bf16 roundings that went the other way
     _cache_close(kd.cpu().numpy().view(np.uint16)[:1], ref_k[:1])
     _cache_close(vd.cpu().numpy().view(np.uint16)[:1], ref_v[:1])
+
+
+@pytest.mark.parametrize("k_tok,bad", [(12, 10), (40, 37), (64, 0)])
+@pytest.mark.parametrize("pos0", [None, 0, 40])
+def test_a_token_that_is_not_finite_leaves_the_earlier_ones_alone(k_tok, bad, pos0, sd2_options):
+    """Causal attention: tokens before the bad one come out as without it, the bad one and those after it are not finite."""
+    import gpu_util as gu
+    from test_gpu_decode import _decode, _model
+    sd2_options.set("forward_multi", 1)
+    get, model = _model(SHAPE, 53)
+    h = wl.gen_x(53, 0, "q", k_tok, SHAPE.hidden)
+    h_bad = h.copy()
+    h_bad[bad] = 0x7FC0  # NaN
+    max_pos = (pos0 or 0) + k_tok
+
+    def forward(x):
+        if pos0 is None:
+            return gu.run_forward(model, x, SHAPE.hidden)
+        rng = np.random.default_rng([53, pos0])
+        cache = [gu.dev(wl.f32_to_bf16_bits(rng.standard_normal((SHAPE.layers, SHAPE.n_kv, max_pos, 128)).astype(np.float32))) for _ in range(2)]
+        return _decode(model, SHAPE, x, *cache, max_pos, pos0)
+
+    got, clean = forward(h_bad), forward(h)
+    assert not np.isfinite(got[bad:]).any()
+    if bad:
+        assert ol.rel_l2(got[:bad], clean[:bad]) <= 1e-3
