@@ -244,7 +244,7 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
             for (int q = 0; q < 2; ++q) st.v[q] = *reinterpret_cast<const u32x4*>(src + 1024 * (2 * my_half + q) + (uint32_t)lane * 16u);
             st.idx = *reinterpret_cast<const uint32_t*>(src + 4096 + 4 * my_half + (uint32_t)lane * 8u);
         } else {
-            // columns past the matrix meet activations that are zero, rows past it are not written: any element of the row will do
+            // columns past the matrix are cleared at the use, rows past it are not written: any element of the row will do
             const bool on = live(r, i);
             const int col0 = on ? 128 * unit_at(r) : 0, row0 = on ? strip_of(ord_at(r, i)) * 16 : 0;
             const int col = min(col0, a.k_in - 64);
@@ -375,6 +375,8 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
         const bool unit_on = u < a.n_units;
         // (a plain select becomes a branch with copies of the masks, which wait for their loads)
         const uint32_t keep = (uint32_t)__builtin_amdgcn_readfirstlane(unit_on ? -1 : 0);
+        // dense: the absent half of the last unit is cleared (infinity times zero is not zero)
+        const uint32_t whole = (uint32_t)__builtin_amdgcn_readfirstlane(128 * u + 128 > a.k_in ? 0 : -1);
         if (u != have_b) {
             have_b = u;
             load_b(u);
@@ -439,6 +441,8 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
             } else {
                 u32x4 w[4] = {s.v[0], s.v[1], s.v[2], s.v[3]};
                 block_to_operands(w, buf, lane);
+                w[2] &= whole;
+                w[3] &= whole;
                 request(s, ahead, i, tl_next, parts_next);
                 asm volatile("" ::: "memory");
                 if (unit_on) {

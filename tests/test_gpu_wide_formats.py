@@ -139,3 +139,16 @@ def test_a_token_that_is_not_finite_leaves_the_earlier_ones_alone(k_tok, bad, po
     assert not np.isfinite(got[bad:]).any()
     if bad:
         assert ol.rel_l2(got[:bad], clean[:bad]) <= 1e-3
+
+
+@pytest.mark.parametrize("fmt", ["bitmask", "dense"])
+@pytest.mark.parametrize("k_tok", [5, 17, 64])
+def test_infinite_weight_stays_in_its_row(k_tok, fmt):
+    """The infinity sits in the first column of the last, half unit, whose absent columns are read as that one."""
+    import gpu_util as gu
+    rng = np.random.default_rng([59, k_tok])
+    w = rng.integers(1, 9, size=(40, 320)).astype(np.float32)
+    w[7, 256] = np.inf
+    x = rng.integers(1, 5, size=(k_tok, 320)).astype(np.float32)
+    mat = gu.DenseMat(_ints(w)) if fmt == "dense" else gu.SparseMat(_ints(w), 1)
+    assert np.array_equal(gu.run_linear(mat, _ints(x), sparse=fmt != "dense"), x @ w.T)
