@@ -103,23 +103,39 @@ inline bool sparse_final_ok(const sd2_matrix_t* m, int k_tok) {
 // partial results as it reads them (kStack; the stack's own workspace holds them for every format).
 enum LinUse { kFinal, kStack };
 
+inline bool strip_gated_ok(const sd2_matrix_t* m, int k_tok) {
+    return sparse_final_ok(m, k_tok) && sparse_strip_gated_supported(mat_args(m), k_tok);
+}
+
+// More than 16 tokens on a small matrix: passes of 16 tokens side by side in one launch of the kernel for 16 tokens, which
+// costs what 16 tokens cost while the compute units are not full.  The line lies where both sides take the same time.  Bitmask, in
+// expanded tiles: 1024 x 512 on 64 tokens 3.6 us against 6.8 in the wide kernel, 1024 x 2560 (2560 tiles) 6.4 against 9.6; 3072 x 1536
+// on 40 tokens (3456 tiles) 8.4 against 7.9.  Dense, a strip and pass per compute unit or its like in columns: 1024 x 2560 on 64
+// tokens 5.7 us against 11.3, 1536 x 1536 6.8 against 8.6; 3072 x 1536 on 17 tokens 6.0 against 5.7.  A 2:4 matrix, with nothing
+// to expand, is as fast in the wide kernel at every size.
+bool few_strips(const sd2_matrix_t* m, int k_tok) {
+    const int passes = (k_tok + 15) / 16;
+    const int64_t groups = (int64_t)m->info.n_strips * passes;
+    if (m->kind == SD2_KIND_DENSE) return is_dense_stream(m) && (groups <= 256 || groups * m->info.k_in <= (passes > 2 ? 384 * 1536 : 512 * 1024));
+    return sparse_final_ok(m, k_tok) && groups * m->info.n_slabs <= 2560;
+}
+
 // More than 16 tokens: the kernel that keeps the activations of all tokens in registers.  SD2_OPT_LINEAR_PARTIALS keeps
 // bitmask matrices on the kernel with one partial result per slab.
 bool wide_choice(const sd2_matrix_t* m, int k_tok, LinUse use, WidePlan* p) {
-    if (k_tok <= 16 || (m->kind == SD2_KIND_SPARSE && !is_nm24(m) && option(SD2_OPT_LINEAR_PARTIALS))) return false;
+    if (k_tok <= 16 || few_strips(m, k_tok) || (m->kind == SD2_KIND_SPARSE && !is_nm24(m) && option(SD2_OPT_LINEAR_PARTIALS))) return false;
     const int room = use == kStack ? kWideMaxSplit : n_partials(m);
     return wide_plan(m->info.n_out, m->info.k_in, m->info.n_strips, k_tok, false, room, use == kStack, p);
 }
 bool wide_gated_choice(const sd2_matrix_t* m, int k_tok, WidePlan* p) {
-    if (k_tok <= 16 || (m->kind == SD2_KIND_SPARSE && !is_nm24(m) && option(SD2_OPT_LINEAR_PARTIALS))) return false;
+    if (k_tok <= 16 || (few_strips(m, k_tok) && strip_gated_ok(m, k_tok)) || (m->kind == SD2_KIND_SPARSE && !is_nm24(m) && option(SD2_OPT_LINEAR_PARTIALS))) return false;
     return wide_plan(m->info.n_out, m->info.k_in, m->info.n_strips, k_tok, true, 1, false, p);
 }
 
 // The gate|up linear and the gated product in one launch (the kernels that add the slabs up inside the workgroup).
 inline bool gated_ok(const sd2_matrix_t* m, int k_tok) {
     WidePlan p;
-    if (k_tok > 16) return wide_gated_choice(m, k_tok, &p);
-    return sparse_final_ok(m, k_tok) && sparse_strip_gated_supported(mat_args(m), k_tok);
+    return (k_tok <= 16 || few_strips(m, k_tok)) && strip_gated_ok(m, k_tok) ? true : wide_gated_choice(m, k_tok, &p);
 }
 hipError_t run_gated(const sd2_matrix_t* m, const uint16_t* x, int k_tok, uint16_t* out, hipStream_t s) {
     WidePlan p;

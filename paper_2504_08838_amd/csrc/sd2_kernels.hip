@@ -244,8 +244,13 @@ constexpr int kStripRound = 4;  // strips (whole pairs of them) between two work
 template <int MAXCH, int SPW, int WAVES, bool GATED = false>
 __global__ __launch_bounds__(64 * WAVES) void sparse_strip_kernel(const DirEnt* __restrict__ dir, const uint2* __restrict__ masks,
                                                                  const uint16_t* __restrict__ vals,
-                                                                 const uint16_t* __restrict__ x, float* __restrict__ y,
-                                                                 int n_out, int k_in, int k_tok, int n_strips, int n_slabs) {
+                                                                 const uint16_t* __restrict__ x_all, float* __restrict__ y_all,
+                                                                 int n_out, int k_in, int k_tok_all, int n_strips, int n_slabs) {
+    // more than 16 tokens (matrices with few strips only): the grid's second dimension numbers passes of 16
+    const int pass = (int)blockIdx.y, k_tok = min(16, k_tok_all - 16 * pass);
+    const uint16_t* __restrict__ x = x_all + (size_t)pass * 16 * k_in;
+    float* __restrict__ y = GATED ? reinterpret_cast<float*>(reinterpret_cast<uint16_t*>(y_all) + (size_t)pass * 16 * (n_out / 2))
+                                  : y_all + (size_t)pass * 16 * n_out;
     extern __shared__ uint32_t strip_smem[];  // [WAVES][MAXCH * 256] tile buffers, then [kStripRound][WAVES][256] floats
     __shared__ uint2 lut[16];
     const int tid = threadIdx.x;
@@ -502,7 +507,7 @@ static bool strip_shape(int n_slabs, int& spw, int& waves) {
 
 bool sparse_strip_supported(const MatArgs& m, int k_tok) {
     int spw, waves;
-    return k_tok >= 1 && k_tok <= 16 && (m.max_tile_nnz * 2 + 8 + 1023) / 1024 <= 5 && strip_shape(m.n_slabs, spw, waves);
+    return k_tok >= 1 && k_tok <= 64 && (m.max_tile_nnz * 2 + 8 + 1023) / 1024 <= 5 && strip_shape(m.n_slabs, spw, waves);
 }
 
 template <int SPW, int WAVES, bool GATED = false>
@@ -520,12 +525,12 @@ static hipError_t launch_strip_t(const MatArgs& m, const LinArgs& a, hipStream_t
         cached.store(resident, std::memory_order_release);
     }
     const int grid = std::min(GATED ? m.n_strips / 2 : m.n_strips, resident);
-    hipLaunchKernelGGL((sparse_strip_kernel<kCh, SPW, WAVES, GATED>), dim3((unsigned)grid), dim3(64 * WAVES), lds, s,
+    hipLaunchKernelGGL((sparse_strip_kernel<kCh, SPW, WAVES, GATED>), dim3((unsigned)grid, (unsigned)((a.k_tok + 15) / 16)), dim3(64 * WAVES), lds, s,
                        static_cast<const DirEnt*>(m.dir), m.masks, m.vals, a.x, a.out, m.n_out, m.k_in, a.k_tok, m.n_strips, m.n_slabs);
     return hipGetLastError();
 }
 
-// y[t][n] final (every entry written), k_tok <= 16; sparse_strip_supported(m, k_tok) must hold
+// y[t][n] final (every entry written); sparse_strip_supported(m, k_tok) must hold
 hipError_t launch_sparse_strip_linear(const MatArgs& m, const LinArgs& a, hipStream_t s) {
     int spw, waves;
     if (!sparse_strip_supported(m, a.k_tok) || !strip_shape(m.n_slabs, spw, waves)) return hipErrorInvalidValue;

@@ -36,6 +36,10 @@ def _matrix(rng, n, k, fmt):
     (333, 320, 33),     # n_out not a multiple of 4: scalar stores
     (4112, 1536, 32),   # more strips than one group per workgroup, ragged last block
     (96, 8960, 49),     # a long contraction: split over workgroups or passes
+    (5003, 832, 49),    # ragged rows, six units and a half, too many strips for passes of 16 tokens
+    (2560, 1024, 64),   # 2560 tiles of a bitmask in passes of 16 tokens: the most (one strip more: the wide kernel)
+    (2576, 1024, 64),
+    (2048, 512, 33),    # dense: passes of 16 tokens
 ])
 def test_wide_linear_exact_integers(n, k, k_tok, fmt):
     import gpu_util as gu
@@ -47,7 +51,7 @@ def test_wide_linear_exact_integers(n, k, k_tok, fmt):
     assert np.array_equal(y.astype(np.int64), x @ w.T)
 
 
-@pytest.mark.parametrize("fmt", ["2:4", "dense"])
+@pytest.mark.parametrize("fmt", ["bitmask", "2:4", "dense"])
 @pytest.mark.parametrize("hidden,inter,k_tok", [(192, 48, 17), (512, 1200, 64)])
 def test_wide_mlp_gated(hidden, inter, k_tok, fmt):
     import torch
@@ -58,7 +62,7 @@ def test_wide_mlp_gated(hidden, inter, k_tok, fmt):
     wg, wu, wd = (wl.gen_weight(2, 1, p, n, k, 50, **pattern) for p, n, k in (("gate", inter, hidden), ("up", inter, hidden), ("down", hidden, inter)))
     x_bits = wl.gen_x(2, 1, "gate", k_tok, hidden)
     ref, _ = os_.mlp_block(wg, wu, wd, x_bits)
-    mk = gu.DenseMat if fmt == "dense" else (lambda w: gu.SparseMat(w, 3))
+    mk = gu.DenseMat if fmt == "dense" else (lambda w: gu.SparseMat(w, 3 if fmt == "2:4" else 1))
     g_u, dn = mk(np.concatenate([wg, wu], axis=0)), mk(wd)
     x = gu.dev(x_bits)
     y = torch.full((k_tok, hidden), float("nan"), dtype=torch.float32, device="cuda")
