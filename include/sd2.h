@@ -216,6 +216,7 @@ typedef struct sd2_model sd2_model_t; /* host-side metadata only; owned by the l
 int sd2_model_create(const sd2_model_shape_t* shape, const sd2_matrix_t* mats, int32_t n_mats,
                      sd2_model_t** out);
 int sd2_model_destroy(sd2_model_t* model);
+/* Among calls on more than 8 tokens the size for the most tokens serves all (here and for sd2_drafter_decode_workspace_size). */
 int sd2_drafter_workspace_size(const sd2_model_t* model, int32_t k_tok, size_t* bytes_out);
 /* h_in: device bf16 [k_tok][hidden]; h_out: device fp32 [k_tok][hidden]. */
 int sd2_sparse_drafter_forward(const sd2_model_t* model, const uint16_t* h_in_bf16_dev, int32_t k_tok,

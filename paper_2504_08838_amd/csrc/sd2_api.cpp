@@ -99,9 +99,30 @@ inline bool sparse_final_ok(const sd2_matrix_t* m, int k_tok) {
     return sparse_strip_supported(mat_args(m), k_tok);
 }
 
-// What happens to a linear's results: final values for the caller (kFinal), or the next kernel of a stack adds the
-// partial results as it reads them (kStack; the stack's own workspace holds them for every format).
-enum LinUse { kFinal, kStack };
+// Where a linear's results go: room for that many partial results of it, and whether the next kernel adds them as it reads
+// them (inside a stack).
+struct LinUse {
+    int room;
+    bool free_add;
+};
+inline LinUse final_use(const sd2_matrix_t* m) { return {n_partials(m), false}; }
+
+// Inside a stack all linears share one area of that many fp32 results per token: what the kernels with one partial result per slab
+// leave, and six partial results of the widest linear whose results another kernel adds (q|k|v, o, down).  It depends on
+// neither the token count nor a switch, so a workspace of a token count serves every smaller one.  Six, because the wide
+// kernel's plan asks for no more than that on decoder shapes of 512 to 3072 columns (a matrix with fewer rows has room for more).
+size_t stack_part_rows(const sd2_model* md) {
+    size_t rows = 0;
+    for (size_t i = 0; i < md->mats.size(); ++i) {
+        const size_t n_out = (size_t)md->mats[i].info.n_out;
+        rows = std::max(rows, n_out * n_partials(&md->mats[i]));
+        if (i % 4 != 2) rows = std::max(rows, n_out * 6);
+    }
+    return rows;
+}
+inline LinUse stack_use(const sd2_matrix_t* m, size_t part_rows) {
+    return {(int)std::min<size_t>(kWideMaxSplit, part_rows / (size_t)m->info.n_out), true};
+}
 
 inline bool strip_gated_ok(const sd2_matrix_t* m, int k_tok) {
     return sparse_final_ok(m, k_tok) && sparse_strip_gated_supported(mat_args(m), k_tok);
@@ -124,8 +145,7 @@ bool few_strips(const sd2_matrix_t* m, int k_tok) {
 // bitmask matrices on the kernel with one partial result per slab.
 bool wide_choice(const sd2_matrix_t* m, int k_tok, LinUse use, WidePlan* p) {
     if (k_tok <= 16 || few_strips(m, k_tok) || (m->kind == SD2_KIND_SPARSE && !is_nm24(m) && option(SD2_OPT_LINEAR_PARTIALS))) return false;
-    const int room = use == kStack ? kWideMaxSplit : n_partials(m);
-    return wide_plan(m->info.n_out, m->info.k_in, m->info.n_strips, k_tok, false, room, use == kStack, p);
+    return wide_plan(m->info.n_out, m->info.k_in, m->info.n_strips, k_tok, false, use.room, use.free_add, p);
 }
 bool wide_gated_choice(const sd2_matrix_t* m, int k_tok, WidePlan* p) {
     if (k_tok <= 16 || (few_strips(m, k_tok) && strip_gated_ok(m, k_tok)) || (m->kind == SD2_KIND_SPARSE && !is_nm24(m) && option(SD2_OPT_LINEAR_PARTIALS))) return false;
@@ -143,17 +163,11 @@ hipError_t run_gated(const sd2_matrix_t* m, const uint16_t* x, int k_tok, uint16
     return launch_sparse_strip_gated(mat_args(m), x, k_tok, out, s);
 }
 
-// Partial results run_linear leaves in `out` for this token count (1: final values).  Never more than n_partials(m) for
-// kFinal, which sizes the buffers.
+// Partial results run_linear leaves in `out` for this token count (1: final values).  Never more than use.room.
 inline int n_splits(const sd2_matrix_t* m, int k_tok, LinUse use) {
     WidePlan p;
     if (wide_choice(m, k_tok, use, &p)) return p.n_split;
     return sparse_final_ok(m, k_tok) ? 1 : n_partials(m);
-}
-
-// Bytes of the partial results of a linear inside a stack.
-size_t stack_partial_bytes(const sd2_matrix_t* m, int k_tok) {
-    return std::max(partial_bytes(m, k_tok), (size_t)n_splits(m, k_tok, kStack) * k_tok * m->info.n_out * sizeof(float));
 }
 
 hipError_t run_linear(const sd2_matrix_t* m, const uint16_t* x, int k_tok, float* out, hipStream_t s, LinUse use, bool allow_final = true) {
@@ -192,18 +206,19 @@ int linear_entry(const sd2_matrix_t* m, int kind, const uint16_t* x, int32_t k_t
         if (!ws) return SD2_ERR_NULL;
         if (!aligned16(ws) || ws_bytes < partial_bytes(m, k_tok)) return SD2_ERR_BUFFER;
     }
-    if (n_splits(m, k_tok, kFinal) == 1) {
-        return run_linear(m, x, k_tok, y, s, kFinal) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
+    if (n_splits(m, k_tok, final_use(m)) == 1) {
+        return run_linear(m, x, k_tok, y, s, final_use(m)) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
     }
     float* part = static_cast<float*>(ws);
-    if (run_linear(m, x, k_tok, part, s, kFinal) != hipSuccess) return SD2_ERR_HIP;
-    if (launch_reduce_partials(part, n_splits(m, k_tok, kFinal), (size_t)k_tok * m->info.n_out, y, s) != hipSuccess)
+    if (run_linear(m, x, k_tok, part, s, final_use(m)) != hipSuccess) return SD2_ERR_HIP;
+    if (launch_reduce_partials(part, n_splits(m, k_tok, final_use(m)), (size_t)k_tok * m->info.n_out, y, s) != hipSuccess)
         return SD2_ERR_HIP;
     return SD2_OK;
 }
 
 struct StackLayout {
     size_t act_off, act2_off, part_off, ssq_off, total;  // two activation buffers: a fused kernel reads one and writes the other
+    size_t part_rows;
 };
 
 StackLayout stack_layout(const sd2_model* md, int k_tok) {
@@ -211,8 +226,8 @@ StackLayout stack_layout(const sd2_model* md, int k_tok) {
     StackLayout L;
     const size_t widest = (size_t)std::max(std::max(sh.hidden, sh.q_out), sh.inter);
     L.act_off = 0;
-    size_t part = 0;
-    for (const sd2_matrix_t& m : md->mats) part = std::max(part, stack_partial_bytes(&m, k_tok));
+    L.part_rows = stack_part_rows(md);
+    const size_t part = L.part_rows * (size_t)k_tok * sizeof(float);
     L.act2_off = align256((size_t)k_tok * widest * sizeof(uint16_t));
     L.part_off = 2 * L.act2_off;
     L.ssq_off = L.part_off + align256(part);
@@ -373,7 +388,7 @@ int sd2_sparse_linear_partials(const sd2_matrix_t* m, const uint16_t* x, int32_t
     if (!x || !part) return SD2_ERR_NULL;
     if ((rc = check_tokens(k_tok)) != SD2_OK) return rc;
     if (!aligned16(x) || !aligned16(part) || part_bytes < partial_bytes(m, k_tok)) return SD2_ERR_BUFFER;
-    return run_linear(m, x, k_tok, part, static_cast<hipStream_t>(stream), kFinal, /*allow_final=*/false) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
+    return run_linear(m, x, k_tok, part, static_cast<hipStream_t>(stream), final_use(m), /*allow_final=*/false) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
 }
 
 int sd2_dense_linear(const sd2_matrix_t* m, const uint16_t* x, int32_t k_tok, float* y, void* ws, size_t ws_bytes,
@@ -415,12 +430,12 @@ int sd2_sparse_mlp_forward(const sd2_matrix_t* gu, const sd2_matrix_t* dn, const
     if (gated_ok(gu, k_tok)) {
         if (run_gated(gu, x, k_tok, act, s) != hipSuccess) return SD2_ERR_HIP;
     } else {
-        if (run_linear(gu, x, k_tok, part, s, kFinal) != hipSuccess) return SD2_ERR_HIP;
-        if (launch_silu_mul(part, n_splits(gu, k_tok, kFinal), k_tok, inter, act, s) != hipSuccess) return SD2_ERR_HIP;
+        if (run_linear(gu, x, k_tok, part, s, final_use(gu)) != hipSuccess) return SD2_ERR_HIP;
+        if (launch_silu_mul(part, n_splits(gu, k_tok, final_use(gu)), k_tok, inter, act, s) != hipSuccess) return SD2_ERR_HIP;
     }
-    if (n_splits(dn, k_tok, kFinal) == 1) return run_linear(dn, act, k_tok, y, s, kFinal) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
-    if (run_linear(dn, act, k_tok, part, s, kFinal) != hipSuccess) return SD2_ERR_HIP;
-    if (launch_reduce_partials(part, n_splits(dn, k_tok, kFinal), (size_t)k_tok * dn->info.n_out, y, s) != hipSuccess)
+    if (n_splits(dn, k_tok, final_use(dn)) == 1) return run_linear(dn, act, k_tok, y, s, final_use(dn)) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
+    if (run_linear(dn, act, k_tok, part, s, final_use(dn)) != hipSuccess) return SD2_ERR_HIP;
+    if (launch_reduce_partials(part, n_splits(dn, k_tok, final_use(dn)), (size_t)k_tok * dn->info.n_out, y, s) != hipSuccess)
         return SD2_ERR_HIP;
     return SD2_OK;
 }
@@ -593,12 +608,12 @@ static int forward_impl(const sd2_model_t* md, const uint16_t* h_in, int32_t k_t
         const sd2_matrix_t* gu = &md->mats[4 * l + 2];
         const sd2_matrix_t* dn = &md->mats[4 * l + 3];
         SD2_TRY(record(4 * l + 0, h, nullptr, 0, sh.hidden, sh.hidden));
-        SD2_TRY(run_linear(qkv, act, k_tok, part, s, kStack));
-        SD2_TRY(launch_inflight_attention(part, n_splits(qkv, k_tok, kStack), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv,
+        SD2_TRY(run_linear(qkv, act, k_tok, part, s, stack_use(qkv, L.part_rows)));
+        SD2_TRY(launch_inflight_attention(part, n_splits(qkv, k_tok, stack_use(qkv, L.part_rows)), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv,
                                           sh.head_dim, act, s));
-        SD2_TRY(record(4 * l + 1, nullptr, part, n_splits(qkv, k_tok, kStack), sh.q_out + 2 * sh.kv_out, sh.q_out));
-        SD2_TRY(run_linear(o, act, k_tok, part, s, kStack));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok, kStack), k_tok, sh.hidden, act, ssq, s));
+        SD2_TRY(record(4 * l + 1, nullptr, part, n_splits(qkv, k_tok, stack_use(qkv, L.part_rows)), sh.q_out + 2 * sh.kv_out, sh.q_out));
+        SD2_TRY(run_linear(o, act, k_tok, part, s, stack_use(o, L.part_rows)));
+        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok, stack_use(o, L.part_rows)), k_tok, sh.hidden, act, ssq, s));
         SD2_TRY(record(4 * l + 2, h, nullptr, 0, sh.hidden, sh.hidden));
         if (!trace && gated_ok(gu, k_tok)) {
             // one launch: the gated product is written by the linear's own epilogue (act is read and written: the
@@ -606,12 +621,12 @@ static int forward_impl(const sd2_model_t* md, const uint16_t* h_in, int32_t k_t
             SD2_TRY(run_gated(gu, act, k_tok, act2, s));
             std::swap(act, act2);
         } else {
-            SD2_TRY(run_linear(gu, act, k_tok, part, s, kStack));
-            SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok, kStack), k_tok, sh.inter, act, s));
+            SD2_TRY(run_linear(gu, act, k_tok, part, s, stack_use(gu, L.part_rows)));
+            SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok, stack_use(gu, L.part_rows)), k_tok, sh.inter, act, s));
         }
-        SD2_TRY(record(4 * l + 3, nullptr, part, n_splits(gu, k_tok, kStack), 2 * sh.inter, sh.inter));
-        SD2_TRY(run_linear(dn, act, k_tok, part, s, kStack));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok, kStack), k_tok, sh.hidden,
+        SD2_TRY(record(4 * l + 3, nullptr, part, n_splits(gu, k_tok, stack_use(gu, L.part_rows)), 2 * sh.inter, sh.inter));
+        SD2_TRY(run_linear(dn, act, k_tok, part, s, stack_use(dn, L.part_rows)));
+        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok, stack_use(dn, L.part_rows)), k_tok, sh.hidden,
                                         l + 1 < sh.layers ? act : nullptr, ssq, s));
     }
 #undef SD2_TRY
@@ -763,21 +778,21 @@ int sd2_sparse_drafter_decode(const sd2_model_t* md, const uint16_t* h_in, int32
         const sd2_matrix_t* dn = &md->mats[4 * l + 3];
         uint16_t* kc = k_cache + (size_t)l * layer_elems;
         uint16_t* vc = v_cache + (size_t)l * layer_elems;
-        SD2_TRY(run_linear(qkv, act, k_tok, part, s, kStack));
-        SD2_TRY(launch_rope_append(part, n_splits(qkv, k_tok, kStack), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv, sh.head_dim, table,
+        SD2_TRY(run_linear(qkv, act, k_tok, part, s, stack_use(qkv, L.part_rows)));
+        SD2_TRY(launch_rope_append(part, n_splits(qkv, k_tok, stack_use(qkv, L.part_rows)), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv, sh.head_dim, table,
                                    pos0, max_pos, q_rot, kc, vc, s));
         SD2_TRY(launch_cached_attention(q_rot, kc, vc, max_pos, pos0, k_tok, sh.q_out, sh.n_heads, sh.n_kv, sh.head_dim, act, s));
-        SD2_TRY(run_linear(o, act, k_tok, part, s, kStack));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok, kStack), k_tok, sh.hidden, act, ssq, s));
+        SD2_TRY(run_linear(o, act, k_tok, part, s, stack_use(o, L.part_rows)));
+        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok, stack_use(o, L.part_rows)), k_tok, sh.hidden, act, ssq, s));
         if (gated_ok(gu, k_tok)) {
             SD2_TRY(run_gated(gu, act, k_tok, act2, s));
             std::swap(act, act2);
         } else {
-            SD2_TRY(run_linear(gu, act, k_tok, part, s, kStack));
-            SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok, kStack), k_tok, sh.inter, act, s));
+            SD2_TRY(run_linear(gu, act, k_tok, part, s, stack_use(gu, L.part_rows)));
+            SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok, stack_use(gu, L.part_rows)), k_tok, sh.inter, act, s));
         }
-        SD2_TRY(run_linear(dn, act, k_tok, part, s, kStack));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok, kStack), k_tok, sh.hidden,
+        SD2_TRY(run_linear(dn, act, k_tok, part, s, stack_use(dn, L.part_rows)));
+        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok, stack_use(dn, L.part_rows)), k_tok, sh.hidden,
                                         l + 1 < sh.layers ? act : nullptr, ssq, s));
     }
 #undef SD2_TRY

@@ -321,6 +321,38 @@ def test_model_create_rejects_head_sizes_the_attention_kernels_cannot_split():
     L.sd2_model_destroy(handle)
 
 
+def _fake_stack(shape, fmt):
+    """A one-layer model of blobs at fake addresses: sizes only, nothing is launched."""
+    mats, keep = [], []
+    for n, k in ((shape.q_out + 2 * shape.kv_out, shape.hidden), (shape.hidden, shape.q_out), (2 * shape.inter, shape.hidden), (shape.hidden, shape.inter)):
+        if fmt == "dense":
+            mats.append(sd2.matrix_init_dense(0x1000, n, k))
+            continue
+        w = np.full((n, k), 0x3F80, dtype=np.uint16)
+        w[:, 1::2] = 0
+        keep.append(sd2.pack_sparse(w, 3 if fmt == "2:4" else 1))
+        mats.append(sd2.matrix_init_sparse(keep[-1], 0x1000))
+    return sd2.model_create(sd2.ModelShape(shape.layers, shape.hidden, shape.q_out, shape.kv_out, shape.inter, shape.n_heads, shape.n_kv, 128),
+                            mats, keep=keep)
+
+
+@pytest.mark.parametrize("heads,n_kv,inter,fmt", [(20, 4, 6912, "dense"), (13, 13, 4800, "dense"), (13, 13, 4800, "2:4"), (13, 13, 4800, "bitmask"),
+                                                  (4, 1, 2048, "dense"), (4, 1, 2048, "2:4"), (4, 1, 2048, "bitmask")])
+def test_a_workspace_serves_every_smaller_call(heads, n_kv, inter, fmt, sd2_options):
+    """More than 8 tokens are always one launch per step; how a linear is cut there depends on the token count, the room for
+    its partial results must not.  Neither may the switches change what a workspace holds."""
+    from types import SimpleNamespace
+    shape = SimpleNamespace(layers=1, hidden=128 * heads, q_out=128 * heads, kv_out=128 * n_kv, inter=inter, n_heads=heads, n_kv=n_kv)
+    model = _fake_stack(shape, fmt)
+    for size in (sd2.drafter_workspace_size, sd2.drafter_decode_workspace_size):
+        sizes = [size(model, t) for t in range(9, 65)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), sizes
+        for value in (1, 2):
+            sd2_options.set("linear_partials", value)
+            assert [size(model, t) for t in range(9, 65)] == sizes
+            sd2_options.reset()
+
+
 def test_greedy_verify_host_against_the_hand_cases_and_the_range_rule(golden_dir):
     path = os.path.join(golden_dir, "verify_hand_cases.txt")
     for line in open(path):
