@@ -4,7 +4,8 @@
 // fp32 the products run on the fp32 matrix instruction; where one operand is bf16 (the cache) the other is split into
 // three bf16 terms of eight bits each -- 24 bits, nothing is dropped -- and each term is multiplied on the bf16
 // instruction, whose products are exact and whose sums are fp32: three instructions of 16 clocks take the place of eight
-// of 32.
+// of 32.  That holds while all is finite: an infinity times a term that is zero is NaN, where fp32 has an infinity.  A score
+// that is not finite is computed again in fp32.
 #include <atomic>
 
 #include "sd2_device.h"
@@ -17,9 +18,9 @@ constexpr int kAttD = 128;
 // A row's weight for a position that it does not attend to is zero, and the matrix instruction multiplies it all the same:
 // an infinity or NaN in a value of a later token would reach the earlier ones.  So a wavefront whose sums are not all finite
 // adds them again on the vector ALU, attended positions only (nothing is paid for that while all is finite).
+constexpr float kFloatMax = 3.402823466e38f;
 __device__ __forceinline__ bool finite4(const f32x4& v) {
-    constexpr float kMax = 3.402823466e38f;
-    return fabsf(v[0]) <= kMax && fabsf(v[1]) <= kMax && fabsf(v[2]) <= kMax && fabsf(v[3]) <= kMax;
+    return fabsf(v[0]) <= kFloatMax && fabsf(v[1]) <= kFloatMax && fabsf(v[2]) <= kFloatMax && fabsf(v[3]) <= kFloatMax;
 }
 
 // ------------------------------------------------------------------ among the call's own tokens (up to 64)
@@ -227,6 +228,30 @@ __global__ __launch_bounds__(64 * kCaWaves) void cached_attention_wide_kernel(co
     int last[4];  // last position of the rows 4 g + v whose results this lane holds
 #pragma unroll
     for (int v = 0; v < 4; ++v) last[v] = pos0 + min(row_lo + 4 * g + v, n_rows - 1) / rep;
+    // scores of the rows 4 g + v at position pos; kf: the sixteen positions' keys as matrix operands
+    auto scores = [&](const Frag (&kf)[4], int pos) __attribute__((always_inline)) {
+        f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 2; k >= 0; --k)  // small terms first
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q[i][k].v, kf[i].v, s, 0, 0, 0);
+        bool finite = true;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) finite = finite && (pos > last[v] || fabsf(s[v]) <= kFloatMax);
+        if (__any(!finite)) {
+            const uint16_t* key = kg + (size_t)min(pos, n_pos - 1) * kAttD;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = min(row_lo + 4 * g + v, n_rows - 1), t = row / rep, r = row - t * rep;
+                const float* src = q_rot + (size_t)t * q_out + ((size_t)grp * rep + r) * kAttD;
+                float dot = 0.f;
+#pragma unroll 1
+                for (int d = 0; d < kAttD; ++d) dot += src[d] * 0.08838834764831845f * __uint_as_float((uint32_t)key[d] << 16);
+                s[v] = dot;
+            }
+        }
+        return s;
+    };
 
     float m[4], l[4];
     f32x4 o[8];
@@ -250,13 +275,7 @@ __global__ __launch_bounds__(64 * kCaWaves) void cached_attention_wide_kernel(co
         for (int i = 0; i < 8; ++i) vr[i] = *reinterpret_cast<const u32x4*>(vg + (size_t)min(base + 4 * i + g, n_pos - 1) * kAttD + 8 * n);
         f32x4 s[2];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int k = 2; k >= 0; --k)  // small terms first
-#pragma unroll
-                for (int i = 0; i < 4; ++i) s[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q[i][k].v, kf[b][i].v, s[b], 0, 0, 0);
-        }
+        for (int b = 0; b < 2; ++b) s[b] = scores(kf[b], base + 16 * b + n);
 #pragma unroll
         for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(vbuf + (4 * i + g) * kCaVRow + 16 * n) = vr[i];
         float p[2][4];
@@ -316,15 +335,10 @@ __global__ __launch_bounds__(64 * kCaWaves) void cached_attention_wide_kernel(co
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
                 const uint16_t* src = kg + (size_t)min(base + 16 * b + n, n_pos - 1) * kAttD + 8 * g;
-                f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+                Frag kf[4];
 #pragma unroll
-                for (int k = 2; k >= 0; --k)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        Frag kf;
-                        kf.q = *reinterpret_cast<const u32x4*>(src + 32 * i);
-                        s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q[i][k].v, kf.v, s, 0, 0, 0);
-                    }
+                for (int i = 0; i < 4; ++i) kf[i].q = *reinterpret_cast<const u32x4*>(src + 32 * i);
+                const f32x4 s = scores(kf, base + 16 * b + n);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) pbuf[(4 * g + v) * kCaPRow + 16 * b + n] = expf(s[v] - m[v]);
             }

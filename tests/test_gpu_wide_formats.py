@@ -145,6 +145,32 @@ def test_a_token_that_is_not_finite_leaves_the_earlier_ones_alone(k_tok, bad, po
         assert ol.rel_l2(got[:bad], clean[:bad]) <= 1e-3
 
 
+@pytest.mark.parametrize("k_tok,pos0", [(5, 40), (33, 300)])
+def test_infinite_key_follows_the_sign_of_its_score(k_tok, pos0, sd2_options):
+    """Minus infinity times a positive query component is a weight of zero: that head's row stays finite.  Plus infinity is NaN.
+    The first head meets the infinite key.  The oracle takes the largest number in its place, and a token is finite where the
+    value at that position does not count."""
+    import gpu_util as gu
+    from test_gpu_decode import _decode, _model, THETA
+    sd2_options.set("forward_multi", 1)
+    shape = SimpleNamespace(layers=1, hidden=512, q_out=512, kv_out=512, inter=1024, n_heads=4, n_kv=4, head_dim=128)
+    get, model = _model(shape, 61)
+    max_pos = pos0 + k_tok
+    rng = np.random.default_rng([61, k_tok])
+    kc, vc = (wl.f32_to_bf16_bits(rng.standard_normal((1, 4, max_pos, 128)).astype(np.float32)) for _ in range(2))
+    h = wl.gen_x(61, 0, "q", k_tok, shape.hidden)
+    kc[0, 0, 7, 70] = 0xFF7F
+    ref = od.drafter_decode(shape, get, h, kc.copy(), vc.copy(), pos0, THETA)
+    other = vc.copy()
+    other[0, 0, 7] = 0x4480  # 1024
+    finite = (od.drafter_decode(shape, get, h, kc.copy(), other, pos0, THETA) == ref).all(axis=1)
+    assert finite.any() and not finite.all()
+    kc[0, 0, 7, 70] = 0xFF80  # -inf
+    got = _decode(model, shape, h, gu.dev(kc), gu.dev(vc), max_pos, pos0)
+    assert np.array_equal(np.isfinite(got).all(axis=1), finite)
+    assert ol.rel_l2(got[finite], ref[finite]) <= 1e-3
+
+
 @pytest.mark.parametrize("fmt", ["bitmask", "dense"])
 @pytest.mark.parametrize("k_tok", [5, 17, 64])
 def test_infinite_weight_stays_in_its_row(k_tok, fmt):
