@@ -120,9 +120,12 @@ size_t stack_part_rows(const sd2_model* md) {
     }
     return rows;
 }
-inline LinUse stack_use(const sd2_matrix_t* m, size_t part_rows) {
-    return {(int)std::min<size_t>(kWideMaxSplit, part_rows / (size_t)m->info.n_out), true};
+inline LinUse stack_use(const sd2_model* md, int kind, size_t part_rows) {
+    const sd2_model_shape_t& sh = md->shape;
+    const int n_out = kind == 0 ? sh.q_out + 2 * sh.kv_out : kind == 2 ? 2 * sh.inter : sh.hidden;
+    return {(int)std::min<size_t>(kWideMaxSplit, part_rows / (size_t)n_out), true};
 }
+constexpr LinUse kGatedUse{1, false};  // the gated product needs final sums
 
 inline bool strip_gated_ok(const sd2_matrix_t* m, int k_tok) {
     return sparse_final_ok(m, k_tok) && sparse_strip_gated_supported(mat_args(m), k_tok);
@@ -141,40 +144,57 @@ bool few_strips(const sd2_matrix_t* m, int k_tok) {
     return sparse_final_ok(m, k_tok) && groups * m->info.n_slabs <= 2560;
 }
 
+// The cut of a linear in the wide kernel, searched at its first use and kept for the call: the search takes about a microsecond of
+// the host's time, and a stack asks for the cut of each linear several times a layer.  All layers' linears of one kind share it --
+// it depends on their shape, not on their format.
+struct LinearCut {
+    LinearCut(LinUse u) : use(u) {}
+    LinUse use;
+    enum { kUnknown, kNone, kFound } state = kUnknown;
+    WidePlan plan;
+};
+bool find_cut(LinearCut& c, const sd2_matrix_t* m, int k_tok, bool gated) {
+    if (c.state == LinearCut::kUnknown)
+        c.state = wide_plan(m->info.n_out, m->info.k_in, m->info.n_strips, k_tok, gated, c.use.room, c.use.free_add, &c.plan) ? LinearCut::kFound
+                                                                                                                             : LinearCut::kNone;
+    return c.state == LinearCut::kFound;
+}
+struct StackCuts {
+    LinearCut lin[4], gated;  // q|k|v, o, gate|up, down; gate|up with the gated product
+    StackCuts(const sd2_model* md, size_t part_rows)
+        : lin{stack_use(md, 0, part_rows), stack_use(md, 1, part_rows), stack_use(md, 2, part_rows), stack_use(md, 3, part_rows)}, gated(kGatedUse) {}
+};
+
 // More than 16 tokens: the kernel that keeps the activations of all tokens in registers.  SD2_OPT_LINEAR_PARTIALS keeps
 // bitmask matrices on the kernel with one partial result per slab.
-bool wide_choice(const sd2_matrix_t* m, int k_tok, LinUse use, WidePlan* p) {
-    if (k_tok <= 16 || few_strips(m, k_tok) || (m->kind == SD2_KIND_SPARSE && !is_nm24(m) && option(SD2_OPT_LINEAR_PARTIALS))) return false;
-    return wide_plan(m->info.n_out, m->info.k_in, m->info.n_strips, k_tok, false, use.room, use.free_add, p);
+inline bool wide_format_ok(const sd2_matrix_t* m) { return m->kind != SD2_KIND_SPARSE || is_nm24(m) || !option(SD2_OPT_LINEAR_PARTIALS); }
+bool wide_choice(const sd2_matrix_t* m, int k_tok, LinearCut& c) {
+    return k_tok > 16 && !few_strips(m, k_tok) && wide_format_ok(m) && find_cut(c, m, k_tok, false);
 }
-bool wide_gated_choice(const sd2_matrix_t* m, int k_tok, WidePlan* p) {
-    if (k_tok <= 16 || (few_strips(m, k_tok) && strip_gated_ok(m, k_tok)) || (m->kind == SD2_KIND_SPARSE && !is_nm24(m) && option(SD2_OPT_LINEAR_PARTIALS))) return false;
-    return wide_plan(m->info.n_out, m->info.k_in, m->info.n_strips, k_tok, true, 1, false, p);
+bool wide_gated_choice(const sd2_matrix_t* m, int k_tok, LinearCut& c) {
+    return k_tok > 16 && !(few_strips(m, k_tok) && strip_gated_ok(m, k_tok)) && wide_format_ok(m) && find_cut(c, m, k_tok, true);
 }
 
 // The gate|up linear and the gated product in one launch (the kernels that add the slabs up inside the workgroup).
-inline bool gated_ok(const sd2_matrix_t* m, int k_tok) {
-    WidePlan p;
-    return (k_tok <= 16 || few_strips(m, k_tok)) && strip_gated_ok(m, k_tok) ? true : wide_gated_choice(m, k_tok, &p);
+inline bool gated_ok(const sd2_matrix_t* m, int k_tok, LinearCut& c) {
+    return (k_tok <= 16 || few_strips(m, k_tok)) && strip_gated_ok(m, k_tok) ? true : wide_gated_choice(m, k_tok, c);
 }
-hipError_t run_gated(const sd2_matrix_t* m, const uint16_t* x, int k_tok, uint16_t* out, hipStream_t s) {
-    WidePlan p;
-    if (wide_gated_choice(m, k_tok, &p)) return launch_wide_linear(mat_args(m), is_nm24(m), x, k_tok, out, true, p, s);
+hipError_t run_gated(const sd2_matrix_t* m, const uint16_t* x, int k_tok, uint16_t* out, hipStream_t s, LinearCut& c) {
+    if (wide_gated_choice(m, k_tok, c)) return launch_wide_linear(mat_args(m), is_nm24(m), x, k_tok, out, true, c.plan, s);
     return launch_sparse_strip_gated(mat_args(m), x, k_tok, out, s);
 }
 
-// Partial results run_linear leaves in `out` for this token count (1: final values).  Never more than use.room.
-inline int n_splits(const sd2_matrix_t* m, int k_tok, LinUse use) {
-    WidePlan p;
-    if (wide_choice(m, k_tok, use, &p)) return p.n_split;
+// Partial results run_linear leaves in `out` for this token count (1: final values).  Never more than c.use.room.
+inline int n_splits(const sd2_matrix_t* m, int k_tok, LinearCut& c) {
+    if (wide_choice(m, k_tok, c)) return c.plan.n_split;
     return sparse_final_ok(m, k_tok) ? 1 : n_partials(m);
 }
 
-hipError_t run_linear(const sd2_matrix_t* m, const uint16_t* x, int k_tok, float* out, hipStream_t s, LinUse use, bool allow_final = true) {
+// cut: null for one partial result per slab, whatever the format's other kernels could do
+hipError_t run_linear(const sd2_matrix_t* m, const uint16_t* x, int k_tok, float* out, hipStream_t s, LinearCut* cut) {
     MatArgs ma = mat_args(m);
-    WidePlan wp;
-    if (allow_final && wide_choice(m, k_tok, use, &wp)) return launch_wide_linear(ma, is_nm24(m), x, k_tok, out, false, wp, s);
-    if (allow_final && sparse_final_ok(m, k_tok)) {
+    if (cut && wide_choice(m, k_tok, *cut)) return launch_wide_linear(ma, is_nm24(m), x, k_tok, out, false, cut->plan, s);
+    if (cut && sparse_final_ok(m, k_tok)) {
         LinArgs la{x, k_tok, out};
         return launch_sparse_strip_linear(ma, la, s);
     }
@@ -194,6 +214,15 @@ hipError_t run_linear(const sd2_matrix_t* m, const uint16_t* x, int k_tok, float
     return m->kind == SD2_KIND_SPARSE ? launch_sparse_linear(ma, la, s) : launch_dense_linear(ma, la, s);
 }
 
+// Final results in y; `part` has room for n_partials(m) partial ones.
+int run_final(const sd2_matrix_t* m, const uint16_t* x, int k_tok, float* y, float* part, hipStream_t s) {
+    LinearCut cut(final_use(m));
+    const int splits = n_splits(m, k_tok, cut);
+    if (splits == 1) return run_linear(m, x, k_tok, y, s, &cut) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
+    if (run_linear(m, x, k_tok, part, s, &cut) != hipSuccess) return SD2_ERR_HIP;
+    return launch_reduce_partials(part, splits, (size_t)k_tok * m->info.n_out, y, s) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
+}
+
 int linear_entry(const sd2_matrix_t* m, int kind, const uint16_t* x, int32_t k_tok, float* y, void* ws,
                  size_t ws_bytes, void* stream) {
     int rc = check_matrix(m, kind);
@@ -206,14 +235,7 @@ int linear_entry(const sd2_matrix_t* m, int kind, const uint16_t* x, int32_t k_t
         if (!ws) return SD2_ERR_NULL;
         if (!aligned16(ws) || ws_bytes < partial_bytes(m, k_tok)) return SD2_ERR_BUFFER;
     }
-    if (n_splits(m, k_tok, final_use(m)) == 1) {
-        return run_linear(m, x, k_tok, y, s, final_use(m)) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
-    }
-    float* part = static_cast<float*>(ws);
-    if (run_linear(m, x, k_tok, part, s, final_use(m)) != hipSuccess) return SD2_ERR_HIP;
-    if (launch_reduce_partials(part, n_splits(m, k_tok, final_use(m)), (size_t)k_tok * m->info.n_out, y, s) != hipSuccess)
-        return SD2_ERR_HIP;
-    return SD2_OK;
+    return run_final(m, x, k_tok, y, static_cast<float*>(ws), s);
 }
 
 struct StackLayout {
@@ -388,7 +410,7 @@ int sd2_sparse_linear_partials(const sd2_matrix_t* m, const uint16_t* x, int32_t
     if (!x || !part) return SD2_ERR_NULL;
     if ((rc = check_tokens(k_tok)) != SD2_OK) return rc;
     if (!aligned16(x) || !aligned16(part) || part_bytes < partial_bytes(m, k_tok)) return SD2_ERR_BUFFER;
-    return run_linear(m, x, k_tok, part, static_cast<hipStream_t>(stream), final_use(m), /*allow_final=*/false) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
+    return run_linear(m, x, k_tok, part, static_cast<hipStream_t>(stream), nullptr) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
 }
 
 int sd2_dense_linear(const sd2_matrix_t* m, const uint16_t* x, int32_t k_tok, float* y, void* ws, size_t ws_bytes,
@@ -427,17 +449,15 @@ int sd2_sparse_mlp_forward(const sd2_matrix_t* gu, const sd2_matrix_t* dn, const
     const int inter = dn->info.k_in;
     uint16_t* act = static_cast<uint16_t*>(ws);
     float* part = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + align256((size_t)k_tok * inter * sizeof(uint16_t)));
-    if (gated_ok(gu, k_tok)) {
-        if (run_gated(gu, x, k_tok, act, s) != hipSuccess) return SD2_ERR_HIP;
+    LinearCut gated_cut(kGatedUse);
+    if (gated_ok(gu, k_tok, gated_cut)) {
+        if (run_gated(gu, x, k_tok, act, s, gated_cut) != hipSuccess) return SD2_ERR_HIP;
     } else {
-        if (run_linear(gu, x, k_tok, part, s, final_use(gu)) != hipSuccess) return SD2_ERR_HIP;
-        if (launch_silu_mul(part, n_splits(gu, k_tok, final_use(gu)), k_tok, inter, act, s) != hipSuccess) return SD2_ERR_HIP;
+        LinearCut cut(final_use(gu));
+        if (run_linear(gu, x, k_tok, part, s, &cut) != hipSuccess) return SD2_ERR_HIP;
+        if (launch_silu_mul(part, n_splits(gu, k_tok, cut), k_tok, inter, act, s) != hipSuccess) return SD2_ERR_HIP;
     }
-    if (n_splits(dn, k_tok, final_use(dn)) == 1) return run_linear(dn, act, k_tok, y, s, final_use(dn)) == hipSuccess ? SD2_OK : SD2_ERR_HIP;
-    if (run_linear(dn, act, k_tok, part, s, final_use(dn)) != hipSuccess) return SD2_ERR_HIP;
-    if (launch_reduce_partials(part, n_splits(dn, k_tok, final_use(dn)), (size_t)k_tok * dn->info.n_out, y, s) != hipSuccess)
-        return SD2_ERR_HIP;
-    return SD2_OK;
+    return run_final(dn, act, k_tok, y, part, s);
 }
 
 int sd2_model_create(const sd2_model_shape_t* sh, const sd2_matrix_t* mats, int32_t n_mats, sd2_model_t** out) {
@@ -580,6 +600,7 @@ static int forward_impl(const sd2_model_t* md, const uint16_t* h_in, int32_t k_t
     float* h = h_out;  // the residual stream lives in the output buffer
 #define SD2_TRY(expr) \
     if ((expr) != hipSuccess) return SD2_ERR_HIP
+    StackCuts cuts(md, L.part_rows);
     const TraceLayout T = trace_layout(md, k_tok);
     // records what linear `lin` consumed: `width` fp32 source values per token (copied, or summed from partials)
     // and the `k_in` bf16 activations now sitting in `act`
@@ -608,25 +629,25 @@ static int forward_impl(const sd2_model_t* md, const uint16_t* h_in, int32_t k_t
         const sd2_matrix_t* gu = &md->mats[4 * l + 2];
         const sd2_matrix_t* dn = &md->mats[4 * l + 3];
         SD2_TRY(record(4 * l + 0, h, nullptr, 0, sh.hidden, sh.hidden));
-        SD2_TRY(run_linear(qkv, act, k_tok, part, s, stack_use(qkv, L.part_rows)));
-        SD2_TRY(launch_inflight_attention(part, n_splits(qkv, k_tok, stack_use(qkv, L.part_rows)), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv,
+        SD2_TRY(run_linear(qkv, act, k_tok, part, s, &cuts.lin[0]));
+        SD2_TRY(launch_inflight_attention(part, n_splits(qkv, k_tok, cuts.lin[0]), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv,
                                           sh.head_dim, act, s));
-        SD2_TRY(record(4 * l + 1, nullptr, part, n_splits(qkv, k_tok, stack_use(qkv, L.part_rows)), sh.q_out + 2 * sh.kv_out, sh.q_out));
-        SD2_TRY(run_linear(o, act, k_tok, part, s, stack_use(o, L.part_rows)));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok, stack_use(o, L.part_rows)), k_tok, sh.hidden, act, ssq, s));
+        SD2_TRY(record(4 * l + 1, nullptr, part, n_splits(qkv, k_tok, cuts.lin[0]), sh.q_out + 2 * sh.kv_out, sh.q_out));
+        SD2_TRY(run_linear(o, act, k_tok, part, s, &cuts.lin[1]));
+        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok, cuts.lin[1]), k_tok, sh.hidden, act, ssq, s));
         SD2_TRY(record(4 * l + 2, h, nullptr, 0, sh.hidden, sh.hidden));
-        if (!trace && gated_ok(gu, k_tok)) {
+        if (!trace && gated_ok(gu, k_tok, cuts.gated)) {
             // one launch: the gated product is written by the linear's own epilogue (act is read and written: the
             // kernel has taken its input columns into registers before the first result leaves)
-            SD2_TRY(run_gated(gu, act, k_tok, act2, s));
+            SD2_TRY(run_gated(gu, act, k_tok, act2, s, cuts.gated));
             std::swap(act, act2);
         } else {
-            SD2_TRY(run_linear(gu, act, k_tok, part, s, stack_use(gu, L.part_rows)));
-            SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok, stack_use(gu, L.part_rows)), k_tok, sh.inter, act, s));
+            SD2_TRY(run_linear(gu, act, k_tok, part, s, &cuts.lin[2]));
+            SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok, cuts.lin[2]), k_tok, sh.inter, act, s));
         }
-        SD2_TRY(record(4 * l + 3, nullptr, part, n_splits(gu, k_tok, stack_use(gu, L.part_rows)), 2 * sh.inter, sh.inter));
-        SD2_TRY(run_linear(dn, act, k_tok, part, s, stack_use(dn, L.part_rows)));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok, stack_use(dn, L.part_rows)), k_tok, sh.hidden,
+        SD2_TRY(record(4 * l + 3, nullptr, part, n_splits(gu, k_tok, cuts.lin[2]), 2 * sh.inter, sh.inter));
+        SD2_TRY(run_linear(dn, act, k_tok, part, s, &cuts.lin[3]));
+        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok, cuts.lin[3]), k_tok, sh.hidden,
                                         l + 1 < sh.layers ? act : nullptr, ssq, s));
     }
 #undef SD2_TRY
@@ -769,6 +790,7 @@ int sd2_sparse_drafter_decode(const sd2_model_t* md, const uint16_t* h_in, int32
     const size_t layer_elems = (size_t)sh.n_kv * max_pos * sh.head_dim;
 #define SD2_TRY(expr) \
     if ((expr) != hipSuccess) return SD2_ERR_HIP
+    StackCuts cuts(md, L.part_rows);
     SD2_TRY(launch_rope_table(pos0, k_tok, sh.head_dim, rope_theta, table, s));
     SD2_TRY(launch_residual_rmsnorm(h, h_in, nullptr, 0, k_tok, sh.hidden, sh.layers > 0 ? act : nullptr, ssq, s));
     for (int l = 0; l < sh.layers; ++l) {
@@ -778,21 +800,21 @@ int sd2_sparse_drafter_decode(const sd2_model_t* md, const uint16_t* h_in, int32
         const sd2_matrix_t* dn = &md->mats[4 * l + 3];
         uint16_t* kc = k_cache + (size_t)l * layer_elems;
         uint16_t* vc = v_cache + (size_t)l * layer_elems;
-        SD2_TRY(run_linear(qkv, act, k_tok, part, s, stack_use(qkv, L.part_rows)));
-        SD2_TRY(launch_rope_append(part, n_splits(qkv, k_tok, stack_use(qkv, L.part_rows)), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv, sh.head_dim, table,
+        SD2_TRY(run_linear(qkv, act, k_tok, part, s, &cuts.lin[0]));
+        SD2_TRY(launch_rope_append(part, n_splits(qkv, k_tok, cuts.lin[0]), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv, sh.head_dim, table,
                                    pos0, max_pos, q_rot, kc, vc, s));
         SD2_TRY(launch_cached_attention(q_rot, kc, vc, max_pos, pos0, k_tok, sh.q_out, sh.n_heads, sh.n_kv, sh.head_dim, act, s));
-        SD2_TRY(run_linear(o, act, k_tok, part, s, stack_use(o, L.part_rows)));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok, stack_use(o, L.part_rows)), k_tok, sh.hidden, act, ssq, s));
-        if (gated_ok(gu, k_tok)) {
-            SD2_TRY(run_gated(gu, act, k_tok, act2, s));
+        SD2_TRY(run_linear(o, act, k_tok, part, s, &cuts.lin[1]));
+        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok, cuts.lin[1]), k_tok, sh.hidden, act, ssq, s));
+        if (gated_ok(gu, k_tok, cuts.gated)) {
+            SD2_TRY(run_gated(gu, act, k_tok, act2, s, cuts.gated));
             std::swap(act, act2);
         } else {
-            SD2_TRY(run_linear(gu, act, k_tok, part, s, stack_use(gu, L.part_rows)));
-            SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok, stack_use(gu, L.part_rows)), k_tok, sh.inter, act, s));
+            SD2_TRY(run_linear(gu, act, k_tok, part, s, &cuts.lin[2]));
+            SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok, cuts.lin[2]), k_tok, sh.inter, act, s));
         }
-        SD2_TRY(run_linear(dn, act, k_tok, part, s, stack_use(dn, L.part_rows)));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok, stack_use(dn, L.part_rows)), k_tok, sh.hidden,
+        SD2_TRY(run_linear(dn, act, k_tok, part, s, &cuts.lin[3]));
+        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok, cuts.lin[3]), k_tok, sh.hidden,
                                         l + 1 < sh.layers ? act : nullptr, ssq, s));
     }
 #undef SD2_TRY

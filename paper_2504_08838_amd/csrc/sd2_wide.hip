@@ -492,22 +492,29 @@ bool wide_plan(int n_out, int k_in, int n_strips, int k_tok, bool gated, int max
         return false;  // 32-bit byte offsets, into the value section and over 64 rows of activations
     const int n_units = (k_in + 127) / 128;
     const int cus = wide_cu_count(), step = gated ? 2 : 1;
+    const int max_cut = std::min(std::min(max_split, kWideMaxSplit), std::min(n_units, cus));
+    int per_wg[kWideMaxSplit + 1], units[kWideMaxSplit + 1];  // strips of a workgroup, units of a split
+    double extra[kWideMaxSplit + 1];
+    for (int split = 1; split <= max_cut; ++split) {
+        const int blocks = std::max(1, std::min(n_strips / step, cus / split));
+        per_wg[split] = step * ((n_strips / step + blocks - 1) / blocks);
+        units[split] = (n_units + split - 1) / split;
+        extra[split] = split > 1 ? (double)split * k_tok * n_out * 8.0 / 4e6 + (free_add ? 0.0 : 3.0) : 0.0;
+    }
     double best = -1.0;
     for (int waves = 8; waves <= 12; waves += 4)
-        for (int sg = 2; sg <= 4; ++sg)
-            for (int wk = waves; wk >= 2; --wk) {
-                if (waves % wk || wk % 2 || (waves == 12 && tg * sg > 6)) continue;
-                const int ws = waves / wk;
-                if (gated && (sg * ws) % 2) continue;  // pairs stay within a group
-                for (int split = 1; split <= std::min(std::min(max_split, kWideMaxSplit), n_units) && split <= cus; ++split) {
-                    const int n_pass = ((n_units + split - 1) / split + wk - 1) / wk;
+        for (int sg = 2; sg <= 4; ++sg) {
+            if (waves == 12 && tg * sg > 6) continue;
+            const double pass = waves == 8 ? sg * (0.7 + 0.06 * tg) + 0.3 + 0.45 * tg : sg * (0.95 + 0.06 * tg) + 0.3 + 0.6 * tg;
+            for (int wk = waves; wk >= 2; wk -= 2) {
+                if (waves % wk) continue;
+                const int group = sg * (waves / wk);
+                if (gated && group % 2) continue;  // pairs stay within a group
+                for (int split = 1; split <= max_cut; ++split) {
+                    const int n_pass = (units[split] + wk - 1) / wk;
                     if ((split - 1) * n_pass * wk >= n_units) continue;  // an empty split
-                    const int blocks = std::max(1, std::min(n_strips / step, cus / split));
-                    const int per_wg = step * ((n_strips / step + blocks - 1) / blocks);
-                    const int groups = (per_wg + sg * ws - 1) / (sg * ws);
-                    const double pass = waves == 8 ? sg * (0.7 + 0.06 * tg) + 0.3 + 0.45 * tg : sg * (0.95 + 0.06 * tg) + 0.3 + 0.6 * tg;
-                    double t = groups * (n_pass * pass + 1.5);
-                    if (split > 1) t += (double)split * k_tok * n_out * 8.0 / 4e6 + (free_add ? 0.0 : 3.0);
+                    const int groups = (per_wg[split] + group - 1) / group;
+                    const double t = groups * (n_pass * pass + 1.5) + extra[split];
                     if (best < 0.0 || t < best) {
                         best = t;
                         out->waves = waves;
@@ -515,12 +522,15 @@ bool wide_plan(int n_out, int k_in, int n_strips, int k_tok, bool gated, int max
                         out->n_pass = n_pass;
                         out->wk = wk;
                         out->sg = sg;
-                        out->strips_per_wg = per_wg;
-                        out->n_wg = split * ((n_strips + per_wg - 1) / per_wg);
-                        out->n_units = n_units;
                     }
                 }
             }
+        }
+    if (best >= 0.0) {
+        out->strips_per_wg = per_wg[out->n_split];
+        out->n_wg = out->n_split * ((n_strips + out->strips_per_wg - 1) / out->strips_per_wg);
+        out->n_units = n_units;
+    }
     return best >= 0.0;
 }
 
