@@ -998,7 +998,7 @@ hipError_t launch_residual_rmsnorm(float* h, const uint16_t* h_in, const float* 
         else if (hidden <= kRnThreads * 8)
             hipLaunchKernelGGL((residual_norm_kernel<2, 4>), grid, block, 0, s, h, h_in, part, n_splits, k_tok, hidden, a);
         else
-            hipLaunchKernelGGL((residual_norm_kernel<4, 4>), grid, block, 0, s, h, h_in, part, n_splits, k_tok, hidden, a);
+            hipLaunchKernelGGL((residual_norm_kernel<4, 2>), grid, block, 0, s, h, h_in, part, n_splits, k_tok, hidden, a);
         return hipGetLastError();
     }
     const dim3 grid((unsigned)((hidden + 255) / 256), (unsigned)k_tok);

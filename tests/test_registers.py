@@ -1,0 +1,27 @@
+"""What the compiler's own notes in the built library say of the kernels: none but the persistent forward spills to memory."""
+import os
+import re
+
+import pytest
+
+from paper_2504_08838_amd import build
+
+# .name and .private_segment_fixed_size are neighbours in a kernel's msgpack map (the keys are sorted)
+NOTE = re.compile(rb"\.name(?:[\xa0-\xbf]|\xd9.|\xda..)(_Z\w+?)\xbb\.private_segment_fixed_size(.)", re.S)
+
+
+@pytest.fixture(scope="module")
+def scratch():
+    """First byte of the scratch size by kernel: 0 is none, anything else is some."""
+    if not os.path.exists(build.LIB):
+        build.build()
+    with open(build.LIB, "rb") as f:
+        notes = f.read()
+    found = {m.group(1).decode(): m.group(2)[0] for m in NOTE.finditer(notes)}
+    assert len(found) == notes.count(b".private_segment_fixed_size")
+    return found
+
+
+def test_streaming_kernels_keep_everything_in_registers(scratch):
+    spilled = [name for name, size in scratch.items() if size and "mega_forward_kernel" not in name]
+    assert len(scratch) > 50 and not spilled
