@@ -52,11 +52,34 @@ def test_wide_linear_exact_integers(n, k, k_tok, fmt):
 
 
 @pytest.mark.parametrize("fmt", ["bitmask", "2:4", "dense"])
-@pytest.mark.parametrize("hidden,inter,k_tok", [(192, 48, 17), (512, 1200, 64)])
+@pytest.mark.parametrize("n,k,k_tok", [
+    (16640, 64, 64),    # four groups of two wavefronts over the strips
+    (32960, 320, 50),   # the same, three units: two passes
+    (8208, 576, 17),    # twelve wavefronts in two groups
+    (24800, 576, 33),   # the same with two strip groups per workgroup, one after the other
+    (32960, 832, 64),   # eight wavefronts along the contraction, three strip groups
+])
+def test_wide_linear_many_strips_exact_integers(n, k, k_tok, fmt):
+    """Short contractions of many strips: wavefronts share out the strips, and a workgroup takes several groups of them."""
+    import gpu_util as gu
+    rng = np.random.default_rng([7, n, k, k_tok])
+    w = _matrix(rng, n, k, fmt)
+    x = rng.integers(-4, 5, size=(k_tok, k))
+    mat = gu.DenseMat(_ints(w)) if fmt == "dense" else gu.SparseMat(_ints(w), 3 if fmt == "2:4" else 1)
+    y = gu.run_linear(mat, _ints(x), sparse=fmt != "dense")
+    assert np.array_equal(y, x.astype(np.float32) @ w.T.astype(np.float32))  # sums below 2^24: exact in any order
+
+
+@pytest.mark.parametrize("fmt", ["bitmask", "2:4", "dense"])
+@pytest.mark.parametrize("hidden,inter,k_tok", [(192, 48, 17), (512, 1200, 64),
+                                                (576, 12416, 40),  # gate|up: two groups of six wavefronts, two strip groups
+                                                (320, 16512, 64)])  # gate|up: four groups of two wavefronts, two passes
 def test_wide_mlp_gated(hidden, inter, k_tok, fmt):
     import torch
     import paper_2504_08838_amd as sd2
     import gpu_util as gu
+    if fmt == "2:4" and inter > 9216:
+        pytest.skip("the down matrix has more columns than a 2:4 matrix may have")
     pattern = dict(pattern="2:4") if fmt == "2:4" else {}
     inter = (inter + 63) // 64 * 64
     wg, wu, wd = (wl.gen_weight(2, 1, p, n, k, 50, **pattern) for p, n, k in (("gate", inter, hidden), ("up", inter, hidden), ("down", hidden, inter)))
