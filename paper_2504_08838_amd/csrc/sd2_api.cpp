@@ -91,12 +91,12 @@ size_t partial_bytes(const sd2_matrix_t* m, int k_tok) {
 
 int check_tokens(int32_t k_tok) { return (k_tok < 1 || k_tok > SD2_MAX_TOKENS) ? SD2_ERR_RANGE : SD2_OK; }
 
-// The bitmask format has a kernel that adds the slabs up inside the workgroup, too (up to 16 tokens, up to 32 slabs,
-// tiles that fit its buffers); SD2_OPT_LINEAR_PARTIALS keeps the kernel with one partial result per slab (tests cover both).
-inline bool sparse_final_ok(const sd2_matrix_t* m, int k_tok) {
+// The bitmask format has a kernel that adds the slabs up inside the workgroup, too (tg token groups a pass, up to 32 slabs
+// with one and 24 with two, tiles that fit its buffers); SD2_OPT_LINEAR_PARTIALS keeps the kernel with one partial result per slab (tests cover both).
+inline bool sparse_final_ok(const sd2_matrix_t* m, int tg) {
     if (m->kind != SD2_KIND_SPARSE || is_nm24(m)) return false;
     if (option(SD2_OPT_LINEAR_PARTIALS)) return false;
-    return sparse_strip_supported(mat_args(m), k_tok);
+    return sparse_strip_supported(mat_args(m), tg);
 }
 
 // Where a linear's results go: room for that many partial results of it, and whether the next kernel adds them as it reads
@@ -127,21 +127,8 @@ inline LinUse stack_use(const sd2_model* md, int kind, size_t part_rows) {
 }
 constexpr LinUse kGatedUse{1, false};  // the gated product needs final sums
 
-inline bool strip_gated_ok(const sd2_matrix_t* m, int k_tok) {
-    return sparse_final_ok(m, k_tok) && sparse_strip_gated_supported(mat_args(m), k_tok);
-}
-
-// More than 16 tokens on a small matrix: passes of 16 tokens side by side in one launch of the kernel for 16 tokens, which
-// costs what 16 tokens cost while the compute units are not full.  The line lies where both sides take the same time.  Bitmask, in
-// expanded tiles: 1024 x 512 on 64 tokens 3.6 us against 6.8 in the wide kernel, 1024 x 2560 (2560 tiles) 6.4 against 9.6; 3072 x 1536
-// on 40 tokens (3456 tiles) 8.4 against 7.9.  Dense, a strip and pass per compute unit or its like in columns: 1024 x 2560 on 64
-// tokens 5.7 us against 11.3, 1536 x 1536 6.8 against 8.6; 3072 x 1536 on 17 tokens 6.0 against 5.7.  A 2:4 matrix, with nothing
-// to expand, is as fast in the wide kernel at every size.
-bool few_strips(const sd2_matrix_t* m, int k_tok) {
-    const int passes = (k_tok + 15) / 16;
-    const int64_t groups = (int64_t)m->info.n_strips * passes;
-    if (m->kind == SD2_KIND_DENSE) return is_dense_stream(m) && (groups <= 256 || groups * m->info.k_in <= (passes > 2 ? 384 * 1536 : 512 * 1024));
-    return sparse_final_ok(m, k_tok) && groups * m->info.n_slabs <= 2560;
+inline bool strip_gated_ok(const sd2_matrix_t* m, int tg) {
+    return sparse_final_ok(m, tg) && sparse_strip_gated_supported(mat_args(m), tg);
 }
 
 // The cut of a linear in the wide kernel, searched at its first use and kept for the call: the search takes about a microsecond of
@@ -165,38 +152,111 @@ struct StackCuts {
         : lin{stack_use(md, 0, part_rows), stack_use(md, 1, part_rows), stack_use(md, 2, part_rows), stack_use(md, 3, part_rows)}, gated(kGatedUse) {}
 };
 
-// More than 16 tokens: the kernel that keeps the activations of all tokens in registers.  SD2_OPT_LINEAR_PARTIALS keeps
-// bitmask matrices on the kernel with one partial result per slab.
+// More than 16 tokens: the kernel that keeps the activations of all tokens in registers (0), or passes of one to four groups of 16
+// tokens side by side in one launch of the kernels for so many.  The wide kernel reads and expands a tile once, but starts
+// slowly and wants many strips; a pass costs what it costs on its tokens alone as long as the compute units are not full.
+// The lines below lie where both sides take the same time, from the kernels timed at 14 x 13 shapes of up to 34 million
+// elements on 17, 24, 32, 33, 48, 49 and 64 tokens, and each linear of nine decoder shapes timed inside its stack, where
+// the wide kernel may leave partial results and so keeps longer contractions.  Over the whole grid they cost half a percent
+// more than the fastest kernel at each point; the wide kernel everywhere costs 20 %.  Microseconds, wide / one group a pass /
+// two: bitmask 512 x 512 on 64 tokens 6.8 / 3.7 / 4.3, 4096 x 2048 on 17 tokens 8.5 / 6.7 / 6.0 and on 33 tokens 9.3 / 9.0 / 9.7
+// (three groups in one pass 6.8), 2048 x 1536 on 64 tokens 9.5 / 6.6 / 6.2; dense 2048 x 1536 on 64 tokens 8.7 / 7.1 / 5.8,
+// 1536 x 4096 on 33 tokens 12.2 / 7.4 / 10.5.  A 2:4 matrix, with nothing to expand, is as fast in the wide kernel at every size.
+struct Passes {
+    int n1, n2;    // passes of one group, of two
+    int wg1, wg2;  // workgroups of them, one per strip (pair of strips) and pass
+    bool light;    // the last pass of one group has eight tokens at most and costs little
+    Passes(int units, int k_tok)
+        : n1((k_tok + 15) / 16), n2((k_tok + 31) / 32), wg1(units * n1), wg2(units * n2), light(k_tok - 16 * (n1 - 1) <= 8) {}
+};
+int bitmask_groups(int strips, int slabs, int k_tok, bool stack) {
+    const Passes p(strips, k_tok);
+    if (slabs > (stack ? 10 : 20)) return 0;
+    if (p.wg1 <= 256) return 1;  // a workgroup per compute unit
+    if (slabs <= 2) {            // short tiles: several workgroups on a compute unit do not wait for each other
+        if (p.wg1 <= 768) return 1;
+        if (p.wg2 <= 512) return 2;
+        if (p.wg1 * slabs <= 1920) return 1;
+        return slabs == 1 && p.wg2 <= 1024 ? 2 : 0;
+    }
+    if (stack && slabs > 8) return 0;
+    if (p.wg2 <= 256) {
+        if (p.n1 == 3 && p.light && slabs <= 8) return 1;
+        return k_tok <= 24 || slabs <= (p.n1 == 4 || (p.n1 == 2 && strips > 224) ? 16 : 10) ? 2 : 0;
+    }
+    if (!stack && p.n1 > 2 && strips <= 256 && slabs <= (p.n1 == 3 ? 12 : 8)) return p.n1;  // all tokens in one pass
+    if (p.n1 > 2 && p.wg1 * slabs <= (p.wg1 <= 512 ? 4096 : 3072)) return 1;
+    return k_tok <= 24 && p.wg2 <= 512 && slabs > 5 && slabs <= 12 ? 2 : 0;
+}
+int dense_groups(int strips, int k_in, int k_tok, bool stack) {
+    const Passes p(strips, k_tok);
+    if (!dense_stream_ok(k_in)) return k_in == 64 || (k_in == 192 && k_tok <= 24) ? 1 : 0;  // one slab: nothing to add up
+    if (stack) {
+        if (p.wg1 <= 256) return k_in <= (p.n1 > 2 ? 2048 : 1536) ? 1 : 0;
+        return p.wg2 <= 256 && k_in <= (p.n1 == 4 ? 1536 : 1024) ? 2 : 0;
+    }
+    if (p.wg1 <= 256) return 1;
+    if (!dense_stream_pair_ok(k_in))  // one group at a time is all there is
+        return strips <= (p.n1 == 2 ? 160 : 128) && (p.n1 == 4 || k_tok - 16 * (p.n1 - 1) <= 4) ? 1 : 0;
+    if (p.n1 == 3 && p.light && p.wg1 <= 288) return 1;
+    if (p.wg2 <= 256) return p.n2 == 2 || k_tok <= 24 || k_in <= 1536 ? 2 : 0;
+    if (p.n1 == 3 && p.light && p.wg2 <= 320) return 2;
+    return p.wg2 <= 512 && (k_in <= 512 || (k_tok <= 24 && (k_in <= 1024 || k_in > 3584))) ? 2 : 0;
+}
+int gated_groups(int pairs, int slabs, int k_tok) {
+    const Passes p(pairs, k_tok);
+    if (p.wg1 <= 256) return 1;
+    if (slabs <= 2 && p.wg2 <= 512) return 2;
+    if (p.wg2 <= 256 && p.n1 == 4) return 2;
+    return k_tok <= 24 && p.wg2 <= 320 && slabs > 4 ? 2 : 0;
+}
+
+// SD2_OPT_LINEAR_PARTIALS keeps bitmask matrices on the kernel with one partial result per slab.
 inline bool wide_format_ok(const sd2_matrix_t* m) { return m->kind != SD2_KIND_SPARSE || is_nm24(m) || !option(SD2_OPT_LINEAR_PARTIALS); }
-bool wide_choice(const sd2_matrix_t* m, int k_tok, LinearCut& c) {
-    return k_tok > 16 && !few_strips(m, k_tok) && wide_format_ok(m) && find_cut(c, m, k_tok, false);
+
+// Token groups per pass, 0: the wide kernel.  What that kernel cannot take runs in passes of one group.
+int pass_groups(const sd2_matrix_t* m, int k_tok, LinearCut& c) {
+    if (k_tok <= 16) return 1;
+    int tg = 0;
+    if (m->kind == SD2_KIND_DENSE)
+        tg = dense_groups(m->info.n_strips, m->info.k_in, k_tok, c.use.free_add);
+    else if (!is_nm24(m) && (tg = bitmask_groups(m->info.n_strips, m->info.n_slabs, k_tok, c.use.free_add)) > 0 && !sparse_final_ok(m, tg))
+        tg = 0;
+    return tg == 0 && !(wide_format_ok(m) && find_cut(c, m, k_tok, false)) ? 1 : tg;
 }
-bool wide_gated_choice(const sd2_matrix_t* m, int k_tok, LinearCut& c) {
-    return k_tok > 16 && !(few_strips(m, k_tok) && strip_gated_ok(m, k_tok)) && wide_format_ok(m) && find_cut(c, m, k_tok, true);
+int gated_pass_groups(const sd2_matrix_t* m, int k_tok, LinearCut& c) {
+    if (k_tok <= 16) return 1;
+    int tg = m->kind == SD2_KIND_DENSE || is_nm24(m) ? 0 : gated_groups(m->info.n_strips / 2, m->info.n_slabs, k_tok);
+    if (tg > 0 && !strip_gated_ok(m, tg)) tg = 0;
+    return tg == 0 && !(wide_format_ok(m) && find_cut(c, m, k_tok, true)) ? 1 : tg;
 }
+inline bool wide_choice(const sd2_matrix_t* m, int k_tok, LinearCut& c) { return pass_groups(m, k_tok, c) == 0; }
 
 // The gate|up linear and the gated product in one launch (the kernels that add the slabs up inside the workgroup).
 inline bool gated_ok(const sd2_matrix_t* m, int k_tok, LinearCut& c) {
-    return (k_tok <= 16 || few_strips(m, k_tok)) && strip_gated_ok(m, k_tok) ? true : wide_gated_choice(m, k_tok, c);
+    const int tg = gated_pass_groups(m, k_tok, c);
+    return tg == 0 || strip_gated_ok(m, tg);
 }
 hipError_t run_gated(const sd2_matrix_t* m, const uint16_t* x, int k_tok, uint16_t* out, hipStream_t s, LinearCut& c) {
-    if (wide_gated_choice(m, k_tok, c)) return launch_wide_linear(mat_args(m), is_nm24(m), x, k_tok, out, true, c.plan, s);
-    return launch_sparse_strip_gated(mat_args(m), x, k_tok, out, s);
+    const int tg = gated_pass_groups(m, k_tok, c);
+    if (tg == 0) return launch_wide_linear(mat_args(m), is_nm24(m), x, k_tok, out, true, c.plan, s);
+    return launch_sparse_strip_gated(mat_args(m), x, k_tok, out, tg, s);
 }
 
 // Partial results run_linear leaves in `out` for this token count (1: final values).  Never more than c.use.room.
 inline int n_splits(const sd2_matrix_t* m, int k_tok, LinearCut& c) {
     if (wide_choice(m, k_tok, c)) return c.plan.n_split;
-    return sparse_final_ok(m, k_tok) ? 1 : n_partials(m);
+    return sparse_final_ok(m, 1) ? 1 : n_partials(m);
 }
 
 // cut: null for one partial result per slab, whatever the format's other kernels could do
 hipError_t run_linear(const sd2_matrix_t* m, const uint16_t* x, int k_tok, float* out, hipStream_t s, LinearCut* cut) {
     MatArgs ma = mat_args(m);
-    if (cut && wide_choice(m, k_tok, *cut)) return launch_wide_linear(ma, is_nm24(m), x, k_tok, out, false, cut->plan, s);
-    if (cut && sparse_final_ok(m, k_tok)) {
+    const int tg = cut ? pass_groups(m, k_tok, *cut) : 1;
+    if (tg == 0) return launch_wide_linear(ma, is_nm24(m), x, k_tok, out, false, cut->plan, s);
+    if (cut && sparse_final_ok(m, 1)) {
         LinArgs la{x, k_tok, out};
-        return launch_sparse_strip_linear(ma, la, s);
+        return launch_sparse_strip_linear(ma, la, tg, s);
     }
     if (is_nm24(m)) {
         // the structured-sparse matrix instruction takes 16 tokens; more tokens stream the matrix once per group
@@ -207,7 +267,7 @@ hipError_t run_linear(const sd2_matrix_t* m, const uint16_t* x, int k_tok, float
         }
         return hipSuccess;
     }
-    if (is_dense_stream(m)) return launch_dense_stream_linear(ma.w, x, ma.n_out, ma.k_in, k_tok, out, s);
+    if (is_dense_stream(m)) return launch_dense_stream_linear(ma.w, x, ma.n_out, ma.k_in, k_tok, out, tg, s);
     LinArgs la{x, k_tok, out};
     if (m->kind == SD2_KIND_SPARSE && option(SD2_OPT_LINEAR_PARTIALS) == 2 && sparse_linear_valu_supported(ma, k_tok))
         return launch_sparse_linear_valu(ma, la, s);  // the measurement variant without matrix instructions

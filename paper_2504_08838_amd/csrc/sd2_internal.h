@@ -26,15 +26,15 @@ struct LinArgs {
 
 hipError_t launch_sparse_linear(const MatArgs& m, const LinArgs& a, hipStream_t s);
 hipError_t launch_dense_linear(const MatArgs& m, const LinArgs& a, hipStream_t s);
-// the sparse linear with final results in one launch (no partial sums): a.out is y [k_tok][n_out]
-bool sparse_strip_supported(const MatArgs& m, int k_tok);
+// the sparse linear with final results in one launch (no partial sums): a.out is y [k_tok][n_out], passes of 16 tg tokens
+bool sparse_strip_supported(const MatArgs& m, int tg);
 // the per-slab kernel with the multiply on the vector ALU (up to 8 tokens): a measurement variant
 bool sparse_linear_valu_supported(const MatArgs& m, int k_tok);
 hipError_t launch_sparse_linear_valu(const MatArgs& m, const LinArgs& a, hipStream_t s);
-hipError_t launch_sparse_strip_linear(const MatArgs& m, const LinArgs& a, hipStream_t s);
+hipError_t launch_sparse_strip_linear(const MatArgs& m, const LinArgs& a, int tg, hipStream_t s);
 // the fused [gate; up] product with the gating in its epilogue: m_out [k_tok][n_out / 2] = bf16(silu(gate x) * (up x))
-bool sparse_strip_gated_supported(const MatArgs& m, int k_tok);
-hipError_t launch_sparse_strip_gated(const MatArgs& m, const uint16_t* x, int k_tok, uint16_t* m_out, hipStream_t s);
+bool sparse_strip_gated_supported(const MatArgs& m, int tg);
+hipError_t launch_sparse_strip_gated(const MatArgs& m, const uint16_t* x, int k_tok, uint16_t* m_out, int tg, hipStream_t s);
 
 // Device address, on the current device, of the library's static scratch array (kStaticScratchBytes bytes, 256-byte
 // aligned): looked up once per device, no allocation.  Calls that use it on one GPU share it.
@@ -192,9 +192,11 @@ constexpr int kLmMaxHidden = 9216;
 hipError_t launch_lm_head(const uint16_t* w, const float* h, int vocab, int hidden, int k_tok, void* part_ws,
                           int32_t* token_ids, float* max_logit, float* logits, hipStream_t s);
 
-// the same streaming kernel as a plain dense linear (final y, tokens [0, k_tok), k_tok <= 16; k_in % 128 == 0, <= 9216)
-hipError_t launch_dense_stream_linear(const uint16_t* w, const uint16_t* x, int n_out, int k_in, int k_tok, float* y,
+// the same streaming kernel as a plain dense linear (final y, passes of 16 tg tokens; k_in % 128 == 0, <= 9216)
+hipError_t launch_dense_stream_linear(const uint16_t* w, const uint16_t* x, int n_out, int k_in, int k_tok, float* y, int tg,
                                       hipStream_t s);
 inline bool dense_stream_ok(int k_in) { return k_in % 128 == 0 && k_in <= kLmMaxHidden; }
+// up to 4096 columns the kernel can take two token groups per pass
+inline bool dense_stream_pair_ok(int k_in) { return dense_stream_ok(k_in) && k_in <= 4096; }
 
 }  // namespace sd2

@@ -229,29 +229,41 @@ __global__ __launch_bounds__(256) void sparse_linear_kernel(const DirEnt* __rest
 
 // ------------------------------------------------------------------ sparse linear, final results in one launch
 //
-// The same tiles, walked so that no partial sums leave the compute unit (k_tok <= 16).  A workgroup owns strips
+// The same tiles, walked so that no partial sums leave the compute unit.  A workgroup owns strips
 // b, b + G, ...; the contraction of a strip is split over its wavefronts by slab: wavefront w owns slabs w, w + WAVES, ...
 // (SPW of them) and sums their tiles of a strip in its accumulator.  The wavefronts' 16 x 16 blocks of a strip meet in
-// LDS; every few strips a barrier that waits for LDS only lets the threads add them in a fixed order and write y.  A wavefront with one slab keeps that slab's activation columns in registers for the whole kernel; with
-// more slabs it fetches them per tile (they stay in the caches).  The streams of the next two tiles are in flight in
-// registers while the current one is expanded.
+// LDS; every few strips a barrier that waits for LDS only lets the threads add them in a fixed order and write y.  A
+// wavefront with one slab keeps that slab's activation columns in registers for the whole kernel; with more slabs it
+// fetches them per tile (they stay in the caches).  The streams of the next two tiles are in flight in registers while
+// the current one is expanded.
+//
+// More than 16 tokens: the grid's second dimension numbers passes of 16 TG tokens.  TG > 1: the tile is expanded once, and
+// each of its eight dense fragments goes through one matrix instruction per token group; with one slab per wavefront two
+// groups' activation columns fit its registers, otherwise they are fetched per 64-column step, one step ahead of the
+// expansion that consumes them.
+constexpr int kStripRound = 4;  // strip results (of 16 tokens each) between two workgroup barriers of the kernel below
+// strips per round for TG token groups; the gated variant needs whole pairs in a round
+constexpr int strip_round(int tg, bool gated) {
+    const int r = kStripRound / tg > 0 ? kStripRound / tg : 1;
+    return gated && (r & 1) ? r + 1 : r;
+}
+
 //
 // GATED: the matrix is [gate; up] (two halves of n_out / 2 rows that share the input) and what leaves the kernel is the
 // gated product bf16(silu(gate x) * (up x)), [k_tok][n_out / 2], written to y (as uint16): a workgroup then owns pairs
 // of strips, strip p of the gate half and strip p of the up half, which sit side by side in a round's slots.
-constexpr int kStripRound = 4;  // strips (whole pairs of them) between two workgroup barriers
-
-template <int MAXCH, int SPW, int WAVES, bool GATED = false>
+template <int MAXCH, int SPW, int WAVES, int TG, bool GATED = false>
 __global__ __launch_bounds__(64 * WAVES) void sparse_strip_kernel(const DirEnt* __restrict__ dir, const uint2* __restrict__ masks,
                                                                  const uint16_t* __restrict__ vals,
                                                                  const uint16_t* __restrict__ x_all, float* __restrict__ y_all,
                                                                  int n_out, int k_in, int k_tok_all, int n_strips, int n_slabs) {
-    // more than 16 tokens (matrices with few strips only): the grid's second dimension numbers passes of 16
-    const int pass = (int)blockIdx.y, k_tok = min(16, k_tok_all - 16 * pass);
-    const uint16_t* __restrict__ x = x_all + (size_t)pass * 16 * k_in;
-    float* __restrict__ y = GATED ? reinterpret_cast<float*>(reinterpret_cast<uint16_t*>(y_all) + (size_t)pass * 16 * (n_out / 2))
-                                  : y_all + (size_t)pass * 16 * n_out;
     extern __shared__ uint32_t strip_smem[];  // [WAVES][MAXCH * 256] tile buffers, then [kStripRound][WAVES][256] floats
+    // (the matrix is streamed once per pass; a pass is this kernel on its own slice of the activations and of the results)
+    const int pass = (int)blockIdx.y;
+    const uint16_t* __restrict__ x = x_all + (size_t)pass * (16 * TG) * k_in;
+    float* __restrict__ y = GATED ? reinterpret_cast<float*>(reinterpret_cast<uint16_t*>(y_all) + (size_t)pass * (16 * TG) * (n_out / 2))
+                                  : y_all + (size_t)pass * (16 * TG) * n_out;
+    const int k_tok = min(16 * TG, k_tok_all - pass * (16 * TG));
     __shared__ uint2 lut[16];
     const int tid = threadIdx.x;
     if (tid < 16) lut[tid] = make_expand_selector((uint32_t)tid);
@@ -261,6 +273,7 @@ __global__ __launch_bounds__(64 * WAVES) void sparse_strip_kernel(const DirEnt* 
     const int n = lane & 15, g = lane >> 4;
     uint32_t* buf = strip_smem + wave * (MAXCH * 256);
     float* red = reinterpret_cast<float*>(strip_smem + WAVES * (MAXCH * 256));
+    constexpr int kRound = strip_round(TG, GATED);  // strips per round: the slots of a round fit LDS
     // the strips this workgroup walks, in order: b, b + G, ... -- or, gated, the pairs (b, b + half), (b + G, b + G + half), ...
     const int n_units = GATED ? n_strips / 2 : n_strips;
     const int my_units = (n_units - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
@@ -277,10 +290,13 @@ __global__ __launch_bounds__(64 * WAVES) void sparse_strip_kernel(const DirEnt* 
         return (wave + WAVES * j) * n_strips + strip_of(i);
     };
 
-    // The strips are handled in rounds: every wavefront leaves its block of a strip in the strip's slot, one barrier (LDS
-    // only: streams stay in flight) ends the round, and the threads share the adding: entry e of a block is token
-    // (e & 63) >> 2, row 4 (e >> 6) + (e & 3) of the strip.  A second barrier frees the slots.
-    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    // The strips are handled in rounds of kRound: every wavefront leaves its blocks of a strip (one per token group) in
+    // the strip's slot, one barrier (LDS only: streams stay in flight) ends the round, and the threads share the adding:
+    // entry e of a block is token 16 tg + ((e & 63) >> 2), row 4 (e >> 6) + (e & 3) of the strip.  A second barrier
+    // frees the slots.
+    f32x4 acc[TG];
+#pragma unroll
+    for (int tg = 0; tg < TG; ++tg) acc[tg] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto round_end = [&](int i_first, int n_in_round) {
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
         __builtin_amdgcn_s_barrier();
@@ -289,27 +305,27 @@ __global__ __launch_bounds__(64 * WAVES) void sparse_strip_kernel(const DirEnt* 
             // a round holds whole pairs: slot 2 r is the gate strip, slot 2 r + 1 the up strip of pair r
             const int half_rows = n_out / 2;
             uint16_t* m_out = reinterpret_cast<uint16_t*>(y);
-            for (int idx = tid; idx < (n_in_round / 2) * 256; idx += 64 * WAVES) {
-                const int e = idx & 255, r = idx >> 8;
-                const float* slot = red + (size_t)(2 * r) * (WAVES * 256);
+            for (int idx = tid; idx < (n_in_round / 2) * TG * 256; idx += 64 * WAVES) {
+                const int e = idx & 255, tg = (idx >> 8) % TG, r = (idx >> 8) / TG;
+                const float* slot = red + (size_t)(2 * r) * (WAVES * TG * 256) + tg * 256;
                 float gv = 0.f, uv = 0.f;
 #pragma unroll
                 for (int ww = 0; ww < WAVES; ++ww) {
-                    gv += slot[ww * 256 + e];
-                    uv += slot[WAVES * 256 + ww * 256 + e];
+                    gv += slot[ww * (TG * 256) + e];
+                    uv += slot[WAVES * TG * 256 + ww * (TG * 256) + e];
                 }
-                const int tok = (e & 63) >> 2;
+                const int tok = 16 * tg + ((e & 63) >> 2);
                 const int row = strip_of(i_first + 2 * r) * 16 + 4 * (e >> 6) + (e & 3);
                 if (row < half_rows && tok < k_tok) m_out[(size_t)tok * half_rows + row] = f32_to_bf16(gv / (1.0f + expf(-gv)) * uv);
             }
         } else {
-            for (int idx = tid; idx < n_in_round * 256; idx += 64 * WAVES) {
-                const int e = idx & 255, r = idx >> 8;
-                const float* slot = red + (size_t)r * (WAVES * 256);
+            for (int idx = tid; idx < n_in_round * TG * 256; idx += 64 * WAVES) {
+                const int e = idx & 255, tg = (idx >> 8) % TG, r = (idx >> 8) / TG;
+                const float* slot = red + (size_t)r * (WAVES * TG * 256) + tg * 256;
                 float v = 0.f;
 #pragma unroll
-                for (int ww = 0; ww < WAVES; ++ww) v += slot[ww * 256 + e];
-                const int tok = (e & 63) >> 2;
+                for (int ww = 0; ww < WAVES; ++ww) v += slot[ww * (TG * 256) + e];
+                const int tok = 16 * tg + ((e & 63) >> 2);
                 const int row = strip_of(i_first + r) * 16 + 4 * (e >> 6) + (e & 3);
                 if (row < n_out && tok < k_tok) y[(size_t)tok * n_out + row] = v;
             }
@@ -319,9 +335,12 @@ __global__ __launch_bounds__(64 * WAVES) void sparse_strip_kernel(const DirEnt* 
         asm volatile("" ::: "memory");
     };
     auto strip_done = [&](int i) {  // lane (n, g) holds rows 4g..4g+3 of token n: entry (16 g + n) * 4 + v of the block
-        *reinterpret_cast<f32x4*>(red + (size_t)(i % kStripRound) * (WAVES * 256) + wave * 256 + lane * 4) = acc;
-        acc = f32x4{0.f, 0.f, 0.f, 0.f};
-        if ((i + 1) % kStripRound == 0 || i + 1 == my_strips) round_end(i - i % kStripRound, i % kStripRound + 1);
+#pragma unroll
+        for (int tg = 0; tg < TG; ++tg) {
+            *reinterpret_cast<f32x4*>(red + (size_t)(i % kRound) * (WAVES * TG * 256) + (wave * TG + tg) * 256 + lane * 4) = acc[tg];
+            acc[tg] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        if ((i + 1) % kRound == 0 || i + 1 == my_strips) round_end(i - i % kRound, i % kRound + 1);
     };
     if (n_mine == 0) {  // a wavefront without slabs contributes zeros and joins every barrier
 #pragma unroll 1
@@ -329,13 +348,19 @@ __global__ __launch_bounds__(64 * WAVES) void sparse_strip_kernel(const DirEnt* 
         return;
     }
 
-    Frag b[4][2];  // operand B: the slab's activation columns
+    // Operand B in registers: always for one token group; for two groups when the wavefront owns a single slab (its
+    // activation columns then never change).  Otherwise B is fetched per 64-column step (below).
+    constexpr bool kBRegs = TG == 1 || (TG == 2 && SPW == 1);
+    constexpr int kBG = kBRegs ? TG : 1;
+    Frag b[kBG][4][2];
     auto load_b = [&](int slab) {
         const int col0 = slab * 256 + 16 * g;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) load_row16(x, n, k_tok, col0 + 64 * q, k_in, b[q][0], b[q][1]);
+        for (int tg = 0; tg < kBG; ++tg)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) load_row16(x, n + 16 * tg, k_tok, col0 + 64 * q, k_in, b[tg][q][0], b[tg][q][1]);
     };
-    if (SPW == 1) load_b(wave);
+    if (kBRegs && SPW == 1) load_b(wave);
 
     // two tiles' streams are in flight in registers while a third is expanded
     u32x4 st[2][MAXCH];
@@ -356,12 +381,36 @@ __global__ __launch_bounds__(64 * WAVES) void sparse_strip_kernel(const DirEnt* 
         for (int c = 0; c < MAXCH; ++c) reinterpret_cast<u32x4*>(buf)[c * 64 + lane] = st[slot][c];
         const uint2 mk = mkn[slot];
         const DirEnt de = den[slot];
-        if (SPW > 1) load_b(wave + WAVES * j);
-        request(slot, f + 2);
-        expand_tile<SD2_LINEAR_STEPS>(reinterpret_cast<const uint8_t*>(buf), lut, de.base, mk, [&](int q, const Frag& f0, const Frag& f1) {
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f0.v, b[q][0].v, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1.v, b[q][1].v, acc, 0, 0, 0);
-        });
+        if (kBRegs) {
+            if (SPW > 1) load_b(wave + WAVES * j);
+            request(slot, f + 2);
+            expand_tile<SD2_LINEAR_STEPS>(reinterpret_cast<const uint8_t*>(buf), lut, de.base, mk,
+                                          [&](int q, const Frag& f0, const Frag& f1) {
+#pragma unroll
+                                              for (int tg = 0; tg < kBG; ++tg) {
+                                                  acc[tg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f0.v, b[tg][q][0].v, acc[tg], 0, 0, 0);
+                                                  acc[tg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1.v, b[tg][q][1].v, acc[tg], 0, 0, 0);
+                                              }
+                                          });
+        } else {
+            // operand B of step q for every token group, requested one step ahead of its use
+            const int col0 = (wave + WAVES * j) * 256 + 16 * g;
+            Frag bb[2][TG][2];
+            auto load_bq = [&](int q) {
+#pragma unroll
+                for (int tg = 0; tg < TG; ++tg) load_row16(x, n + 16 * tg, k_tok, col0 + 64 * q, k_in, bb[q & 1][tg][0], bb[q & 1][tg][1]);
+            };
+            load_bq(0);
+            request(slot, f + 2);
+            expand_tile<1>(reinterpret_cast<const uint8_t*>(buf), lut, de.base, mk, [&](int q, const Frag& f0, const Frag& f1) {
+                if (q < 3) load_bq(q + 1);
+#pragma unroll
+                for (int tg = 0; tg < TG; ++tg) {
+                    acc[tg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f0.v, bb[q & 1][tg][0].v, acc[tg], 0, 0, 0);
+                    acc[tg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1.v, bb[q & 1][tg][1].v, acc[tg], 0, 0, 0);
+                }
+            });
+        }
         if (++j == n_mine) {
             j = 0;
             strip_done(i);
@@ -494,76 +543,92 @@ hipError_t launch_sparse_linear_valu(const MatArgs& m, const LinArgs& a, hipStre
     return launch_sparse_valu_t<5>(m, a, s);
 }
 
-// Slabs per wavefront and wavefronts per workgroup of the kernel that writes final results: one slab per wavefront up to
-// 16 slabs, two beyond (then with 16 wavefronts).  More than 32 slabs or tiles too dense for the 5 KiB buffers go to the
-// kernel with partial sums.
-static bool strip_shape(int n_slabs, int& spw, int& waves) {
-    if (n_slabs < 1 || n_slabs > 32) return false;
-    spw = n_slabs <= 16 ? 1 : 2;
+// Slabs per wavefront and wavefronts per workgroup of the kernel that writes final results.  One token group per pass: one
+// slab per wavefront up to 16 slabs, two beyond (then with 16 wavefronts).  More groups need more registers per wavefront, so
+// at most 12 wavefronts share a compute unit, and with four groups 8 (12 would spill).  More than 32 slabs or tiles too dense for
+// the 5 KiB buffers go to the kernel with partial sums.
+static bool strip_shape(int n_slabs, int tg, int& spw, int& waves) {
+    constexpr int kMostSlabs[5] = {0, 32, 24, 12, 8};
+    if (n_slabs < 1 || tg < 1 || tg > 4 || n_slabs > kMostSlabs[tg]) return false;
+    spw = n_slabs <= (tg == 1 ? 16 : 12) ? 1 : 2;
     const int need = (n_slabs + spw - 1) / spw;
     waves = std::max(4, (need + 3) / 4 * 4);
     return true;
 }
 
-bool sparse_strip_supported(const MatArgs& m, int k_tok) {
+bool sparse_strip_supported(const MatArgs& m, int tg) {
     int spw, waves;
-    return k_tok >= 1 && k_tok <= 64 && (m.max_tile_nnz * 2 + 8 + 1023) / 1024 <= 5 && strip_shape(m.n_slabs, spw, waves);
+    return (m.max_tile_nnz * 2 + 8 + 1023) / 1024 <= 5 && strip_shape(m.n_slabs, tg, spw, waves);
 }
 
-template <int SPW, int WAVES, bool GATED = false>
+template <int SPW, int WAVES, int TG, bool GATED = false>
 static hipError_t launch_strip_t(const MatArgs& m, const LinArgs& a, hipStream_t s) {
     constexpr int kCh = 5;
-    const size_t lds = (size_t)WAVES * kCh * 1024 + (size_t)kStripRound * WAVES * 256 * sizeof(float);
+    constexpr int kRound = strip_round(TG, GATED);
+    const size_t lds = (size_t)WAVES * kCh * 1024 + (size_t)kRound * TG * WAVES * 256 * sizeof(float);
     static std::atomic<int> cached{0};  // workgroups resident on the chip; threads that race here compute the same value
     int resident = cached.load(std::memory_order_acquire);
     if (resident == 0) {
-        const void* fn = reinterpret_cast<const void*>(sparse_strip_kernel<kCh, SPW, WAVES, GATED>);
+        const void* fn = reinterpret_cast<const void*>(sparse_strip_kernel<kCh, SPW, WAVES, TG, GATED>);
         int per_cu = 0;
         if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) return hipErrorInvalidValue;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 64 * WAVES, lds) != hipSuccess || per_cu < 1) per_cu = 1;
         resident = device_cu_count() * per_cu;
         cached.store(resident, std::memory_order_release);
     }
-    const int grid = std::min(GATED ? m.n_strips / 2 : m.n_strips, resident);
-    hipLaunchKernelGGL((sparse_strip_kernel<kCh, SPW, WAVES, GATED>), dim3((unsigned)grid, (unsigned)((a.k_tok + 15) / 16)), dim3(64 * WAVES), lds, s,
+    const int grid = std::min(GATED ? m.n_strips / 2 : m.n_strips, resident), passes = (a.k_tok + 16 * TG - 1) / (16 * TG);
+    hipLaunchKernelGGL((sparse_strip_kernel<kCh, SPW, WAVES, TG, GATED>), dim3((unsigned)grid, (unsigned)passes), dim3(64 * WAVES), lds, s,
                        static_cast<const DirEnt*>(m.dir), m.masks, m.vals, a.x, a.out, m.n_out, m.k_in, a.k_tok, m.n_strips, m.n_slabs);
     return hipGetLastError();
 }
 
-// y[t][n] final (every entry written); sparse_strip_supported(m, k_tok) must hold
-hipError_t launch_sparse_strip_linear(const MatArgs& m, const LinArgs& a, hipStream_t s) {
+// y[t][n] final (every entry written), 16 tg tokens a pass; sparse_strip_supported(m, tg) must hold
+hipError_t launch_sparse_strip_linear(const MatArgs& m, const LinArgs& a, int tg, hipStream_t s) {
     int spw, waves;
-    if (!sparse_strip_supported(m, a.k_tok) || !strip_shape(m.n_slabs, spw, waves)) return hipErrorInvalidValue;
-#define SD2_STRIP_CASE(S, W) \
-    if (spw == S && waves == W) return launch_strip_t<S, W>(m, a, s)
-    SD2_STRIP_CASE(1, 4);
-    SD2_STRIP_CASE(1, 8);
-    SD2_STRIP_CASE(1, 12);
-    SD2_STRIP_CASE(1, 16);
-    SD2_STRIP_CASE(2, 12);
-    SD2_STRIP_CASE(2, 16);
+    if (a.k_tok < 1 || a.k_tok > 64 || !sparse_strip_supported(m, tg) || !strip_shape(m.n_slabs, tg, spw, waves)) return hipErrorInvalidValue;
+#define SD2_STRIP_CASE(S, W, T) \
+    if (spw == S && waves == W && tg == T) return launch_strip_t<S, W, T>(m, a, s)
+    SD2_STRIP_CASE(1, 4, 1);
+    SD2_STRIP_CASE(1, 8, 1);
+    SD2_STRIP_CASE(1, 12, 1);
+    SD2_STRIP_CASE(1, 16, 1);
+    SD2_STRIP_CASE(2, 12, 1);
+    SD2_STRIP_CASE(2, 16, 1);
+    SD2_STRIP_CASE(1, 4, 2);
+    SD2_STRIP_CASE(1, 8, 2);
+    SD2_STRIP_CASE(1, 12, 2);
+    SD2_STRIP_CASE(2, 8, 2);
+    SD2_STRIP_CASE(2, 12, 2);
+    SD2_STRIP_CASE(1, 4, 3);
+    SD2_STRIP_CASE(1, 8, 3);
+    SD2_STRIP_CASE(1, 12, 3);
+    SD2_STRIP_CASE(1, 4, 4);
+    SD2_STRIP_CASE(1, 8, 4);
 #undef SD2_STRIP_CASE
     return hipErrorInvalidValue;
 }
 
 // The gated product of a fused [gate; up] matrix in one launch: m_out [k_tok][n_out / 2] bf16 = bf16(silu(gate x) * (up x)).
-// One slab per wavefront (k_in <= 4096), whole strips per half.
-bool sparse_strip_gated_supported(const MatArgs& m, int k_tok) {
+// One slab per wavefront (k_in <= 4096, on two token groups 3072), whole strips per half.
+bool sparse_strip_gated_supported(const MatArgs& m, int tg) {
     int spw, waves;
-    return sparse_strip_supported(m, k_tok) && strip_shape(m.n_slabs, spw, waves) && spw == 1 && m.n_out % 32 == 0;
+    return sparse_strip_supported(m, tg) && strip_shape(m.n_slabs, tg, spw, waves) && spw == 1 && m.n_out % 32 == 0;
 }
 
-hipError_t launch_sparse_strip_gated(const MatArgs& m, const uint16_t* x, int k_tok, uint16_t* m_out, hipStream_t s) {
-    if (!sparse_strip_gated_supported(m, k_tok)) return hipErrorInvalidValue;
+hipError_t launch_sparse_strip_gated(const MatArgs& m, const uint16_t* x, int k_tok, uint16_t* m_out, int tg, hipStream_t s) {
+    if (k_tok < 1 || k_tok > 64 || !sparse_strip_gated_supported(m, tg)) return hipErrorInvalidValue;
     int spw, waves;
-    strip_shape(m.n_slabs, spw, waves);
+    strip_shape(m.n_slabs, tg, spw, waves);
     const LinArgs a{x, k_tok, reinterpret_cast<float*>(m_out)};
-#define SD2_GATED_CASE(W) \
-    if (waves == W) return launch_strip_t<1, W, true>(m, a, s)
-    SD2_GATED_CASE(4);
-    SD2_GATED_CASE(8);
-    SD2_GATED_CASE(12);
-    SD2_GATED_CASE(16);
+#define SD2_GATED_CASE(W, T) \
+    if (waves == W && tg == T) return launch_strip_t<1, W, T, true>(m, a, s)
+    SD2_GATED_CASE(4, 1);
+    SD2_GATED_CASE(8, 1);
+    SD2_GATED_CASE(12, 1);
+    SD2_GATED_CASE(16, 1);
+    SD2_GATED_CASE(4, 2);
+    SD2_GATED_CASE(8, 2);
+    SD2_GATED_CASE(12, 2);
 #undef SD2_GATED_CASE
     return hipErrorInvalidValue;
 }

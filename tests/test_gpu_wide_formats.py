@@ -36,19 +36,33 @@ def _matrix(rng, n, k, fmt):
     (333, 320, 33),     # n_out not a multiple of 4: scalar stores
     (4112, 1536, 32),   # more strips than one group per workgroup, ragged last block
     (96, 8960, 49),     # a long contraction: split over workgroups or passes
-    (5003, 832, 49),    # ragged rows, six units and a half, too many strips for passes of 16 tokens
-    (2560, 1024, 64),   # 2560 tiles of a bitmask in passes of 16 tokens: the most (one strip more: the wide kernel)
-    (2576, 1024, 64),
-    (2048, 512, 33),    # dense: passes of 16 tokens
+    (5003, 832, 49),    # ragged rows, six units and a half, too many strips for passes of 16 or 32 tokens
+    (5008, 768, 33),    # bitmask: 2817 tiles in passes of 16 tokens
+    (2048, 512, 33),    # passes of 16 tokens, the last of one
+    (2041, 1600, 64),   # two passes of 32 tokens, one slab per wavefront (bitmask), ragged rows
+    (2500, 3392, 17),   # one pass of 32 tokens, two slabs per wavefront (bitmask)
+    (2500, 2048, 49),   # bitmask: all 64 and all 48 tokens in one pass
+    (4096, 1024, 64),
+    (2500, 3008, 40),
+    (3300, 960, 48),
+    (8192, 64, 31),     # one short tile per strip; a dense matrix of one slab
+    (8000, 192, 24),
+    (1536, 512, 49),    # dense: passes of 32 tokens, one to four column chunks per wavefront
+    (2040, 2048, 64),
+    (1600, 3072, 40),
+    (2560, 4096, 17),
+    (600, 10240, 33),   # dense: more columns than the streaming kernel takes
 ])
 def test_wide_linear_exact_integers(n, k, k_tok, fmt):
     import gpu_util as gu
     rng = np.random.default_rng([5, n, k, k_tok])
     w = _matrix(rng, n, k, fmt)
     x = rng.integers(-4, 5, size=(k_tok, k))
+    if fmt == "2:4" and k > 9216:
+        pytest.skip("more columns than a 2:4 matrix may have")
     mat = gu.DenseMat(_ints(w)) if fmt == "dense" else gu.SparseMat(_ints(w), 3 if fmt == "2:4" else 1)
     y = gu.run_linear(mat, _ints(x), sparse=fmt != "dense")
-    assert np.array_equal(y.astype(np.int64), x @ w.T)
+    assert np.array_equal(y, x.astype(np.float64) @ w.T.astype(np.float64))  # sums below 2^24: exact in fp32 in any order
 
 
 @pytest.mark.parametrize("fmt", ["bitmask", "2:4", "dense"])
@@ -72,6 +86,10 @@ def test_wide_linear_many_strips_exact_integers(n, k, k_tok, fmt):
 
 @pytest.mark.parametrize("fmt", ["bitmask", "2:4", "dense"])
 @pytest.mark.parametrize("hidden,inter,k_tok", [(192, 48, 17), (512, 1200, 64),
+                                                (512, 2048, 33),   # bitmask gate|up in passes of 16 tokens, 256 workgroups and
+                                                (1216, 2048, 64),  # in passes of 32, one slab per wavefront
+                                                (448, 4096, 40),   # the same, short tiles
+                                                (1344, 4160, 20),  # one pass of 32, six slabs
                                                 (576, 12416, 40),  # gate|up: two groups of six wavefronts, two strip groups
                                                 (320, 16512, 64)])  # gate|up: four groups of two wavefronts, two passes
 def test_wide_mlp_gated(hidden, inter, k_tok, fmt):
