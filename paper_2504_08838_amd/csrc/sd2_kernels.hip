@@ -1163,6 +1163,7 @@ __global__ __launch_bounds__(128) void inflight_attention_kernel(const float* __
 hipError_t launch_inflight_attention(const float* part, int n_splits, int k_tok, int q_out, int kv_out, int n_heads,
                                      int n_kv, int head_dim, uint16_t* ctx, hipStream_t s) {
     if (k_tok < 1 || k_tok > 64 || head_dim < 8 || head_dim > 256 || head_dim % 8) return hipErrorInvalidValue;
+    // stacks of four layers on 9 to 16 tokens: 1 to 4 % faster than with the kernel below; eight and fewer tokens keep that kernel
     if (head_dim == 128 && k_tok > 8) return launch_inflight_attention_wide(part, n_splits, k_tok, q_out, kv_out, n_heads, n_kv, ctx, s);
     hipLaunchKernelGGL(inflight_attention_kernel, dim3((unsigned)n_heads, (unsigned)k_tok), dim3(128), 0, s, part, n_splits, k_tok,
                        q_out, kv_out, n_heads, n_kv, head_dim, ctx);
@@ -1397,6 +1398,9 @@ hipError_t launch_cached_attention(const float* q_rot, const uint16_t* k_cache, 
                                    int k_tok, int q_out, int n_heads, int n_kv, int head_dim, uint16_t* ctx, hipStream_t s) {
     if (!cached_attention_supported(n_heads, n_kv, head_dim, max_pos) || pos0 < 0 || pos0 + k_tok > max_pos)
         return hipErrorInvalidValue;
+    // On any number of tokens: eight dense layers, kernel below -> matrix cores, 12 heads on 2 key/value heads: 1 token behind 448
+    // positions 402 -> 263 us, behind 3000 1036 -> 491, 8 tokens 415 -> 280 and 1049 -> 511; 24 heads on 8: 1 token 340 -> 285 and
+    // 748 -> 570, 32 tokens 406 -> 338 and 800 -> 600.
     if (head_dim == 128) return launch_cached_attention_wide(q_rot, k_cache, v_cache, max_pos, pos0, k_tok, q_out, n_heads, n_kv, ctx, s);
     const int rep = n_heads / n_kv;
     // register arrays are sized for 4 or 8 query heads per key/value head
