@@ -189,10 +189,13 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
             asm volatile("" ::: "memory");
             issue_chunk(ci + kLmRing);
+            // (a column chunk past the matrix is a copy of the last one: its zero activations times an infinite weight would be NaN)
+            if (cc < CPW - 1 || wave + kLmWaves * cc < n_colchunks) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
+                for (int q = 0; q < 4; ++q)
 #pragma unroll
-                for (int tg = 0; tg < TG; ++tg) acc[tg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q].v, b[tg][cc][q].v, acc[tg], 0, 0, 0);
+                    for (int tg = 0; tg < TG; ++tg) acc[tg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q].v, b[tg][cc][q].v, acc[tg], 0, 0, 0);
+            }
             ++ci;
         }
         // one token group: the partial strips alternate between two buffers (one barrier per strip); two groups fill

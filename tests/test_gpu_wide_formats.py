@@ -213,13 +213,15 @@ def test_infinite_key_follows_the_sign_of_its_score(k_tok, pos0, sd2_options):
 
 
 @pytest.mark.parametrize("fmt", ["bitmask", "dense"])
+@pytest.mark.parametrize("k", [320, 384, 1152])
 @pytest.mark.parametrize("k_tok", [5, 17, 64])
-def test_infinite_weight_stays_in_its_row(k_tok, fmt):
-    """The infinity sits in the first column of the last, half unit, whose absent columns are read as that one."""
+def test_infinite_weight_stays_in_its_row(k_tok, k, fmt):
+    """The infinity sits in the first column of the last 64 or 128, where a kernel that reads absent columns as existing ones
+    would multiply it with zero: a half unit, wavefronts without a column chunk, a second chunk that one wavefront has."""
     import gpu_util as gu
     rng = np.random.default_rng([59, k_tok])
-    w = rng.integers(1, 9, size=(40, 320)).astype(np.float32)
-    w[7, 256] = np.inf
-    x = rng.integers(1, 5, size=(k_tok, 320)).astype(np.float32)
+    w = rng.integers(1, 9, size=(40, k)).astype(np.float32)
+    w[7, k - (64 if k == 320 else 128)] = np.inf
+    x = rng.integers(1, 5, size=(k_tok, k)).astype(np.float32)
     mat = gu.DenseMat(_ints(w)) if fmt == "dense" else gu.SparseMat(_ints(w), 1)
     assert np.array_equal(gu.run_linear(mat, _ints(x), sparse=fmt != "dense"), x @ w.T)
