@@ -79,8 +79,8 @@ def test_cfg1_single_linear(k_tok):
     (333, 64, 50, 1, "row"),        # n_out not a multiple of 4: scalar stores
     (64, 8960, 66, 5, "row"),
     (256, 3072, 75, 16, "row"),
-    (256, 3072, 50, 17, "row"),     # two token groups
-    (128, 1024, 50, 33, "row"),     # three token groups (runs as four)
+    (256, 3072, 50, 17, "row"),     # two passes of 16 tokens; with partial sums two token groups
+    (128, 1024, 50, 33, "row"),     # three passes; with partial sums three token groups (runs as four)
     (128, 1024, 50, 64, "row"),
     (8192, 3072, 50, 5, "row"),     # several tiles per wavefront: exercises the prefetch pipeline
     (8192, 3072, 30, 5, "row"),     # dense tiles: the large LDS staging variant

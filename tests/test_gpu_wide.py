@@ -57,10 +57,10 @@ def test_full_size_linears_element_by_element(full_size_mats, which, k_tok, kern
 
 
 @pytest.mark.parametrize("n,k,k_tok", [
-    (96, 1280, 40),     # three token groups, one slab per wavefront
-    (200, 3328, 64),    # four groups, 13 slabs: two slabs per wavefront, ragged rows
-    (48, 8960, 17),     # 35 slabs: three per wavefront
-    (64, 12288, 33),    # 48 slabs: four per wavefront
+    (96, 1280, 40),     # three passes of 16 tokens, one slab per wavefront
+    (200, 3328, 64),    # four passes, 13 slabs, ragged rows
+    (48, 8960, 17),     # 35 slabs: the wide kernel, the contraction split
+    (64, 12288, 33),    # 48 slabs
     (1040, 512, 64),    # more strips than one round per workgroup, ragged last strip
 ])
 def test_wide_exact_integers(n, k, k_tok):
