@@ -198,19 +198,21 @@ __device__ __forceinline__ void expand_tile(const uint8_t* __restrict__ bufb, co
 }
 
 // The same request with the value stream written straight into LDS (no staging registers): piece c of the
-// tile lands at lds_buf + c * 1024 bytes, 16 bytes per lane in lane order.  lds_buf is wave-uniform.  The
+// tile lands at lds_buf + c * 1024 bytes, 16 bytes per lane in lane order; pieces past the tile's last are
+// not requested.  lds_buf is wave-uniform.  The
 // data is in LDS once the wavefront's vector-memory counter has drained (s_waitcnt vmcnt(0)).
 template <int MAXCH>
 __device__ __forceinline__ void issue_tile_lds(uint32_t* lds_buf, uint2& mk, const uint16_t* __restrict__ vals,
                                                const uint2* __restrict__ tile_masks, uint32_t val_start, uint32_t nnz,
                                                int lane) {
-    const u32x4* __restrict__ src = reinterpret_cast<const u32x4*>(vals + (size_t)val_start * 8);
+    // The stream as a buffer of exactly its length: its base, its length and the piece's offset are scalars, so a request costs
+    // no vector instruction, and pieces past the end ask memory for nothing (the hardware's range check).
     const uint32_t n16 = (nnz * 2 + 8 + 15) / 16;
+    const auto stream = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint8_t*>(reinterpret_cast<const uint8_t*>(vals)) + (size_t)val_start * 16, 0, (int)(n16 * 16u), 0x00020000);
 #pragma unroll
     for (int c = 0; c < MAXCH; ++c)
-        __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void*)(src + min((uint32_t)(c * 64 + lane), n16 - 1u)),
-            (__attribute__((address_space(3))) void*)(lds_buf + c * 256), 16, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(stream, (__attribute__((address_space(3))) void*)(lds_buf + c * 256), 16, lane * 16, c * 1024, 0, 0);
     mk = tile_masks[lane];
 }
 

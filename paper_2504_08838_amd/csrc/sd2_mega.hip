@@ -109,7 +109,7 @@ typedef const __attribute__((address_space(4))) MegaArgs* KArgs;
 // the matrix, so every position of the s_eff x b_eff block is a real tile) and the blob offsets common to all
 // layers of the kind.
 constexpr int kMaxTilesPerWave = 8;  // per phase: ceil(kMaxS * kMaxB / waves)
-constexpr int kFlushIters = (kMaxS * kMegaMaxTok * 16 + kMegaThreads - 1) / kMegaThreads;  // results per thread leaving the CU
+constexpr int kFlushIters = ((kMaxS + 3) / 4 * kMegaMaxTok + kMegaWaves - 1) / kMegaWaves;  // items per wavefront leaving the CU
 
 
 __device__ __forceinline__ int uni(uint32_t v) { return __builtin_amdgcn_readfirstlane((int)v); }
@@ -184,8 +184,7 @@ __device__ __forceinline__ uint32_t lane_word(uint32_t v, int l) { return (uint3
 // dead -- the request before it into that buffer was drained by a full wait (vmcnt(0): nothing here is decided by
 // counting outstanding loads, so no assumption about their completion order is made), and the expansion that read
 // those contents has ended, i.e. its LDS reads have returned (their results were consumed before this point in
-// program order).  A wavefront never has two requests for one buffer in flight.  Lanes past a tile's last 16-byte
-// piece repeat that piece's source address, each into a destination of its own that no window reads.
+// program order).  A wavefront never has two requests for one buffer in flight.
 template <bool NM24>
 __device__ __forceinline__ void issue_phase_tile(const PhaseTiles& pt, int j, uint32_t* lds_buf, uint2& mk, int lane) {
     if (lane_word(pt.key, 8 * j) & kKeyEmpty) {  // nothing stored for it: all-zero masks expand to zeros
@@ -676,22 +675,33 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
             tpre.v[0] = tpre.v[1] = tpre.v[2] = tpre.v[3] = u32x4{0, 0, 0, 0};
             tpre.idx = make_uint2(0u, 0u);
         }
+        // How the block's results leave the compute unit: an item is four strips (64 consecutive rows, one per lane) of one
+        // token, items are dealt to the wavefronts; everything but the row is wave-uniform.
+        const bool active = uni(plans[kind * kPlanDw + 6]) != 0;
+        const int strip_lo = uni(plans[kind * kPlanDw + 2]);
+        const int n_items = active ? ((ge.s_blk + 3) >> 2) * k_tok : 0;
+        const int row_hi = min(ge.n_out, (strip_lo + ge.s_blk) * 16);
+        struct Item {
+            int t, quad;
+        };
+        auto item_at = [&](int i) {
+            Item it;
+            it.quad = (int)(((uint32_t)i * tok_mul) >> 10);
+            it.t = i - it.quad * k_tok;
+            return it;
+        };
         // The next version of the residual stream starts from zero and receives every slab block's contribution by
         // integer adds; the workgroups of the first slab block add the current version along with theirs.  Their
         // entries of it are requested here, between arrival and release (final since the barrier before last).
-        const int slab_block = cu / ka->geo[kind].n_sblk;
-        const uint32_t* kpl_s = plans + kind * kPlanDw;
-        const int strip_lo_s = uni(kpl_s[2]);
-        const bool adds_residual = (kind & 1) && uni(kpl_s[6]) != 0 && slab_block == 0;
+        const bool adds_residual = (kind & 1) && uni(plans[kind * kPlanDw + 3]) == 0;
         const int* h_seed_src = a.hv + (size_t)(2 * layer + (kind >= 2 ? 1 : 0)) * a.h_stride;
         int hseed[kFlushIters];
 #pragma unroll
         for (int j = 0; j < kFlushIters; ++j) {
             hseed[j] = 0;
-            const int idx = tid + j * kMegaThreads;
-            const int r = idx & 15, sl = (int)(((uint32_t)(idx >> 4) * tok_mul) >> 10), t = (idx >> 4) - sl * k_tok;
-            const int strip = strip_lo_s + sl, row = strip * 16 + r;
-            if (adds_residual && sl < ge.s_blk && strip < ge.n_strips && row < ge.n_out) hseed[j] = h_seed_src[(size_t)t * ge.n_out + row];
+            const Item it = item_at(wave + j * kMegaWaves);
+            const int row = (strip_lo + 4 * it.quad) * 16 + lane;
+            if (adds_residual && wave + j * kMegaWaves < n_items && row < row_hi) hseed[j] = h_seed_src[(size_t)it.t * ge.n_out + row];
         }
 
         if (PROBE && tt && tid == 0) tt[4] = __builtin_amdgcn_s_memrealtime();
@@ -701,8 +711,6 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
 
         // ---------------- prologue: the activation columns of this workgroup's slabs, as bf16 in LDS
         const uint32_t* kpl = plans + kind * kPlanDw;
-        const bool active = uni(kpl[6]) != 0;
-        const int strip_lo = uni(kpl[2]);
         const int col_lo = uni(kpl[3]) * 256;                                     // first column of the block
         const int n_col = active ? max(0, min(ge.b_blk * 256, ge.k_in - col_lo)) : 0;  // columns that exist
         const int nqkv = a.q_out + 2 * a.kv_out;
@@ -979,6 +987,10 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
         lds_barrier();
         if (tt && tid == 0) tt[2] = __builtin_amdgcn_s_memrealtime();
 
+        // waited for here, where everything requested before the release has landed: at their use the next stream is in flight
+#pragma unroll
+        for (int j = 0; j < kFlushIters; ++j) asm volatile("" : "+v"(hseed[j]));
+
         // ---------------- this wave's tiles of the phase
         int cur_slab = -1;
         Frag b[4][2];
@@ -1065,26 +1077,34 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
         if (tt && tid == 0) tt[3] = __builtin_amdgcn_s_memrealtime();
 
         // ---------------- the block's results leave the CU: split-K across the slab blocks by exact fixed-point adds
-        if (active) {
+        // Bound by its instructions and one LDS round trip: every wavefront has one item at the usual sizes (five tokens, at most
+        // eight strips), whose index arithmetic is scalar, whose slots are all read before the first add and whose 64 adds
+        // are one contiguous request.  No load may be waited for here: the next phase's first stream is in flight and would
+        // be waited for too.  (A result per thread, with divisions per lane and three spilled registers reloaded here, took 0.12 us
+        // more per phase; with the streams requested as buffers and nothing spilled the 3B shape's forward went from 1018 to
+        // 991 us, its decode step from 1296 to 1221.)
+        if (n_items > 0) {
             int* ybase = kind == 0 ? yq : (kind == 2 ? yg : h_nxt);
             const float scale = a.fix_scale, lim = ka->fix_limit[kind];
             bool bad = false;
+            const float* lane_slot = red + (lane >> 4) * n_grp * (kMegaMaxTok * 16) + (lane & 15);
 #pragma unroll
             for (int j = 0; j < kFlushIters; ++j) {
-                const int idx = tid + j * kMegaThreads;
-                if (idx >= ge.s_blk * k_tok * 16) break;
-                const int r = idx & 15, sl = (int)(((uint32_t)(idx >> 4) * tok_mul) >> 10), t = (idx >> 4) - sl * k_tok;
-                float v = 0.f;
-                for (int gq = 0; gq < n_grp; ++gq) {  // the strip's slab groups, each summed by one wavefront
-                    float* slot = red + (((sl * n_grp + gq) * kMegaMaxTok + t) << 4) + r;
-                    v += *slot;
-                    *slot = 0.f;
-                }
-                const int strip = strip_lo + sl, row = strip * 16 + r;
-                if (strip < ge.n_strips && row < ge.n_out) {
+                const int i = wave + j * kMegaWaves;
+                if (i >= n_items) break;
+                const Item it = item_at(i);
+                const int row = (strip_lo + 4 * it.quad) * 16 + lane;
+                if (row < row_hi) {
+                    const float* slot = lane_slot + (4 * it.quad * n_grp * kMegaMaxTok + it.t) * 16;
+                    float part[kMaxB];  // the strip's slab groups, each summed by one wavefront: read in one go
+#pragma unroll
+                    for (int gq = 0; gq < kMaxB; ++gq) part[gq] = gq < n_grp ? slot[gq * kMegaMaxTok * 16] : 0.f;
+                    float v = part[0];
+#pragma unroll
+                    for (int gq = 1; gq < kMaxB; ++gq) v += part[gq];
                     const float sv = v * scale;
                     bad |= !(fabsf(sv) < lim);  // also true for NaN
-                    aadd_i(ybase + (size_t)t * ge.n_out + row, (int)__builtin_rintf(fminf(fmaxf(sv, -lim), lim)) + hseed[j]);
+                    aadd_i(ybase + (size_t)it.t * ge.n_out + row, (int)__builtin_rintf(fminf(fmaxf(sv, -lim), lim)) + hseed[j]);
                 }
             }
             if (bad) __hip_atomic_fetch_or(a.err, 2u, __ATOMIC_RELAXED, SD2_AGENT);  // the call's results are invalid
