@@ -232,14 +232,17 @@ int gated_pass_groups(const sd2_matrix_t* m, int k_tok, LinearCut& c) {
 }
 inline bool wide_choice(const sd2_matrix_t* m, int k_tok, LinearCut& c) { return pass_groups(m, k_tok, c) == 0; }
 
+inline bool dense_gated_ok(const sd2_matrix_t* m) { return m->kind == SD2_KIND_DENSE && dense_stream_gated_ok(m->info.n_out, m->info.k_in); }
+
 // The gate|up linear and the gated product in one launch (the kernels that add the slabs up inside the workgroup).
 inline bool gated_ok(const sd2_matrix_t* m, int k_tok, LinearCut& c) {
     const int tg = gated_pass_groups(m, k_tok, c);
-    return tg == 0 || strip_gated_ok(m, tg);
+    return tg == 0 || strip_gated_ok(m, tg) || dense_gated_ok(m);
 }
 hipError_t run_gated(const sd2_matrix_t* m, const uint16_t* x, int k_tok, uint16_t* out, hipStream_t s, LinearCut& c) {
     const int tg = gated_pass_groups(m, k_tok, c);
     if (tg == 0) return launch_wide_linear(mat_args(m), is_nm24(m), x, k_tok, out, true, c.plan, s);
+    if (m->kind == SD2_KIND_DENSE) return launch_dense_stream_gated(mat_args(m).w, x, nullptr, m->info.n_out, m->info.k_in, k_tok, out, s);
     return launch_sparse_strip_gated(mat_args(m), x, k_tok, out, tg, s);
 }
 
@@ -297,6 +300,29 @@ int linear_entry(const sd2_matrix_t* m, int kind, const uint16_t* x, int32_t k_t
     }
     return run_final(m, x, k_tok, y, static_cast<float*>(ws), s);
 }
+
+// The glue of a stack run as one launch per linear: where a linear cannot take the norm of its input itself, or cannot add its
+// results to the residual, a launch between them does.  `fused` off keeps every step a launch of its own (a trace records what
+// lies between them).
+struct StackGlue {
+    int k_tok, hidden;
+    float *h, *part, *ssq;
+    bool fused;
+    hipStream_t s;
+    // next linear takes bf16(norm(h)) from h itself
+    bool norms_itself(const sd2_matrix_t* next, bool gated, LinearCut& gated_cut) const {
+        if (!fused || next->kind != SD2_KIND_DENSE || !dense_stream_norm_ok(next->info.k_in, k_tok)) return false;
+        return !gated || (gated_ok(next, k_tok, gated_cut) && dense_gated_ok(next));
+    }
+    // h += the linear's results; act_out: where the norm of the sum goes, null where nobody wants it
+    hipError_t close(const sd2_matrix_t* m, const uint16_t* x, LinearCut& cut, uint16_t* act_out) const {
+        const bool added = fused && m->kind == SD2_KIND_DENSE && dense_stream_add_ok(m->info.n_out, m->info.k_in, k_tok);
+        const hipError_t e = added ? launch_dense_stream_add(mat_args(m).w, x, m->info.n_out, m->info.k_in, k_tok, h, s)
+                                   : run_linear(m, x, k_tok, part, s, &cut);
+        if (e != hipSuccess || (added && !act_out)) return e;
+        return launch_residual_rmsnorm(h, nullptr, part, added ? 0 : n_splits(m, k_tok, cut), k_tok, hidden, act_out, ssq, s);
+    }
+};
 
 struct StackLayout {
     size_t act_off, act2_off, part_off, ssq_off, total;  // two activation buffers: a fused kernel reads one and writes the other
@@ -682,21 +708,29 @@ static int forward_impl(const sd2_model_t* md, const uint16_t* h_in, int32_t k_t
         }
         return hipSuccess;
     };
-    SD2_TRY(launch_residual_rmsnorm(h, h_in, nullptr, 0, k_tok, sh.hidden, sh.layers > 0 ? act : nullptr, ssq, s));
+    const StackGlue glue{k_tok, sh.hidden, h, part, ssq, trace == nullptr, s};
+    bool self = sh.layers > 0 && glue.norms_itself(&md->mats[0], false, cuts.gated);
+    SD2_TRY(launch_residual_rmsnorm(h, h_in, nullptr, 0, k_tok, sh.hidden, sh.layers > 0 && !self ? act : nullptr, ssq, s));
     for (int l = 0; l < sh.layers; ++l) {
         const sd2_matrix_t* qkv = &md->mats[4 * l + 0];
         const sd2_matrix_t* o = &md->mats[4 * l + 1];
         const sd2_matrix_t* gu = &md->mats[4 * l + 2];
         const sd2_matrix_t* dn = &md->mats[4 * l + 3];
         SD2_TRY(record(4 * l + 0, h, nullptr, 0, sh.hidden, sh.hidden));
-        SD2_TRY(run_linear(qkv, act, k_tok, part, s, &cuts.lin[0]));
+        if (self) {
+            SD2_TRY(launch_dense_stream_norm(mat_args(qkv).w, h, qkv->info.n_out, qkv->info.k_in, k_tok, part, s));
+        } else {
+            SD2_TRY(run_linear(qkv, act, k_tok, part, s, &cuts.lin[0]));
+        }
         SD2_TRY(launch_inflight_attention(part, n_splits(qkv, k_tok, cuts.lin[0]), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv,
                                           sh.head_dim, act, s));
         SD2_TRY(record(4 * l + 1, nullptr, part, n_splits(qkv, k_tok, cuts.lin[0]), sh.q_out + 2 * sh.kv_out, sh.q_out));
-        SD2_TRY(run_linear(o, act, k_tok, part, s, &cuts.lin[1]));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok, cuts.lin[1]), k_tok, sh.hidden, act, ssq, s));
+        self = glue.norms_itself(gu, true, cuts.gated);
+        SD2_TRY(glue.close(o, act, cuts.lin[1], self ? nullptr : act));
         SD2_TRY(record(4 * l + 2, h, nullptr, 0, sh.hidden, sh.hidden));
-        if (!trace && gated_ok(gu, k_tok, cuts.gated)) {
+        if (self) {
+            SD2_TRY(launch_dense_stream_gated(mat_args(gu).w, nullptr, h, gu->info.n_out, gu->info.k_in, k_tok, act, s));
+        } else if (!trace && gated_ok(gu, k_tok, cuts.gated)) {
             // one launch: the gated product is written by the linear's own epilogue (act is read and written: the
             // kernel has taken its input columns into registers before the first result leaves)
             SD2_TRY(run_gated(gu, act, k_tok, act2, s, cuts.gated));
@@ -706,9 +740,9 @@ static int forward_impl(const sd2_model_t* md, const uint16_t* h_in, int32_t k_t
             SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok, cuts.lin[2]), k_tok, sh.inter, act, s));
         }
         SD2_TRY(record(4 * l + 3, nullptr, part, n_splits(gu, k_tok, cuts.lin[2]), 2 * sh.inter, sh.inter));
-        SD2_TRY(run_linear(dn, act, k_tok, part, s, &cuts.lin[3]));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok, cuts.lin[3]), k_tok, sh.hidden,
-                                        l + 1 < sh.layers ? act : nullptr, ssq, s));
+        const bool last = l + 1 == sh.layers;
+        self = !last && glue.norms_itself(&md->mats[4 * (l + 1)], false, cuts.gated);
+        SD2_TRY(glue.close(dn, act, cuts.lin[3], last || self ? nullptr : act));
     }
 #undef SD2_TRY
     return SD2_OK;
@@ -852,7 +886,9 @@ int sd2_sparse_drafter_decode(const sd2_model_t* md, const uint16_t* h_in, int32
     if ((expr) != hipSuccess) return SD2_ERR_HIP
     StackCuts cuts(md, L.part_rows);
     SD2_TRY(launch_rope_table(pos0, k_tok, sh.head_dim, rope_theta, table, s));
-    SD2_TRY(launch_residual_rmsnorm(h, h_in, nullptr, 0, k_tok, sh.hidden, sh.layers > 0 ? act : nullptr, ssq, s));
+    const StackGlue glue{k_tok, sh.hidden, h, part, ssq, true, s};
+    bool self = sh.layers > 0 && glue.norms_itself(&md->mats[0], false, cuts.gated);
+    SD2_TRY(launch_residual_rmsnorm(h, h_in, nullptr, 0, k_tok, sh.hidden, sh.layers > 0 && !self ? act : nullptr, ssq, s));
     for (int l = 0; l < sh.layers; ++l) {
         const sd2_matrix_t* qkv = &md->mats[4 * l + 0];
         const sd2_matrix_t* o = &md->mats[4 * l + 1];
@@ -860,22 +896,28 @@ int sd2_sparse_drafter_decode(const sd2_model_t* md, const uint16_t* h_in, int32
         const sd2_matrix_t* dn = &md->mats[4 * l + 3];
         uint16_t* kc = k_cache + (size_t)l * layer_elems;
         uint16_t* vc = v_cache + (size_t)l * layer_elems;
-        SD2_TRY(run_linear(qkv, act, k_tok, part, s, &cuts.lin[0]));
+        if (self) {
+            SD2_TRY(launch_dense_stream_norm(mat_args(qkv).w, h, qkv->info.n_out, qkv->info.k_in, k_tok, part, s));
+        } else {
+            SD2_TRY(run_linear(qkv, act, k_tok, part, s, &cuts.lin[0]));
+        }
         SD2_TRY(launch_rope_append(part, n_splits(qkv, k_tok, cuts.lin[0]), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv, sh.head_dim, table,
                                    pos0, max_pos, q_rot, kc, vc, s));
         SD2_TRY(launch_cached_attention(q_rot, kc, vc, max_pos, pos0, k_tok, sh.q_out, sh.n_heads, sh.n_kv, sh.head_dim, act, s));
-        SD2_TRY(run_linear(o, act, k_tok, part, s, &cuts.lin[1]));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(o, k_tok, cuts.lin[1]), k_tok, sh.hidden, act, ssq, s));
-        if (gated_ok(gu, k_tok, cuts.gated)) {
+        self = glue.norms_itself(gu, true, cuts.gated);
+        SD2_TRY(glue.close(o, act, cuts.lin[1], self ? nullptr : act));
+        if (self) {
+            SD2_TRY(launch_dense_stream_gated(mat_args(gu).w, nullptr, h, gu->info.n_out, gu->info.k_in, k_tok, act, s));
+        } else if (gated_ok(gu, k_tok, cuts.gated)) {
             SD2_TRY(run_gated(gu, act, k_tok, act2, s, cuts.gated));
             std::swap(act, act2);
         } else {
             SD2_TRY(run_linear(gu, act, k_tok, part, s, &cuts.lin[2]));
             SD2_TRY(launch_silu_mul(part, n_splits(gu, k_tok, cuts.lin[2]), k_tok, sh.inter, act, s));
         }
-        SD2_TRY(run_linear(dn, act, k_tok, part, s, &cuts.lin[3]));
-        SD2_TRY(launch_residual_rmsnorm(h, nullptr, part, n_splits(dn, k_tok, cuts.lin[3]), k_tok, sh.hidden,
-                                        l + 1 < sh.layers ? act : nullptr, ssq, s));
+        const bool last = l + 1 == sh.layers;
+        self = !last && glue.norms_itself(&md->mats[4 * (l + 1)], false, cuts.gated);
+        SD2_TRY(glue.close(dn, act, cuts.lin[3], last || self ? nullptr : act));
     }
 #undef SD2_TRY
     return SD2_OK;

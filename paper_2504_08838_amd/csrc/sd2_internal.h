@@ -199,4 +199,17 @@ inline bool dense_stream_ok(int k_in) { return k_in % 128 == 0 && k_in <= kLmMax
 // up to 4096 columns the kernel can take two token groups per pass
 inline bool dense_stream_pair_ok(int k_in) { return dense_stream_ok(k_in) && k_in <= 4096; }
 
+// A dense stack's glue inside the streaming kernel, up to 16 tokens (one pass; with more, launches of their own cost less than
+// what every workgroup and pass would repeat):
+// y = norm(h) W^T from the fp32 residual, up to 4096 columns (a wavefront's columns of the residual fit its registers)
+inline bool dense_stream_norm_ok(int k_in, int k_tok) { return dense_stream_pair_ok(k_in) && k_tok <= 16; }
+hipError_t launch_dense_stream_norm(const uint16_t* w, const float* h, int n_out, int k_in, int k_tok, float* y, hipStream_t s);
+// m_out = bf16(silu(gate) * up) with [gate; up] = W x (or of norm(h) where x is null); halves of whole groups of eight rows
+inline bool dense_stream_gated_ok(int n_out, int k_in) { return dense_stream_ok(k_in) && n_out % 16 == 0; }
+hipError_t launch_dense_stream_gated(const uint16_t* w, const uint16_t* x, const float* h, int n_out, int k_in, int k_tok, uint16_t* m_out,
+                                     hipStream_t s);
+// h += W x, up to 4096 rows (a strip per workgroup)
+inline bool dense_stream_add_ok(int n_out, int k_in, int k_tok) { return dense_stream_ok(k_in) && n_out <= 4096 && k_tok <= 16; }
+hipError_t launch_dense_stream_add(const uint16_t* w, const uint16_t* x, int n_out, int k_in, int k_tok, float* h, hipStream_t s);
+
 }  // namespace sd2

@@ -44,23 +44,36 @@ __device__ __forceinline__ void lm_better(float& a, int32_t& ia, float b, int32_
     }
 }
 
-// HEAD = true: the LM head (fp32 residual in `h`, final norm, greedy choice, logits optional).
-// HEAD = false: the same stream as a plain dense linear, y = x W^T with bf16 activations `x` and every result
-// written to `logits` ([k_tok][vocab] with vocab = n_out): the dense baseline of the sparse linears.  There TG = 2
-// takes up to 32 tokens in one pass (two sets of B operands in registers, two accumulators per strip; the partial
+// What a launch of the kernel is.  kHead: the LM head (fp32 residual in `h`, final norm, greedy choice, logits optional).  The others
+// are the same stream as a dense linear, y = x W^T with every sum final inside the workgroup:
+//   kPlain  every result written to `out` ([k_tok][vocab] with vocab = n_out)
+//   kGated  the matrix is [gate; up]: a strip is eight rows of each half, and bf16(silu(gate) * up) leaves as the next linear's
+//           activations ([k_tok][vocab / 2] bf16 in `out`): no launch for the product and no fp32 results in memory.  Eight rows
+//           and eight, not pairs of strips: as many strips as the plain linear has, so the workgroups share them as evenly.
+//   kAdd    results are added to the residual stream `out`; a workgroup has one strip (n_out <= 4096), whose residual is requested first
+// NORM: the activations are the RMS norm of the fp32 residual `h` (in place of bf16 `x`).  Every workgroup normalises for itself:
+// it reads twice the bytes of `x` from L2, and a launch with its gap (about 4 us) goes.
+// Dense stacks of 8 layers, us, every step a launch of its own and the activations behind the stream, then now: hidden 3072 on 5 tokens
+// 493 -> 421, on 16 tokens 573 -> 512; hidden 640 on one token 206 -> 176; MLP 2048 x 8192 on 5 tokens 23.9 -> 20.9.
+enum { kLmHead, kLmPlain, kLmGated, kLmAdd };
+
+// As a linear TG = 2 takes up to 32 tokens in one pass (two sets of B operands in registers, two accumulators per strip; the partial
 // strips then share one LDS buffer and need a second barrier per strip).
-template <int CPW, bool HEAD, int TG = 1>
+template <int CPW, int MODE, bool NORM, int TG>
 __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* __restrict__ w,
                                                                 const float* __restrict__ h,
                                                                 const uint16_t* __restrict__ x_all, int vocab, int hidden,
                                                                 int k_tok_all, int n_strips, LmCand* __restrict__ part,
-                                                                float* __restrict__ logits_all) {
+                                                                float* __restrict__ out_all) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lm_smem[];
-    // As a plain linear with more tokens than one pass takes, the grid's second dimension numbers the passes of 16 TG
+    constexpr bool HEAD = MODE == kLmHead;
+    // As a linear with more tokens than one pass takes, the grid's second dimension numbers the passes of 16 TG
     // tokens (the matrix is streamed once per pass); the head itself is launched with one pass.
     const int pass = HEAD ? 0 : (int)blockIdx.y;
-    const uint16_t* __restrict__ x = HEAD ? x_all : x_all + (size_t)pass * (16 * TG) * hidden;
-    float* __restrict__ logits = (HEAD || !logits_all) ? logits_all : logits_all + (size_t)pass * (16 * TG) * vocab;
+    const int n_cols_out = MODE == kLmGated ? vocab / 2 : vocab;
+    const uint16_t* __restrict__ x = (HEAD || NORM) ? x_all : x_all + (size_t)pass * (16 * TG) * hidden;
+    float* __restrict__ logits = (HEAD || MODE == kLmGated) ? out_all : out_all + (size_t)pass * (16 * TG) * vocab;
+    uint16_t* __restrict__ gated = reinterpret_cast<uint16_t*>(out_all) + (size_t)pass * (16 * TG) * n_cols_out;
     const int k_tok = HEAD ? k_tok_all : min(16 * TG, k_tok_all - pass * (16 * TG));
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -72,28 +85,51 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
 
     const int n_colchunks = hidden / kLmChunkCols;
     const int my_strips = (n_strips - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int n_chunks = my_strips * CPW;
+    constexpr int kSure = CPW == 6 || CPW == 8 ? CPW - 2 : CPW - 1;  // column chunks that every wavefront has (6 and 8 also serve 5 and 7)
+    int n_cc = 0;                                                    // this wavefront's: wave + 8 cc
+#pragma unroll
+    for (int cc = 0; cc < CPW; ++cc) n_cc += wave + kLmWaves * cc < n_colchunks ? 1 : 0;
+    const int n_chunks = my_strips * n_cc;
 
     static_assert(kLmRing == 4, "the waits below count four loads per chunk and three chunks behind the current one");
-    // Chunk ci of this wavefront: strip blockIdx.x + (ci / CPW) * gridDim.x, column chunk wave + 8 * (ci % CPW).
+    // The wavefront's chunks, in order: its n_cc column chunks of strip blockIdx.x, then of strip blockIdx.x + gridDim.x, ...
     // Instruction i of a chunk fills LDS rows 4i..4i+3 (16 lanes per row); lane l brings the 16-byte piece
     // (l & 15) ^ row of its row, so piece j of row r sits at LDS piece position j ^ r.
-    auto issue_chunk = [&](int ci) {
-        if (ci >= n_chunks) return;
-        uint32_t* dst = ring + (ci & (kLmRing - 1)) * kLmChunkDw;
-        const int strip = (int)blockIdx.x + (ci / CPW) * (int)gridDim.x;
-        const int colchunk = min(wave + kLmWaves * (ci % CPW), n_colchunks - 1);
+    // Requested as a buffer that starts at the chunk and ends with its last row: only its base is per request, in scalars, and
+    // rows past the matrix ask memory for nothing (the hardware's range check).  It also lets the compiler count these requests where
+    // it waits for the activations; global-memory requests into LDS make it wait for all.  What does not exist is not requested
+    // either: a request that the range check empties costs as much issue as a full one (three of them per wavefront
+    // at the end cost a linear 0.7 us).
+    uint32_t piece[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = 4 * i + g;
-            // rows past the end of a ragged last strip read the row 16 above instead (results unused): valid, and
-            // distinct from every other address this wavefront has in flight
-            int row = strip * 16 + r;
-            if (row >= vocab) row = max(row - 16, 0);
-            const uint16_t* src = w + (size_t)row * hidden + colchunk * kLmChunkCols + ((n ^ r) * 8);
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                             (__attribute__((address_space(3))) void*)(dst + i * 256), 16, 0, 0);
+    for (int i = 0; i < 4; ++i) {
+        const int r = 4 * i + g;
+        piece[i] = (uint32_t)((MODE == kLmGated ? 4 * (i & 1) + g : r) * hidden + ((n ^ r) * 8)) * 2u;
+    }
+    int issued = 0, r_strip = 0, r_cc = 0;  // chunks requested; the next one's strip and column chunk
+    auto request_chunk = [&](bool exists) {
+        uint32_t* dst = ring + (issued & (kLmRing - 1)) * kLmChunkDw;
+        const int row = ((int)blockIdx.x + r_strip * (int)gridDim.x) * (MODE == kLmGated ? 8 : 16);
+        const int rows = MODE == kLmGated ? 8 : min(16, vocab - row);
+        const int bytes = exists ? ((rows - 1) * hidden + kLmChunkCols) * 2 : 0;
+        const uint16_t* src = w + (size_t)row * hidden + (wave + kLmWaves * r_cc) * kLmChunkCols;
+        const auto rows_lo = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src), 0, bytes, 0x00020000);
+        const auto rows_hi = MODE == kLmGated
+                                 ? __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src + (size_t)n_cols_out * hidden), 0, bytes, 0x00020000)
+                                 : rows_lo;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(i < 2 ? rows_lo : rows_hi, (__attribute__((address_space(3))) void*)(dst + i * 256), 16,
+                                                     (int)piece[i], 0, 0, 0);
+        issued += exists ? 1 : 0;
+        r_cc += exists ? 1 : 0;
+        if (r_cc >= n_cc) {
+            r_cc = 0;
+            ++r_strip;
         }
+    };
+    auto issue_chunk = [&]() {
+        if (issued < n_chunks) request_chunk(true);
     };
     // Chunk ci has landed once at most the loads of the chunks issued after it are outstanding (loads return in
     // order): up to three chunks of four loads each, fewer at the end of the wavefront's work.
@@ -109,13 +145,18 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
             __builtin_amdgcn_s_waitcnt(0x0F70);
         asm volatile("" ::: "memory");
     };
-#pragma unroll
-    for (int c = 0; c < kLmRing; ++c) issue_chunk(c);
 
-    static_assert(TG == 1 || !HEAD, "the head takes one token group per pass");
+    static_assert(TG == 1 || (!HEAD && !NORM), "the norm takes one token group per pass");
+    static_assert(!NORM || CPW <= 4, "the residual's columns of a wavefront fit its registers");
     const int tok = min(n, k_tok - 1);  // lanes past the last token repeat it; their results are never used
+    // Reducing thread (wave rho < 4, lane l) owns result element l of source lane group rho: token l >> 2,
+    // row 4 rho + (l & 3) of each strip, so its running best needs no cross-lane work until the very end.
+    const int red_tok = lane >> 2, red_row = 4 * wave + (lane & 3);
+    float residual = 0.f;
     Frag b[TG][CPW][4];
-    if (HEAD) {
+    if (HEAD && !NORM) {
+#pragma unroll
+        for (int c = 0; c < kLmRing; ++c) issue_chunk();
         // ---- final norm of the residual stream, straight into operand B: a = bf16(h / sqrt(mean(h^2) + eps))
         for (int t = 0; t < k_tok; ++t) {
             float s = 0.f;
@@ -151,27 +192,86 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
             }
         }
     } else {
+        // The activations are requested in front of the wavefront's stream and without branches, so that their wait leaves the stream
+        // in flight.  Behind it they came with its last byte (loads return in the order of their issue): the ring was full and
+        // idle until then, and nothing was requested meanwhile.  A barrier that puts every wavefront's in front of anybody's stream
+        // costs more than it gives here: 55 us a layer against 52.5 (hidden 3072, 5 tokens), the stream starts later.
+        f32x4 hr[NORM ? CPW : 1][4][2];
+        if (MODE == kLmAdd) {
+            const int row = (int)blockIdx.x * 16 + red_row;
+            if (wave < 4 && row < vocab && red_tok < k_tok) residual = logits[(size_t)red_tok * vocab + row];
+        }
 #pragma unroll
-        for (int tg = 0; tg < TG; ++tg) {
-            const int tk = min(n + 16 * tg, k_tok - 1);
+        for (int cc = 0; cc < CPW; ++cc) {
+            const size_t col = (size_t)min(wave + kLmWaves * cc, n_colchunks - 1) * kLmChunkCols + g * 8;
 #pragma unroll
-            for (int cc = 0; cc < CPW; ++cc) {
-                const int colchunk = wave + kLmWaves * cc;
+            for (int q = 0; q < 4; ++q) {
+                if (NORM) {
+                    const float* src = h + (size_t)tok * hidden + col + q * 32;
+                    hr[cc][q][0] = *reinterpret_cast<const f32x4*>(src);
+                    hr[cc][q][1] = *reinterpret_cast<const f32x4*>(src + 4);
+                } else {
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    b[tg][cc][q].q = colchunk < n_colchunks
-                                         ? *reinterpret_cast<const u32x4*>(x + (size_t)tk * hidden + colchunk * kLmChunkCols + (q * 4 + g) * 8)
-                                         : u32x4{0u, 0u, 0u, 0u};
+                    for (int tg = 0; tg < TG; ++tg)
+                        b[tg][cc][q].q = *reinterpret_cast<const u32x4*>(x + (size_t)min(n + 16 * tg, k_tok - 1) * hidden + col + q * 32);
+                }
             }
         }
+        __builtin_amdgcn_sched_barrier(0);  // all of them on their way before the first is waited for
+#pragma unroll
+        for (int c = 0; c < CPW && c < kLmRing; ++c) request_chunk(c < n_cc);  // the first strip's: without a branch
+        __builtin_amdgcn_sched_barrier(0);
+        if (NORM) {
+            // lane (n, g) has token n's columns of its groups of eight: four lanes hold a wavefront's share of a token
+            float s = 0.f;
+#pragma unroll
+            for (int cc = 0; cc < CPW; ++cc) {
+                float sc = 0.f;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const f32x4 v = hr[cc][q][e];
+                        sc += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+                    }
+                s += wave + kLmWaves * cc < n_colchunks ? sc : 0.f;
+            }
+            s += __shfl_xor(s, 16);
+            s += __shfl_xor(s, 32);
+            if (lane < 16) misc[wave * 16 + lane] = s;
+            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            float tot = 0.f;
+#pragma unroll
+            for (int ww = 0; ww < kLmWaves; ++ww) tot += misc[ww * 16 + n];
+            const float inv = 1.0f / sqrtf(tot / (float)hidden + 1e-5f);
+#pragma unroll
+            for (int cc = 0; cc < CPW; ++cc)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const f32x4 v = hr[cc][q][e];
+                        b[0][cc][q].u[2 * e] = pack_bf16(v[0] * inv, v[1] * inv);
+                        b[0][cc][q].u[2 * e + 1] = pack_bf16(v[2] * inv, v[3] * inv);
+                    }
+        }
+        // waited for here, where what is behind them is known: in the loop the compiler would wait for the stream, too
+#pragma unroll
+        for (int tg = 0; tg < TG; ++tg)
+#pragma unroll
+            for (int cc = 0; cc < CPW; ++cc)
+                asm volatile("" : "+v"(b[tg][cc][0].q), "+v"(b[tg][cc][1].q), "+v"(b[tg][cc][2].q), "+v"(b[tg][cc][3].q));
+        if (MODE == kLmAdd) asm volatile("" : "+v"(residual));
+#pragma unroll
+        for (int c = 0; c < kLmRing; ++c)
+            if (issued < kLmRing) issue_chunk();
     }
 
     // ---- strips
-    // Reducing thread (wave rho < 4, lane l) owns result element l of source lane group rho: token l >> 2,
-    // row 4 rho + (l & 3) of each strip, so its running best needs no cross-lane work until the very end.
     float best = -INFINITY;
     int32_t best_i = 0x7fffffff;
-    const int red_tok = lane >> 2, red_row = 4 * wave + (lane & 3);
     int ci = 0;
 #pragma unroll 1
     for (int si = 0; si < my_strips; ++si) {
@@ -180,6 +280,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
         for (int tg = 0; tg < TG; ++tg) acc[tg] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int cc = 0; cc < CPW; ++cc) {
+            if (cc >= kSure && cc >= n_cc) break;
             wait_chunk(ci);
             const uint32_t* buf = ring + (ci & (kLmRing - 1)) * kLmChunkDw;
             Frag a[4];
@@ -188,14 +289,11 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
             // the buffer is refilled only after its reads have returned
             __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
             asm volatile("" ::: "memory");
-            issue_chunk(ci + kLmRing);
-            // (a column chunk past the matrix is a copy of the last one: its zero activations times an infinite weight would be NaN)
-            if (cc < CPW - 1 || wave + kLmWaves * cc < n_colchunks) {
+            issue_chunk();
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+            for (int q = 0; q < 4; ++q)
 #pragma unroll
-                    for (int tg = 0; tg < TG; ++tg) acc[tg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q].v, b[tg][cc][q].v, acc[tg], 0, 0, 0);
-            }
+                for (int tg = 0; tg < TG; ++tg) acc[tg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[q].v, b[tg][cc][q].v, acc[tg], 0, 0, 0);
             ++ci;
         }
         // one token group: the partial strips alternate between two buffers (one barrier per strip); two groups fill
@@ -206,20 +304,28 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the partial strip is in LDS; loads stay in flight
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (wave < 4) {
+        if (wave < (MODE == kLmGated ? 2 : 4)) {
 #pragma unroll
             for (int tg = 0; tg < TG; ++tg) {
+                const int rt = red_tok + 16 * tg;
                 float v = 0.f;
 #pragma unroll
                 for (int ww = 0; ww < kLmWaves; ++ww) v += mine[tg * kLmRedDw + ww * 256 + wave * 64 + lane];
+                if (MODE == kLmGated) {  // waves 0 and 1: rows 0..7 are the gate's, rows 8..15 the same rows of up
+                    float up = 0.f;
+#pragma unroll
+                    for (int ww = 0; ww < kLmWaves; ++ww) up += mine[tg * kLmRedDw + ww * 256 + (wave + 2) * 64 + lane];
+                    if (rt < k_tok)
+                        gated[(size_t)rt * n_cols_out + ((int)blockIdx.x + si * (int)gridDim.x) * 8 + red_row] = f32_to_bf16(v / (1.0f + expf(-v)) * up);
+                    continue;
+                }
                 const int row = ((int)blockIdx.x + si * (int)gridDim.x) * 16 + red_row;
-                const int rt = red_tok + 16 * tg;
                 if (row < vocab && rt < k_tok) {
                     if (HEAD && v > best) {  // rows come in increasing order: '>' keeps the lowest index among equals
                         best = v;
                         best_i = row;
                     }
-                    if (!HEAD || logits) logits[(size_t)rt * vocab + row] = v;
+                    if (!HEAD || logits) logits[(size_t)rt * vocab + row] = MODE == kLmAdd ? residual + v : v;
                 }
             }
         }
@@ -229,6 +335,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
             asm volatile("" ::: "memory");
         }
     }
+    wait_vector_memory();  // nothing is on its way into LDS when the wavefront ends
     if (!HEAD) return;
     // ---- 16 threads per token hold candidates: pick one per token and workgroup
     LmCand* cand = reinterpret_cast<LmCand*>(misc + kLmWaves * 16);
@@ -278,45 +385,55 @@ static int lm_cu_count() {
     return 256;
 }
 
-template <int CPW, bool HEAD, int TG = 1>
-static hipError_t launch_lm_t(const uint16_t* w, const float* h, const uint16_t* x, int vocab, int hidden, int k_tok,
-                              int n_strips, int n_wg, LmCand* part, float* logits, hipStream_t s, int passes = 1) {
+// one per compute unit; the head's candidates have room for kLmMaxWorkgroups
+static int lm_workgroups(int n_strips, bool head) {
+    const int n = std::min(n_strips, lm_cu_count());
+    return head ? std::min(n, kLmMaxWorkgroups) : n;
+}
+
+template <int CPW, int MODE, bool NORM, int TG = 1>
+static hipError_t launch_lm_t(const uint16_t* w, const float* h, const uint16_t* x, int vocab, int hidden, int k_tok, LmCand* part, float* out,
+                              hipStream_t s) {
     static std::atomic<bool> attr_set{false};  // more than the default 64 KiB of dynamic LDS needs opting in, once per kernel
     const size_t lds = (size_t)kLmLdsDw * 4;
     if (!attr_set.load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lm_head_kernel<CPW, HEAD, TG>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lm_head_kernel<CPW, MODE, NORM, TG>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((lm_head_kernel<CPW, HEAD, TG>), dim3((unsigned)n_wg, (unsigned)passes), dim3(64 * kLmWaves), lds, s, w, h, x, vocab, hidden,
-                       k_tok, n_strips, part, logits);
+    const int n_strips = (vocab + 15) / 16;
+    const int n_wg = MODE == kLmAdd ? n_strips : lm_workgroups(n_strips, MODE == kLmHead);
+    const int passes = MODE == kLmHead ? 1 : (k_tok + 16 * TG - 1) / (16 * TG);
+    hipLaunchKernelGGL((lm_head_kernel<CPW, MODE, NORM, TG>), dim3((unsigned)n_wg, (unsigned)passes), dim3(64 * kLmWaves), lds, s, w, h, x, vocab,
+                       hidden, k_tok, n_strips, part, out);
     return hipGetLastError();
 }
 
-template <bool HEAD>
-static hipError_t launch_lm_cpw(const uint16_t* w, const float* h, const uint16_t* x, int vocab, int hidden, int k_tok,
-                                int n_strips, int n_wg, LmCand* part, float* logits, hipStream_t s, int passes = 1) {
-    const int cpw = (hidden / kLmChunkCols + kLmWaves - 1) / kLmWaves;
-    switch (cpw) {
-        case 1: return launch_lm_t<1, HEAD>(w, h, x, vocab, hidden, k_tok, n_strips, n_wg, part, logits, s, passes);
-        case 2: return launch_lm_t<2, HEAD>(w, h, x, vocab, hidden, k_tok, n_strips, n_wg, part, logits, s, passes);
-        case 3: return launch_lm_t<3, HEAD>(w, h, x, vocab, hidden, k_tok, n_strips, n_wg, part, logits, s, passes);
-        case 4: return launch_lm_t<4, HEAD>(w, h, x, vocab, hidden, k_tok, n_strips, n_wg, part, logits, s, passes);
-        case 5: case 6: return launch_lm_t<6, HEAD>(w, h, x, vocab, hidden, k_tok, n_strips, n_wg, part, logits, s, passes);
-        case 7: case 8: return launch_lm_t<8, HEAD>(w, h, x, vocab, hidden, k_tok, n_strips, n_wg, part, logits, s, passes);
-        case 9: return launch_lm_t<9, HEAD>(w, h, x, vocab, hidden, k_tok, n_strips, n_wg, part, logits, s, passes);
-        default: return hipErrorInvalidValue;
+// NORM is a request: up to 4096 columns (four column chunks a wavefront) the residual's columns fit the registers
+template <int MODE, bool NORM>
+static hipError_t launch_lm_cpw(const uint16_t* w, const float* h, const uint16_t* x, int vocab, int hidden, int k_tok, LmCand* part, float* out,
+                                hipStream_t s) {
+    constexpr bool kLong = !NORM || MODE == kLmHead;  // the head has another prologue for longer rows
+    switch ((hidden / kLmChunkCols + kLmWaves - 1) / kLmWaves) {
+        case 1: return launch_lm_t<1, MODE, NORM>(w, h, x, vocab, hidden, k_tok, part, out, s);
+        case 2: return launch_lm_t<2, MODE, NORM>(w, h, x, vocab, hidden, k_tok, part, out, s);
+        case 3: return launch_lm_t<3, MODE, NORM>(w, h, x, vocab, hidden, k_tok, part, out, s);
+        case 4: return launch_lm_t<4, MODE, NORM>(w, h, x, vocab, hidden, k_tok, part, out, s);
+        case 5: case 6: if constexpr (kLong) return launch_lm_t<6, MODE, false>(w, h, x, vocab, hidden, k_tok, part, out, s); break;
+        case 7: case 8: if constexpr (kLong) return launch_lm_t<8, MODE, false>(w, h, x, vocab, hidden, k_tok, part, out, s); break;
+        case 9: if constexpr (kLong) return launch_lm_t<9, MODE, false>(w, h, x, vocab, hidden, k_tok, part, out, s); break;
+        default: break;
     }
+    return hipErrorInvalidValue;
 }
 
 // tokens [0, k_tok) with k_tok <= 16; `part` holds kLmMaxWorkgroups * 16 candidates
 hipError_t launch_lm_head(const uint16_t* w, const float* h, int vocab, int hidden, int k_tok, void* part_ws,
                           int32_t* token_ids, float* max_logit, float* logits, hipStream_t s) {
-    const int n_strips = (vocab + 15) / 16;
-    const int n_wg = std::min(std::min(n_strips, lm_cu_count()), kLmMaxWorkgroups);
+    const int n_wg = lm_workgroups((vocab + 15) / 16, true);
     LmCand* part = static_cast<LmCand*>(part_ws);
-    const hipError_t e = launch_lm_cpw<true>(w, h, nullptr, vocab, hidden, k_tok, n_strips, n_wg, part, logits, s);
+    const hipError_t e = launch_lm_cpw<kLmHead, true>(w, h, nullptr, vocab, hidden, k_tok, part, logits, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(lm_head_pick_kernel, dim3(1), dim3(1024), 0, s, part, n_wg, k_tok, token_ids, max_logit);
     return hipGetLastError();
@@ -328,21 +445,37 @@ hipError_t launch_lm_head(const uint16_t* w, const float* h, int vocab, int hidd
 // tokens are further passes of the same launch (the grid's second dimension).
 hipError_t launch_dense_stream_linear(const uint16_t* w, const uint16_t* x, int n_out, int k_in, int k_tok, float* y, int tg,
                                       hipStream_t s) {
-    const int n_strips = (n_out + 15) / 16;
-    const int n_wg = std::min(n_strips, lm_cu_count());
     if (k_tok < 1 || k_tok > 64) return hipErrorInvalidValue;
     if (tg == 2) {
         if (!dense_stream_pair_ok(k_in)) return hipErrorInvalidValue;
-        const int passes = (k_tok + 31) / 32;
         switch ((k_in / kLmChunkCols + kLmWaves - 1) / kLmWaves) {
-            case 1: return launch_lm_t<1, false, 2>(w, nullptr, x, n_out, k_in, k_tok, n_strips, n_wg, nullptr, y, s, passes);
-            case 2: return launch_lm_t<2, false, 2>(w, nullptr, x, n_out, k_in, k_tok, n_strips, n_wg, nullptr, y, s, passes);
-            case 3: return launch_lm_t<3, false, 2>(w, nullptr, x, n_out, k_in, k_tok, n_strips, n_wg, nullptr, y, s, passes);
-            case 4: return launch_lm_t<4, false, 2>(w, nullptr, x, n_out, k_in, k_tok, n_strips, n_wg, nullptr, y, s, passes);
+            case 1: return launch_lm_t<1, kLmPlain, false, 2>(w, nullptr, x, n_out, k_in, k_tok, nullptr, y, s);
+            case 2: return launch_lm_t<2, kLmPlain, false, 2>(w, nullptr, x, n_out, k_in, k_tok, nullptr, y, s);
+            case 3: return launch_lm_t<3, kLmPlain, false, 2>(w, nullptr, x, n_out, k_in, k_tok, nullptr, y, s);
+            case 4: return launch_lm_t<4, kLmPlain, false, 2>(w, nullptr, x, n_out, k_in, k_tok, nullptr, y, s);
             default: return hipErrorInvalidValue;
         }
     }
-    return launch_lm_cpw<false>(w, nullptr, x, n_out, k_in, k_tok, n_strips, n_wg, nullptr, y, s, (k_tok + 15) / 16);
+    return launch_lm_cpw<kLmPlain, false>(w, nullptr, x, n_out, k_in, k_tok, nullptr, y, s);
+}
+
+hipError_t launch_dense_stream_norm(const uint16_t* w, const float* h, int n_out, int k_in, int k_tok, float* y, hipStream_t s) {
+    if (k_tok < 1 || k_tok > 16 || !dense_stream_norm_ok(k_in, k_tok)) return hipErrorInvalidValue;
+    return launch_lm_cpw<kLmPlain, true>(w, h, nullptr, n_out, k_in, k_tok, nullptr, y, s);
+}
+
+hipError_t launch_dense_stream_gated(const uint16_t* w, const uint16_t* x, const float* h, int n_out, int k_in, int k_tok, uint16_t* m_out,
+                                     hipStream_t s) {
+    if (k_tok < 1 || k_tok > 64 || !dense_stream_gated_ok(n_out, k_in)) return hipErrorInvalidValue;
+    float* out = reinterpret_cast<float*>(m_out);
+    if (x) return launch_lm_cpw<kLmGated, false>(w, nullptr, x, n_out, k_in, k_tok, nullptr, out, s);
+    if (!dense_stream_norm_ok(k_in, k_tok)) return hipErrorInvalidValue;
+    return launch_lm_cpw<kLmGated, true>(w, h, nullptr, n_out, k_in, k_tok, nullptr, out, s);
+}
+
+hipError_t launch_dense_stream_add(const uint16_t* w, const uint16_t* x, int n_out, int k_in, int k_tok, float* h, hipStream_t s) {
+    if (k_tok < 1 || !dense_stream_add_ok(n_out, k_in, k_tok)) return hipErrorInvalidValue;
+    return launch_lm_cpw<kLmAdd, false>(w, nullptr, x, n_out, k_in, k_tok, nullptr, h, s);
 }
 
 }  // namespace sd2

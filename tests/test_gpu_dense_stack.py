@@ -1,0 +1,114 @@
+"""Dense stacks up to 16 tokens: the norm, the gated product and the residual inside the linears, where each can go wrong -- one to four
+column chunks a wavefront and wavefronts without one, longer rows than the norm takes, ragged strips, the last token of a pass,
+and layers that mix dense and packed matrices, so that some of the glue stays a launch of its own."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+
+import sd2_workload as wl
+from oracle import decode as od
+from oracle import linear as ol
+from oracle import stack as os_
+
+pytestmark = pytest.mark.gpu
+# Whole-stack bar of tests/test_gpu_stack.py.  Two layers round their activations to bf16 eight times; a value next to a boundary moves by
+# one spacing, 2^-8 at most: with one in twenty of them 2^-8 sqrt(8 / 20) = 2.5e-3, and the next linear may amplify that.
+TOL = 5e-3
+
+
+def _shape(hidden, heads, kv, inter, layers=2):
+    return SimpleNamespace(layers=layers, hidden=hidden, q_out=128 * heads, kv_out=128 * kv, inter=inter, n_heads=heads, n_kv=kv, head_dim=128)
+
+
+def _model(shape, seed, dense=(True, True, True, True)):
+    import gpu_util as gu
+    import paper_2504_08838_amd as sd2
+    table = {p: (n, k) for p, n, k in wl.layer_matrix_shapes(shape)}
+    cache = {}
+
+    def get(layer, proj):
+        if (layer, proj) not in cache:
+            cache[(layer, proj)] = wl.gen_weight(seed, layer, proj, *table[proj], 50)
+        return cache[(layer, proj)]
+
+    mats = []
+    for l in range(shape.layers):
+        for parts, is_dense in zip(("qkv", ("o",), ("gate", "up"), ("down",)), dense):
+            w = np.concatenate([get(l, p) for p in parts], axis=0)
+            mats.append(gu.DenseMat(w) if is_dense else gu.SparseMat(w, 1))
+    ms = sd2.ModelShape(shape.layers, shape.hidden, shape.q_out, shape.kv_out, shape.inter, shape.n_heads, shape.n_kv, shape.head_dim)
+    return get, sd2.model_create(ms, [m.m for m in mats], keep=mats)
+
+
+@pytest.mark.parametrize("shape", [
+    _shape(128, 2, 1, 128),     # one chunk: seven wavefronts have none
+    _shape(1536, 3, 1, 1088),   # two chunks, half of the wavefronts one; down has 64 columns too many for the stream
+    _shape(2304, 2, 2, 8960),   # three chunks, a ragged third; nine in down
+    _shape(4096, 2, 1, 640),    # four chunks; 256 strips
+    _shape(4224, 2, 1, 4224),   # longer than the norm takes; 33 chunks
+], ids=lambda s: str(s.hidden))
+@pytest.mark.parametrize("k_tok", [1, 5, 16, 17])
+def test_dense_forward(shape, k_tok):
+    import gpu_util as gu
+    get, model = _model(shape, 71)
+    h = wl.gen_x(71, 0, "q", k_tok, shape.hidden)
+    out = gu.run_forward(model, h, shape.hidden)
+    assert ol.rel_l2(out, os_.drafter_forward(shape, get, h)) <= TOL
+    assert np.array_equal(gu.run_forward(model, h, shape.hidden), out)
+
+
+@pytest.mark.parametrize("dense", [(True, False, False, False), (False, True, False, False), (False, False, True, False),
+                                   (False, False, False, True), (True, False, True, True)])
+@pytest.mark.parametrize("k_tok", [5, 17])
+def test_mixed_layers(dense, k_tok):
+    import gpu_util as gu
+    shape = _shape(768, 2, 1, 640)
+    get, model = _model(shape, 73, dense)
+    h = wl.gen_x(73, 0, "q", k_tok, shape.hidden)
+    assert ol.rel_l2(gu.run_forward(model, h, shape.hidden), os_.drafter_forward(shape, get, h)) <= TOL
+
+
+@pytest.mark.parametrize("k_tok", [1, 13])
+def test_dense_decode(k_tok):
+    import gpu_util as gu
+    from test_gpu_decode import _decode, THETA
+    shape, pos0 = _shape(1152, 4, 2, 1216), 37
+    get, model = _model(shape, 79)
+    rng = np.random.default_rng([79, k_tok])
+    kc, vc = (wl.f32_to_bf16_bits(rng.standard_normal((2, 2, 64, 128)).astype(np.float32)) for _ in range(2))
+    h = wl.gen_x(79, 0, "q", k_tok, shape.hidden)
+    out = _decode(model, shape, h, gu.dev(kc), gu.dev(vc), 64, pos0)
+    assert ol.rel_l2(out, od.drafter_decode(shape, get, h, kc.copy(), vc.copy(), pos0, THETA)) <= TOL
+
+
+@pytest.mark.parametrize("hidden,inter", [(128, 64), (1536, 8960), (4224, 1088)])
+@pytest.mark.parametrize("k_tok", [1, 7, 16])
+def test_dense_mlp(hidden, inter, k_tok):
+    import torch
+    import gpu_util as gu
+    import paper_2504_08838_amd as sd2
+    wg, wu, wd = (wl.gen_weight(2, 1, p, n, k, 50) for p, n, k in (("gate", inter, hidden), ("up", inter, hidden), ("down", hidden, inter)))
+    x_bits = wl.gen_x(2, 1, "gate", k_tok, hidden)
+    ref, _ = os_.mlp_block(wg, wu, wd, x_bits)
+    g_u, dn, x = gu.DenseMat(np.concatenate([wg, wu], axis=0)), gu.DenseMat(wd), gu.dev(x_bits)
+    y = torch.full((k_tok, hidden), float("nan"), dtype=torch.float32, device="cuda")
+    nb = sd2.mlp_workspace_size(g_u.m, dn.m, k_tok)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    sd2.sparse_mlp_forward(g_u.m, dn.m, x.data_ptr(), k_tok, y.data_ptr(), ws.data_ptr(), nb, gu.stream_ptr())
+    torch.cuda.synchronize()
+    assert ol.rel_l2(y.cpu().numpy(), ref) <= 2e-3  # as the bitmask blocks: one rounding to bf16 between the linears
+
+
+@pytest.mark.parametrize("k", [4224, 5248, 6272])
+def test_infinite_weight_with_five_and_seven_chunks(k):
+    """33, 41 and 49 column chunks on eight wavefronts: some have one or two chunks fewer than the kernel is built for."""
+    import gpu_util as gu
+    w = np.random.default_rng([83, k]).integers(1, 9, size=(40, k)).astype(np.float32)
+    w[7, k - 128] = np.inf
+    x = np.random.default_rng([84, k]).integers(1, 5, size=(5, k)).astype(np.float32)
+    assert np.array_equal(gu.run_linear(gu.DenseMat(_bits(w)), _bits(x), sparse=False), x @ w.T)
+
+
+def _bits(a):
+    return wl.f32_to_bf16_bits(a)
