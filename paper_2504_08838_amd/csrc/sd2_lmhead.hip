@@ -8,7 +8,7 @@
 // workgroup the contraction is split eight ways: wavefront w owns the 128-column chunks w, w+8, ...
 // of every strip, and keeps the matching slice of the normalised activations (operand B of the
 // MFMAs) in registers for the whole kernel.  Weights travel HBM -> LDS directly
-// (global_load_lds_dwordx4, 256 contiguous bytes per row piece) into a per-wave ring of four 4 KiB
+// (16-byte buffer requests, 256 contiguous bytes per row piece) into a per-wave ring of four 4 KiB
 // chunk buffers, refilled as soon as its reads have returned, so up to four chunks are in flight; the 16-byte
 // pieces of a row are stored xor-swizzled by the row number so that the MFMA-layout reads
 // (one row per lane) hit sixteen different bank groups.  Per strip the eight partial 16 x 16
