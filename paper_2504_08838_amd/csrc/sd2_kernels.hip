@@ -979,7 +979,8 @@ __global__ __launch_bounds__(256) void rmsnorm_apply_kernel(const float* __restr
 // partial result.)  Whole stacks with 57 of these, 28 layers: hidden 3072 on 64 tokens 2284 -> 2242 us, hidden 1536 on 64
 // tokens against a cache 2073 -> 2015, hidden 1536 dense on 5 tokens 1321 -> 1291.  Eight partial results are requested at
 // a time where a thread holds one piece, four where it holds two, two where it holds four: more would spill (four of four pieces:
-// hidden 12288 on 64 tokens 105.1 us a layer against 102.5, hidden 16384 on 5 tokens 246.9 against 244.0).
+// hidden 12288 on 64 tokens 105.1 us a layer against 102.5, hidden 16384 on 5 tokens 246.9 against 244.0).  Dense linears that normalise
+// for themselves (lm_head_kernel with NORM, up to 4096 columns) add the squares in the order of one piece here.
 constexpr int kRnThreads = 1024;
 
 template <int P, int GRP>

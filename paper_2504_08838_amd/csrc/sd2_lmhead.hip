@@ -28,7 +28,7 @@ constexpr int kLmChunkCols = 128;               // columns of one staged chunk (
 constexpr int kLmRing = 4;                      // chunk buffers per wavefront
 constexpr int kLmChunkDw = 16 * kLmChunkCols / 2;
 constexpr int kLmRedDw = kLmWaves * 256;        // one set of partial strips
-constexpr int kLmMiscDw = kLmWaves * 16 + 512;  // sums of squares per wave and token; final candidates
+constexpr int kLmMiscDw = kLmWaves * 16 + 512;  // sums of squares per block of columns and token; final candidates (behind the first 128)
 constexpr int kLmLdsDw = kLmWaves * kLmRing * kLmChunkDw + 2 * kLmRedDw + kLmMiscDw;
 
 struct LmCand {
@@ -221,30 +221,96 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
 #pragma unroll
         for (int c = 0; c < CPW && c < kLmRing; ++c) request_chunk(c < n_cc);  // the first strip's: without a branch
         __builtin_amdgcn_sched_barrier(0);
+        // The rest of the ring: as soon as the activations are there.  (Behind the norm, dense stack of 28 layers, hidden 1536, 5 tokens: 1131 us
+        // against 1100.)
+        auto fill_ring = [&]() {
+#pragma unroll
+            for (int c = 0; c < kLmRing; ++c)
+                if (issued < kLmRing) issue_chunk();
+        };
         if (NORM) {
-            // lane (n, g) has token n's columns of its groups of eight: four lanes hold a wavefront's share of a token
-            float s = 0.f;
 #pragma unroll
-            for (int cc = 0; cc < CPW; ++cc) {
-                float sc = 0.f;
+            for (int cc = 0; cc < CPW; ++cc)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+                for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(hr[cc][q][0]), "+v"(hr[cc][q][1]));
+            fill_ring();
+            // The sum of squares, in the order in which a launch of its own adds it (residual_norm_kernel; for the head, the prologue
+            // above), so that the same residual gives the same activations on either way.  That order: four columns, then a tree over the
+            // 64 such groups of 256 columns whose first step adds columns 128 apart, then the blocks of 256 columns in turn.  Here
+            // lane (n, g) of wavefront w has token n's groups (q, e) = columns 32 q + 8 g + 4 e of its column chunks, and the columns
+            // 128 away are the neighbouring wavefront's.  Neighbours meet in the room of the partial strips, two chunks at a time: of the
+            // first chunk's block the even wavefront adds up all, of the second's the odd one.  (Adding in whatever order was nearest cost
+            // 0.4 us less a launch and moved a dense stack's outputs by 2e-3: other bf16 neighbours.)
+            constexpr int kBlocks = HEAD && CPW > 2 ? 2 : CPW;  // the head's threads first add their columns 2048 apart
+            constexpr int kTokDw = 4 * kBlocks + 4;             // a token's blocks, and a piece to spread the tokens over the banks
+            static_assert(!NORM || (16 * kTokDw <= kLmMiscDw && kLmRedDw % 4 == 0), "the blocks' sums fit, 16-byte aligned");
+            const bool odd = wave & 1;
+            auto squares = [&](int cc, f32x4 (&sq)[2]) {
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
-                        const f32x4 v = hr[cc][q][e];
-                        sc += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+                for (int e = 0; e < 2; ++e)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        sq[e][q] = 0.f;
+#pragma unroll
+                        for (int c = cc; c < CPW; c += kBlocks) {
+                            const f32x4 v = hr[c][q][e];
+                            const float s = HEAD ? v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3]
+                                                 : (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+                            sq[e][q] += wave + kLmWaves * c < n_colchunks ? s : 0.f;
+                        }
                     }
-                s += wave + kLmWaves * cc < n_colchunks ? sc : 0.f;
+            };
+            auto meet = [&]() {
+                __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            };
+#pragma unroll
+            for (int c0 = 0; c0 < kBlocks; c0 += 2) {
+                // the second pair of chunks goes where this wavefront has just read of the first (nobody else reads there)
+                f32x4* put = reinterpret_cast<f32x4*>(red) + (c0 ? wave : wave ^ 1) * 128 + lane;
+                const f32x4* get = reinterpret_cast<const f32x4*>(red) + (c0 ? wave ^ 1 : wave) * 128 + lane;
+                const bool pair = c0 + 1 < kBlocks;
+                f32x4 first[2], second[2], v[2];
+                squares(c0, first);
+                squares(pair ? c0 + 1 : c0, second);
+                if (odd) {
+                    put[0] = first[0];
+                    put[64] = first[1];
+                    v[0] = second[0];
+                    v[1] = second[1];
+                } else {
+                    if (pair) {
+                        put[0] = second[0];
+                        put[64] = second[1];
+                    }
+                    v[0] = first[0];
+                    v[1] = first[1];
+                }
+                meet();
+                if (!odd || pair) {
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) v[e] += get[64 * e];
+                    float s[2];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) s[e] = (v[e][0] + v[e][2]) + (v[e][1] + v[e][3]);
+#pragma unroll
+                    for (int o = 32; o >= 16; o >>= 1)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) s[e] += __shfl_xor(s[e], o);
+                    if (lane < 16) misc[lane * kTokDw + (wave >> 1) + 4 * (odd ? c0 + 1 : c0)] = s[0] + s[1];
+                }
+                asm volatile("" ::: "memory");  // (the reads have returned: their sums are on their way)
             }
-            s += __shfl_xor(s, 16);
-            s += __shfl_xor(s, 32);
-            if (lane < 16) misc[wave * 16 + lane] = s;
-            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
+            meet();
+            f32x4 blocks[kBlocks];
+#pragma unroll
+            for (int j = 0; j < kBlocks; ++j) blocks[j] = *reinterpret_cast<const f32x4*>(misc + n * kTokDw + 4 * j);
             float tot = 0.f;
 #pragma unroll
-            for (int ww = 0; ww < kLmWaves; ++ww) tot += misc[ww * 16 + n];
+            for (int j = 0; j < kBlocks; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) tot += blocks[j][i];
             const float inv = 1.0f / sqrtf(tot / (float)hidden + 1e-5f);
 #pragma unroll
             for (int cc = 0; cc < CPW; ++cc)
@@ -264,9 +330,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
             for (int cc = 0; cc < CPW; ++cc)
                 asm volatile("" : "+v"(b[tg][cc][0].q), "+v"(b[tg][cc][1].q), "+v"(b[tg][cc][2].q), "+v"(b[tg][cc][3].q));
         if (MODE == kLmAdd) asm volatile("" : "+v"(residual));
-#pragma unroll
-        for (int c = 0; c < kLmRing; ++c)
-            if (issued < kLmRing) issue_chunk();
+        if (!NORM) fill_ring();
     }
 
     // ---- strips

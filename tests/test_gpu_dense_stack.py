@@ -58,6 +58,26 @@ def test_dense_forward(shape, k_tok):
     assert np.array_equal(gu.run_forward(model, h, shape.hidden), out)
 
 
+@pytest.mark.parametrize("shape", [
+    _shape(128, 2, 1, 128),
+    _shape(1536, 3, 1, 1088),
+    _shape(2304, 2, 2, 1152),   # an odd number of column chunks in the norm
+    _shape(3072, 2, 1, 640),
+    _shape(4096, 2, 1, 640),
+    _shape(4224, 2, 1, 1280),
+], ids=lambda s: str(s.hidden))
+@pytest.mark.parametrize("k_tok", [1, 5, 16])
+def test_glue_inside_the_linears_changes_no_bit(shape, k_tok):
+    """A traced forward keeps every step a launch of its own: the norm, the gated product and the residual inside the linears add the
+    same numbers in the same order."""
+    import gpu_util as gu
+    get, model = _model(shape, 77)
+    for i in range(6):  # a sum of squares that is off by its last bit changes few activations
+        h = wl.gen_x(77 + i, 0, "q", k_tok, shape.hidden)
+        apart, _, _ = gu.run_forward_trace(model, h, shape)
+        assert np.array_equal(gu.run_forward(model, h, shape.hidden), apart)
+
+
 @pytest.mark.parametrize("dense", [(True, False, False, False), (False, True, False, False), (False, False, True, False),
                                    (False, False, False, True), (True, False, True, True)])
 @pytest.mark.parametrize("k_tok", [5, 17])
