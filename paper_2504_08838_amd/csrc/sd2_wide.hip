@@ -295,19 +295,22 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
         }
     };
     // The same by way of LDS alone: requested straight into the wavefront's own place for them, in the order that the operand
-    // reads want (the memory side of a request may be any 16 bytes), a whole pass ahead.  Rows past the last token read as zero.
-    const auto x_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.x), 0, a.k_tok * a.k_in * 2, 0x00020000);
+    // reads want (the memory side of a request may be any 16 bytes), a whole pass ahead.  Requested of a buffer from the unit's first
+    // column to the end of x, empty for a unit past the matrix; a token's row is in the vector offset, so that rows past the last
+    // token ask memory for nothing (the hardware's range check, which does not look at scalar offsets).
     auto send_b = [&](int u) SD2_INLINE {
         int l = lane;
         asm volatile("" : "+v"(l));
+        const int left = u < a.n_units ? (a.k_tok * a.k_in - 128 * u) * 2 : 0;  // bytes
+        const auto part = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.x) + 128 * u, 0, left, 0x00020000);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int r = 4 * j + (l >> 4);
             const int off = (r * a.k_in + 8 * ((l & 15) ^ r)) * 2;
 #pragma unroll
             for (int tg = 0; tg < TG; ++tg)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (__attribute__((address_space(3))) void*)(xbuf + tg * 1024 + j * 256), 16, off,
-                                                         256 * u + 32 * tg * a.k_in, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(part, (__attribute__((address_space(3))) void*)(xbuf + tg * 1024 + j * 256), 16,
+                                                         off + 32 * tg * a.k_in, 0, 0, 0);
         }
     };
     auto read_b = [&](int u) SD2_INLINE {
