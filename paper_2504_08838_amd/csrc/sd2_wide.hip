@@ -69,9 +69,10 @@ constexpr uint32_t kWideStaged = 2560;
 
 // A wavefront's LDS: room for the staged stream of half a tile (bitmask) or a block that goes from row order to operand order
 // (dense), then, where it fits, the next unit's activations.  A stream is staged whole up to 2560 bytes; when a tile's values
-// crowd into one half, a step of 64 columns at a time (2048 bytes of values, 14 of misalignment, 8 of slack).
+// crowd into one half, a step of 64 columns at a time.
 constexpr int wide_buf_dw(int fmt) { return fmt == 0 /* bitmask */ ? (2560 + 32) / 4 : fmt == 2 /* dense */ ? 4096 / 4 : 0; }
-constexpr uint32_t kWideStepPieces = (2048 + 14 + 8 + 15) / 16;
+constexpr uint32_t kWideStepPieces = (2048 + 14 + 8 + 15) / 16;  // values, misalignment, slack
+static_assert(kWideStepPieces * 16 <= kWideStaged, "a step fits the stage");
 constexpr int kWideLdsBytes = 160 * 1024;
 constexpr bool wide_x_ahead(int fmt, int tg, int w) { return w * (wide_buf_dw(fmt) * 4 + tg * 4096) + (fmt == 0 ? 128 : 0) <= kWideLdsBytes; }
 constexpr int wide_wave_dw(int fmt, int tg, int w) {
@@ -450,6 +451,13 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
             send_b(unit_at(ahead));
             asm volatile("" ::: "memory");
         }
+        auto stage_out = [&](const Stage& s) SD2_INLINE {
+            if constexpr (FMT == kWideBitmask) {
+                reinterpret_cast<u32x4*>(buf)[lane] = s.v[0];
+                reinterpret_cast<u32x4*>(buf)[64 + lane] = s.v[1];
+                reinterpret_cast<uint2*>(buf)[256 + lane] = s.tail;
+            }
+        };
         // bitmask: the step whose reads are in flight and the one being used (one where the registers do not hold two)
         WideWindow win[2];
         auto use = [&](int k) SD2_INLINE {  // step k of the round: strip k / 2, step k % 2 of its half
@@ -471,12 +479,22 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
             // shape on 64 tokens: 2182 us against 2211; everything waited for at the start of the next round: 2219.)
             if (i == SG - 1 && sent_b) wait_vector_memory();
             if constexpr (FMT == kWideBitmask) {
-                reinterpret_cast<u32x4*>(buf)[lane] = s.v[0];
-                reinterpret_cast<u32x4*>(buf)[64 + lane] = s.v[1];
-                reinterpret_cast<uint2*>(buf)[256 + lane] = s.tail;
-                const bool crowded = dense >> i & 1u;
+                stage_out(s);
                 const uint32_t mk = s.mk & keep;
-                request(s, ahead, i, tl_next, parts_next);
+                // A half that did not fit the stage: its first step did (2048 bytes of values, 14 of misalignment, 8 of slack).  Its second is
+                // fetched by way of the stage, whose next request waits for it, and takes the first one's place in LDS once that has been read.
+                // (gate|up of the 3B shape on 17 tokens, 20 % sparse: 26.5 us, with a half's steps fetched one by one behind the next request 43.4.)
+                const bool crowded = dense >> i & 1u;
+                uint32_t first = 0u;  // piece of the half's stream
+                if (crowded) {
+                    first = (wide_lane(runs, 16 * i + 4) - lds) >> 4;
+                    const uint32_t off = wide_lane(parts.off, 16 * i) + first * 16u, last = min(wide_lane(parts.n16, 16 * i) - first, kWideStepPieces) - 1u;
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) s.v[c] = *reinterpret_cast<const u32x4*>(a.vals + (off + min((uint32_t)(c * 64 + lane), last) * 16u));
+                    s.tail = *reinterpret_cast<const uint2*>(a.vals + (off + min(256u + lane, 2u * last + 1u) * 8u));
+                } else {
+                    request(s, ahead, i, tl_next, parts_next);
+                }
                 asm volatile("" ::: "memory");  // the request goes out before the expansion, not after it
                 uint32_t ex[2];
                 wide_scan(mk, ex);
@@ -484,11 +502,9 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
                 for (int q = 0; q < 2; ++q) {
                     const int k = 2 * i + q;
                     uint32_t step_runs = runs;
-                    if (crowded) {  // the step's own stream is fetched here
-                        const uint32_t first = (wide_lane(runs, 16 * i + 4 * q) - lds) >> 4;  // piece of the half's stream
-                        const u32x4* s16 = reinterpret_cast<const u32x4*>(a.vals + wide_lane(parts.off, 16 * i)) + first;
-                        const uint32_t n = min(wide_lane(parts.n16, 16 * i) - first, kWideStepPieces);
-                        for (uint32_t c = lane; c < n; c += 64) reinterpret_cast<u32x4*>(buf)[c] = s16[c];
+                    if (q == 1 && crowded) {
+                        stage_out(s);
+                        request(s, ahead, i, tl_next, parts_next);
                         asm volatile("" ::: "memory");
                         step_runs = runs - first * 16u;
                     }
