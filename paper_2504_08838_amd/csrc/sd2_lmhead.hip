@@ -29,7 +29,8 @@ constexpr int kLmRing = 4;                      // chunk buffers per wavefront
 constexpr int kLmChunkDw = 16 * kLmChunkCols / 2;
 constexpr int kLmRedDw = kLmWaves * 256;        // one set of partial strips
 constexpr int kLmMiscDw = kLmWaves * 16 + 512;  // sums of squares per block of columns and token; final candidates (behind the first 128)
-constexpr int kLmLdsDw = kLmWaves * kLmRing * kLmChunkDw + 2 * kLmRedDw + kLmMiscDw;
+constexpr int kLmNowhereDw = 256;                // where requests for nothing lead; nobody reads it
+constexpr int kLmLdsDw = kLmWaves * kLmRing * kLmChunkDw + 2 * kLmRedDw + kLmMiscDw + kLmNowhereDw;
 
 struct LmCand {
     float v;
@@ -108,7 +109,9 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
     }
     int issued = 0, r_strip = 0, r_cc = 0;  // chunks requested; the next one's strip and column chunk
     auto request_chunk = [&](bool exists) {
-        uint32_t* dst = ring + (issued & (kLmRing - 1)) * kLmChunkDw;
+        // a request for nothing must not lead to the slot that the next chunk takes while it is in flight
+        uint32_t* dst = exists ? ring + (issued & (kLmRing - 1)) * kLmChunkDw : lm_smem + kLmLdsDw - kLmNowhereDw;
+        const int step = exists ? 256 : 0;
         const int row = ((int)blockIdx.x + r_strip * (int)gridDim.x) * (MODE == kLmGated ? 8 : 16);
         const int rows = MODE == kLmGated ? 8 : min(16, vocab - row);
         const int bytes = exists ? ((rows - 1) * hidden + kLmChunkCols) * 2 : 0;
@@ -119,7 +122,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
                                  : rows_lo;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(i < 2 ? rows_lo : rows_hi, (__attribute__((address_space(3))) void*)(dst + i * 256), 16,
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(i < 2 ? rows_lo : rows_hi, (__attribute__((address_space(3))) void*)(dst + i * step), 16,
                                                      (int)piece[i], 0, 0, 0);
         issued += exists ? 1 : 0;
         r_cc += exists ? 1 : 0;
@@ -219,7 +222,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
         }
         __builtin_amdgcn_sched_barrier(0);  // all of them on their way before the first is waited for
 #pragma unroll
-        for (int c = 0; c < CPW && c < kLmRing; ++c) request_chunk(c < n_cc);  // the first strip's: without a branch
+        for (int c = 0; c < CPW && c < kLmRing; ++c) request_chunk(c < kSure || c < n_cc);  // the first strip's: without a branch
         __builtin_amdgcn_sched_barrier(0);
         // The rest of the ring: as soon as the activations are there.  (Behind the norm, dense stack of 28 layers, hidden 1536, 5 tokens: 1131 us
         // against 1100.)
