@@ -537,10 +537,10 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
     const int n = lane & 15, g = lane >> 4;
     const int n_phases = 4 * a.layers;
     const int k_tok = a.k_tok;
-    // Results leave the CU as (strip, token, row) triples dealt to the threads: entry q = idx / 16 is strip q / k_tok, token
-    // q % k_tok; for q < 128 and k_tok <= 8 the quotient is (q * ceil(1024 / k_tok)) >> 10.
+    // Results leave the CU as items of four strips and one token, dealt to the wavefronts: item i is strips 4 (i / k_tok) .., token
+    // i % k_tok; for i < 128 and k_tok <= 8 the quotient is (i * ceil(1024 / k_tok)) >> 10.
     const uint32_t tok_mul = (1024u + (uint32_t)k_tok - 1u) / (uint32_t)k_tok;
-    static_assert(kMaxS * kMegaMaxTok <= 128 && kMegaMaxTok <= 8, "range in which the multiply-shift division is exact");
+    static_assert(kFlushIters * kMegaWaves <= 128 && kMegaMaxTok <= 8, "range in which the multiply-shift division is exact");
     KArgs ka = (KArgs)__builtin_amdgcn_kernarg_segment_ptr();
 
     uint32_t* bufs = mega_lds + wave * (2 * kTileDw);           // this wave's two tile buffers
@@ -1010,7 +1010,9 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
             }
         };
         // The sums of a unit (a strip's group of slabs) stay in the accumulators from its first tile to its last;
-        // then lane (n, g) stores rows 4g..4g+3 of token n into the unit's own slot: no other wavefront writes there.
+        // then lane (n, g) stores rows 4g..4g+3 of token n into the unit's own slot: no other wavefront writes there.  Every unit
+        // of a strip that exists is stored in every phase, units of which the matrix has no tile included (zeros), so the slots need no
+        // clearing behind their reader.
         f32x4 acc0 = f32x4{0.f, 0.f, 0.f, 0.f}, acc1 = f32x4{0.f, 0.f, 0.f, 0.f};
         auto unit_done = [&](uint32_t key) {
             if (n < kMegaMaxTok) {
@@ -1080,7 +1082,7 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
         // Bound by its instructions and one LDS round trip: every wavefront has one item at the usual sizes (five tokens, at most
         // eight strips), whose index arithmetic is scalar, whose slots are all read before the first add and whose 64 adds
         // are one contiguous request.  No load may be waited for here: the next phase's first stream is in flight and would
-        // be waited for too.  (A result per thread, with divisions per lane and three spilled registers reloaded here, took 0.12 us
+        // be waited for too.  (A result per thread, with divisions per lane and spilled registers reloaded here, took 0.12 us
         // more per phase; with the streams requested as buffers and nothing spilled the 3B shape's forward went from 1018 to
         // 991 us, its decode step from 1296 to 1221.)
         if (n_items > 0) {
