@@ -390,8 +390,7 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
     Round cur{0, 0}, ahead = next(cur);
     Tiles tl = directory(cur), tl_next = directory(ahead);
     // The first unit's activations go out in front of the stream, every wavefront's in front of anybody's: the compute unit
-    // returns loads in order, and behind another wavefront's stream they would wait for all of it (waited for at 8.6 us
-    // by half of the wavefronts instead of at 3.2).
+    // returns loads in order, and behind another wavefront's stream they would wait for all of it.
     int have_b = kXAhead ? -1 : unit_at(cur);
     bool sent_b = kXAhead;  // the next unit's activations are on their way
     if (kXAhead)
@@ -442,7 +441,7 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
         }
         // The next pass's activations, once this one's have been read: in front of the next pass's streams, so that they cost nobody
         // a wait.  Not across the end of a group, whose sums meet in the same LDS.
-        // (3B shape, 64 tokens: gate|up 24.1 -> 23.2 us, down 18.3 -> 18.1, a whole stack 2216 -> 2165.)
+        // (3B shape, 64 tokens, a whole stack: 2253 -> 2211 us.)
         sent_b = kXAhead && cur.pass + 1 < n_pass;
         if (sent_b) {
             asm volatile("" ::: "memory");

@@ -21,7 +21,7 @@ def _shape(hidden, heads, kv, inter, layers=2):
     return SimpleNamespace(layers=layers, hidden=hidden, q_out=128 * heads, kv_out=128 * kv, inter=inter, n_heads=heads, n_kv=kv, head_dim=128)
 
 
-def _model(shape, seed, dense=(True, True, True, True)):
+def _model(shape, seed, dense=(True, True, True, True), make=None):
     import gpu_util as gu
     import paper_2504_08838_amd as sd2
     table = {p: (n, k) for p, n, k in wl.layer_matrix_shapes(shape)}
@@ -29,7 +29,7 @@ def _model(shape, seed, dense=(True, True, True, True)):
 
     def get(layer, proj):
         if (layer, proj) not in cache:
-            cache[(layer, proj)] = wl.gen_weight(seed, layer, proj, *table[proj], 50)
+            cache[(layer, proj)] = make(proj, *table[proj]) if make else wl.gen_weight(seed, layer, proj, *table[proj], 50)
         return cache[(layer, proj)]
 
     mats = []
@@ -76,6 +76,50 @@ def test_glue_inside_the_linears_changes_no_bit(shape, k_tok):
         h = wl.gen_x(77 + i, 0, "q", k_tok, shape.hidden)
         apart, _, _ = gu.run_forward_trace(model, h, shape)
         assert np.array_equal(gu.run_forward(model, h, shape.hidden), apart)
+
+
+@pytest.mark.parametrize("shape", [_shape(h, 3, 1, i, layers=1) for h, i in ((128, 128), (1536, 1280), (2304, 640), (4096, 8960), (4224, 384))],
+                         ids=lambda s: str(s.hidden))
+@pytest.mark.parametrize("k_tok", [1, 5, 16])
+@pytest.mark.parametrize("half", ["attention", "mlp"])
+def test_one_layer_exact_integers(shape, k_tok, half):
+    """Every value between the launches is a whole number that its type holds: the norm's result (the residual's mean square is a power of
+    four), the values of the heads (the same for every token, so their average too), silu(32 m) = 32 m for m >= 0 (no gate is negative)."""
+    import gpu_util as gu
+    rng = np.random.default_rng([89, shape.hidden, k_tok])
+    hidden, shared = shape.hidden, shape.hidden // 2  # columns that all tokens share, up to their scale
+    few = min(1.0, 48 / hidden)
+
+    a = np.repeat([2, 1, 0], [hidden // 8, hidden // 2, hidden - hidden // 8 - hidden // 2])  # mean square 1
+    common = rng.permutation(a)
+    a = np.concatenate([np.broadcast_to(common[:shared], (k_tok, shared)), rng.permuted(np.broadcast_to(common[shared:], (k_tok, hidden - shared)), axis=1)],
+                       axis=1)
+    a = a * np.where(np.arange(hidden) < shared, rng.integers(0, 2, hidden) * 2 - 1, rng.integers(0, 2, (k_tok, hidden)) * 2 - 1)
+
+    def make(proj, n, k):
+        w = rng.integers(-2, 3, size=(n, k)) * (rng.random((n, k)) < few)
+        if proj in ("v", "gate"):
+            w[:, shared:] = 0
+        if proj == "gate":
+            w = 32 * abs(w) * np.sign(a[0])
+        if proj in (("down", "q") if half == "attention" else ("v", "q")):
+            w[:] = 0
+        weights[proj] = w
+        return _bits(w.astype(np.float32))
+
+    weights = {}
+    _, model = _model(shape, 0, make=make)
+    h = a * (4.0 * 2.0 ** (np.arange(k_tok) % 3))[:, None]
+    if half == "attention":
+        ctx = a @ weights["v"].T
+        assert abs(ctx).max() <= 256
+        ref = h + np.tile(ctx.reshape(k_tok, 1, 128), (1, 3, 1)).reshape(k_tok, -1) @ weights["o"].T
+    else:
+        gated = ((a @ weights["gate"].T) * (a @ weights["up"].T)).astype(np.float32)
+        gated = (wl.f32_to_bf16_bits(gated).astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+        ref = h + gated @ weights["down"].T
+    assert abs(ref).max() < 2 ** 24
+    assert np.array_equal(gu.run_forward(model, _bits(h.astype(np.float32)), hidden), ref)
 
 
 @pytest.mark.parametrize("dense", [(True, False, False, False), (False, True, False, False), (False, False, True, False),
