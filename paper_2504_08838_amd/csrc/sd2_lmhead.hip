@@ -30,7 +30,9 @@ constexpr int kLmChunkDw = 16 * kLmChunkCols / 2;
 constexpr int kLmRedDw = kLmWaves * 256;        // one set of partial strips
 constexpr int kLmMiscDw = kLmWaves * 16 + 512;  // sums of squares per block of columns and token; final candidates (behind the first 128)
 constexpr int kLmNowhereDw = 256;                // where requests for nothing lead; nobody reads it
-constexpr int kLmLdsDw = kLmWaves * kLmRing * kLmChunkDw + 2 * kLmRedDw + kLmMiscDw + kLmNowhereDw;
+constexpr int kLmThirdDw = kLmWaves / 2 * 512;   // squares of a third block of columns on their way between neighbours
+constexpr int kLmLdsDw = kLmWaves * kLmRing * kLmChunkDw + 2 * kLmRedDw + kLmMiscDw + kLmThirdDw + kLmNowhereDw;
+static_assert(kLmLdsDw * 4 <= 160 * 1024, "a workgroup fits a compute unit");
 
 struct LmCand {
     float v;
@@ -55,7 +57,7 @@ __device__ __forceinline__ void lm_better(float& a, int32_t& ia, float b, int32_
 // NORM: the activations are the RMS norm of the fp32 residual `h` (in place of bf16 `x`).  Every workgroup normalises for itself:
 // it reads twice the bytes of `x` from L2, and a launch with its gap (about 4 us) goes.
 // Dense stacks of 8 layers, us, every step a launch of its own and the activations behind the stream, then now: hidden 3072 on 5 tokens
-// 493 -> 421, on 16 tokens 573 -> 512; hidden 640 on one token 206 -> 176; MLP 2048 x 8192 on 5 tokens 23.9 -> 20.9.
+// 498 -> 436, on 16 tokens 574 -> 519; hidden 4096 on 5 tokens 612 -> 572; MLP 2048 x 8192 on 5 tokens 28.1 -> 24.2.
 enum { kLmHead, kLmPlain, kLmGated, kLmAdd };
 
 // As a linear TG = 2 takes up to 32 tokens in one pass (two sets of B operands in registers, two accumulators per strip; the partial
@@ -224,25 +226,21 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
 #pragma unroll
         for (int c = 0; c < CPW && c < kLmRing; ++c) request_chunk(c < kSure || c < n_cc);  // the first strip's: without a branch
         __builtin_amdgcn_sched_barrier(0);
-        // The rest of the ring: as soon as the activations are there.  (Behind the norm, dense stack of 28 layers, hidden 1536, 5 tokens: 1131 us
-        // against 1100.)
+        // The rest of the ring, once the activations are there.  (Behind the whole norm, dense stack of 28 layers, hidden 1536, 5 tokens: 1131 us
+        // against 1106.)
         auto fill_ring = [&]() {
 #pragma unroll
             for (int c = 0; c < kLmRing; ++c)
                 if (issued < kLmRing) issue_chunk();
         };
         if (NORM) {
-#pragma unroll
-            for (int cc = 0; cc < CPW; ++cc)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) asm volatile("" : "+v"(hr[cc][q][0]), "+v"(hr[cc][q][1]));
-            fill_ring();
             // The sum of squares, in the order in which a launch of its own adds it (residual_norm_kernel; for the head, the prologue
             // above), so that the same residual gives the same activations on either way.  That order: four columns, then a tree over the
             // 64 such groups of 256 columns whose first step adds columns 128 apart, then the blocks of 256 columns in turn.  Here
             // lane (n, g) of wavefront w has token n's groups (q, e) = columns 32 q + 8 g + 4 e of its column chunks, and the columns
-            // 128 away are the neighbouring wavefront's.  Neighbours meet in the room of the partial strips, two chunks at a time: of the
-            // first chunk's block the even wavefront adds up all, of the second's the odd one.  (Adding in whatever order was nearest cost
+            // 128 away are the neighbouring wavefront's.  Neighbours meet in the room of the partial strips, two chunks at a time (three
+            // chunks at once, by way of room of its own for the third): of the first chunk's block the even wavefront adds up all, of the
+            // second's the odd one, of the third's the even one again.  (Adding in whatever order was nearest cost
             // 0.4 us less a launch and moved a dense stack's outputs by 2e-3: other bf16 neighbours.)
             constexpr int kBlocks = HEAD && CPW > 2 ? 2 : CPW;  // the head's threads first add their columns 2048 apart
             constexpr int kTokDw = 4 * kBlocks + 4;             // a token's blocks, and a piece to spread the tokens over the banks
@@ -268,18 +266,39 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
             };
+            // adds up a block whose squares are in `v` and, of the neighbour, at `get`
+            auto add_up = [&](const f32x4 (&v)[2], const f32x4* get, int block) {
+                float s[2];
 #pragma unroll
-            for (int c0 = 0; c0 < kBlocks; c0 += 2) {
+                for (int e = 0; e < 2; ++e) {
+                    const f32x4 both = v[e] + get[64 * e];
+                    s[e] = (both[0] + both[2]) + (both[1] + both[3]);
+                }
+#pragma unroll
+                for (int o = 32; o >= 16; o >>= 1)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) s[e] += __shfl_xor(s[e], o);
+                if (lane < 16) misc[lane * kTokDw + (wave >> 1) + 4 * block] = s[0] + s[1];
+            };
+            constexpr bool kThird = kBlocks == 3;
+            f32x4* third_at = reinterpret_cast<f32x4*>(misc + kLmMiscDw) + (wave >> 1) * 128 + lane;
+#pragma unroll
+            for (int c0 = 0; c0 < (kThird ? 1 : kBlocks); c0 += 2) {
                 // the second pair of chunks goes where this wavefront has just read of the first (nobody else reads there)
                 f32x4* put = reinterpret_cast<f32x4*>(red) + (c0 ? wave : wave ^ 1) * 128 + lane;
                 const f32x4* get = reinterpret_cast<const f32x4*>(red) + (c0 ? wave ^ 1 : wave) * 128 + lane;
                 const bool pair = c0 + 1 < kBlocks;
-                f32x4 first[2], second[2], v[2];
+                f32x4 first[2], second[2], third[2], v[2];
                 squares(c0, first);
                 squares(pair ? c0 + 1 : c0, second);
+                if (kThird) squares(kBlocks - 1, third);
                 if (odd) {
                     put[0] = first[0];
                     put[64] = first[1];
+                    if (kThird) {
+                        third_at[0] = third[0];
+                        third_at[64] = third[1];
+                    }
                     v[0] = second[0];
                     v[1] = second[1];
                 } else {
@@ -290,19 +309,10 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
                     v[0] = first[0];
                     v[1] = first[1];
                 }
+                if (kThird || c0 + 2 >= kBlocks) fill_ring();  // all of the residual is there
                 meet();
-                if (!odd || pair) {
-#pragma unroll
-                    for (int e = 0; e < 2; ++e) v[e] += get[64 * e];
-                    float s[2];
-#pragma unroll
-                    for (int e = 0; e < 2; ++e) s[e] = (v[e][0] + v[e][2]) + (v[e][1] + v[e][3]);
-#pragma unroll
-                    for (int o = 32; o >= 16; o >>= 1)
-#pragma unroll
-                        for (int e = 0; e < 2; ++e) s[e] += __shfl_xor(s[e], o);
-                    if (lane < 16) misc[lane * kTokDw + (wave >> 1) + 4 * (odd ? c0 + 1 : c0)] = s[0] + s[1];
-                }
+                if (!odd || pair) add_up(v, get, odd ? c0 + 1 : c0);
+                if (kThird && !odd) add_up(third, third_at, kBlocks - 1);
                 asm volatile("" ::: "memory");  // (the reads have returned: their sums are on their way)
             }
             meet();
