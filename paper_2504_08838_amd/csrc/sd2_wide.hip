@@ -67,17 +67,9 @@ struct WideStage<kWideDense> {
 };
 constexpr uint32_t kWideStaged = 2560;
 
-// A wavefront's LDS: room for the staged stream of half a tile (bitmask) or a block that goes from row order to operand order
-// (dense), then, where it fits, the next unit's activations.  A stream is staged whole up to 2560 bytes; when a tile's values
-// crowd into one half, a step of 64 columns at a time.
-constexpr int wide_buf_dw(int fmt) { return fmt == 0 /* bitmask */ ? (2560 + 32) / 4 : fmt == 2 /* dense */ ? 4096 / 4 : 0; }
-constexpr uint32_t kWideStepPieces = (2048 + 14 + 8 + 15) / 16;  // values, misalignment, slack
-static_assert(kWideStepPieces * 16 <= kWideStaged, "a step fits the stage");
-constexpr int kWideLdsBytes = 160 * 1024;
-constexpr bool wide_x_ahead(int fmt, int tg, int w) { return w * (wide_buf_dw(fmt) * 4 + tg * 4096) + (fmt == 0 ? 128 : 0) <= kWideLdsBytes; }
-constexpr int wide_wave_dw(int fmt, int tg, int w) {
-    return wide_x_ahead(fmt, tg, w) ? wide_buf_dw(fmt) + tg * 1024 : (wide_buf_dw(fmt) > 1024 ? wide_buf_dw(fmt) : 1024);
-}
+// A wavefront's LDS: the staged stream of half a tile (it can hold 4096 bytes of values when a tile's values crowd into one
+// half, 14 bytes of misalignment and 8 of slack), or a block that goes from row order to operand order.
+constexpr int kWideBufDw = (4096 + 32) / 4;
 
 // One 64-column step of a bitmask tile between its LDS reads and their use: the windows of its four runs, their selectors and
 // byte offsets.  The reads of a step are issued before the step ahead of it is used, so that a wavefront always has LDS
@@ -160,9 +152,7 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
         if (tid < 16) lut[tid] = make_expand_selector((uint32_t)tid);
         __syncthreads();
     }
-    constexpr bool kXAhead = wide_x_ahead(FMT, TG, W);  // the next unit's activations travel while this one's are used
-    uint32_t* buf = wide_smem + wave * wide_wave_dw(FMT, TG, W);
-    uint32_t* xbuf = kXAhead ? buf + wide_buf_dw(FMT) : buf;
+    uint32_t* buf = wide_smem + wave * kWideBufDw;
     float* red = reinterpret_cast<float*>(wide_smem);  // [strip of the group][wk][TG][256], in place of the buffers
 
     const int split = (int)blockIdx.x % a.n_split, sblk = (int)blockIdx.x / a.n_split;
@@ -267,14 +257,8 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
     };
 
     // The unit's activations: operand B of token group tg, columns 64 q + 16 g + 8 e of the unit in b[tg][2 q + e].
-    // Tokens past the last repeat it or are zero (their results are not written).
+    // Columns past the matrix are zero; tokens past the last repeat it (their results are not written).
     u32x4 b[TG][4];
-    auto clear_past = [&](u32x4 (&v)[4], int u) SD2_INLINE {  // columns past the matrix are zero
-        const int col = 128 * u + 16 * g;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (col + 64 * (j >> 1) >= a.k_in) v[j] = u32x4{0u, 0u, 0u, 0u};
-    };
     auto load_b = [&](int u) SD2_INLINE {  // first half: the loads
         int l = lane;
         asm volatile("" : "+v"(l));
@@ -289,35 +273,10 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
         for (int tg = 0; tg < TG; ++tg) {
             asm volatile("" : "+v"(b[tg][0]), "+v"(b[tg][1]), "+v"(b[tg][2]), "+v"(b[tg][3]));
             block_to_operands(b[tg], buf, lane);
-            clear_past(b[tg], u);
-        }
-    };
-    // The same by way of LDS alone: requested straight into the wavefront's own place for them, in the order that the operand
-    // reads want (the memory side of a request may be any 16 bytes), a whole pass ahead.  Requested of a buffer from the unit's first
-    // column to the end of x, empty for a unit past the matrix; a token's row is in the vector offset, so that rows past the last
-    // token ask memory for nothing (the hardware's range check, which does not look at scalar offsets).
-    auto send_b = [&](int u) SD2_INLINE {
-        int l = lane;
-        asm volatile("" : "+v"(l));
-        const int left = u < a.n_units ? (a.k_tok * a.k_in - 128 * u) * 2 : 0;  // bytes
-        const auto part = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(a.x) + 128 * u, 0, left, 0x00020000);
+            const int col = 128 * u + 16 * g;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = 4 * j + (l >> 4);
-            const int off = (r * a.k_in + 8 * ((l & 15) ^ r)) * 2;
-#pragma unroll
-            for (int tg = 0; tg < TG; ++tg)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(part, (__attribute__((address_space(3))) void*)(xbuf + tg * 1024 + j * 256), 16,
-                                                         off + 32 * tg * a.k_in, 0, 0, 0);
-        }
-    };
-    auto read_b = [&](int u) SD2_INLINE {
-#pragma unroll
-        for (int tg = 0; tg < TG; ++tg) {
-            const u32x4* b16 = reinterpret_cast<const u32x4*>(xbuf + tg * 1024);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) b[tg][i] = b16[n * 16 + ((8 * (i >> 1) + 2 * g + (i & 1)) ^ n)];
-            clear_past(b[tg], u);
+            for (int j = 0; j < 4; ++j)
+                if (col + 64 * (j >> 1) >= a.k_in) b[tg][j] = u32x4{0u, 0u, 0u, 0u};
         }
     };
     auto op = [&](const u32x4& q) SD2_INLINE { return __builtin_bit_cast(bf16x8, q); };
@@ -389,21 +348,13 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
     Stage st[SG];  // each is requested for the next round as soon as it is used: a round's worth is in flight
     Round cur{0, 0}, ahead = next(cur);
     Tiles tl = directory(cur), tl_next = directory(ahead);
-    // The first unit's activations go out in front of the stream, every wavefront's in front of anybody's: the compute unit
-    // returns loads in order, and behind another wavefront's stream they would wait for all of it.
-    int have_b = kXAhead ? -1 : unit_at(cur);
-    bool sent_b = kXAhead;  // the next unit's activations are on their way
-    if (kXAhead)
-        send_b(unit_at(cur));
-    else
-        load_b(have_b);
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    // the first unit's activations go out in front of the stream: behind it they would wait for all of it
+    int have_b = unit_at(cur);
+    load_b(have_b);
     Parts parts = parts_of(tl);
 #pragma unroll
     for (int i = 0; i < SG; ++i) request(st[i], cur, i, tl, parts);
-    if (!kXAhead) turn_b(have_b);
+    turn_b(have_b);
     clear();
     const uint32_t lds = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)reinterpret_cast<const uint8_t*>(buf);
     // LDS byte addresses of a round's runs, and which of its halves do not fit the staged part
@@ -428,35 +379,11 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
         const uint32_t whole = (uint32_t)__builtin_amdgcn_readfirstlane(128 * u + 128 > a.k_in ? 0 : -1);
         if (u != have_b) {
             have_b = u;
-            if constexpr (kXAhead) {
-                if (!sent_b) send_b(u);
-                if (!sent_b || r == 0) wait_vector_memory();  // else waited for in the round before
-                read_b(u);
-            } else {
-                load_b(u);
-                // waited for here: a wait at the use, on every strip, would take the requests in flight with it
-                __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-                turn_b(u);
-            }
+            load_b(u);
+            // waited for here: a wait at the use, on every strip, would take the requests in flight with it
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+            turn_b(u);
         }
-        // The next pass's activations, once this one's have been read: in front of the next pass's streams, so that they cost nobody
-        // a wait.  Not across the end of a group, whose sums meet in the same LDS.
-        // (3B shape, 64 tokens, a whole stack: 2253 -> 2211 us.)
-        sent_b = kXAhead && cur.pass + 1 < n_pass;
-        if (sent_b) {
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-            asm volatile("" ::: "memory");
-            send_b(unit_at(ahead));
-            asm volatile("" ::: "memory");
-        }
-        auto stage_out = [&](const Stage& s) SD2_INLINE {
-            if constexpr (FMT == kWideBitmask) {
-                reinterpret_cast<u32x4*>(buf)[lane] = s.v[0];
-                reinterpret_cast<u32x4*>(buf)[64 + lane] = s.v[1];
-                reinterpret_cast<uint2*>(buf)[256 + lane] = s.tail;
-            }
-        };
         // bitmask: the step whose reads are in flight and the one being used (one where the registers do not hold two)
         WideWindow win[2];
         auto use = [&](int k) SD2_INLINE {  // step k of the round: strip k / 2, step k % 2 of its half
@@ -473,41 +400,24 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
 #pragma unroll
         for (int i = 0; i < SG; ++i) {
             Stage& s = st[i];
-            // The next pass's activations are in LDS once everything asked for has come: no count of requests decides it, they are of
-            // several kinds and some repeat an address.  Here the youngest request is a strip old.  (Counting on the order of loads, 3B
-            // shape on 64 tokens: 2182 us against 2211; everything waited for at the start of the next round: 2219.)
-            if (i == SG - 1 && sent_b) wait_vector_memory();
             if constexpr (FMT == kWideBitmask) {
-                stage_out(s);
-                const uint32_t mk = s.mk & keep;
-                // A half that did not fit the stage: its first step did (2048 bytes of values, 14 of misalignment, 8 of slack).  Its second is
-                // fetched by way of the stage, whose next request waits for it, and takes the first one's place in LDS once that has been read.
-                // (gate|up of the 3B shape on 17 tokens, 20 % sparse: 26.5 us, with a half's steps fetched one by one behind the next request 43.4.)
-                const bool crowded = dense >> i & 1u;
-                uint32_t first = 0u;  // piece of the half's stream
-                if (crowded) {
-                    first = (wide_lane(runs, 16 * i + 4) - lds) >> 4;
-                    const uint32_t off = wide_lane(parts.off, 16 * i) + first * 16u, last = min(wide_lane(parts.n16, 16 * i) - first, kWideStepPieces) - 1u;
-#pragma unroll
-                    for (int c = 0; c < 2; ++c) s.v[c] = *reinterpret_cast<const u32x4*>(a.vals + (off + min((uint32_t)(c * 64 + lane), last) * 16u));
-                    s.tail = *reinterpret_cast<const uint2*>(a.vals + (off + min(256u + lane, 2u * last + 1u) * 8u));
-                } else {
-                    request(s, ahead, i, tl_next, parts_next);
+                reinterpret_cast<u32x4*>(buf)[lane] = s.v[0];
+                reinterpret_cast<u32x4*>(buf)[64 + lane] = s.v[1];
+                reinterpret_cast<uint2*>(buf)[256 + lane] = s.tail;
+                if (dense >> i & 1u) {  // the rest of a dense half's stream is fetched here
+                    const u32x4* s16 = reinterpret_cast<const u32x4*>(a.vals + wide_lane(parts.off, 16 * i));
+                    const uint32_t n16 = wide_lane(parts.n16, 16 * i);
+                    for (uint32_t c = kWideStaged / 16 + lane; c < n16; c += 64) reinterpret_cast<u32x4*>(buf)[c] = s16[c];
                 }
+                const uint32_t mk = s.mk & keep;
+                request(s, ahead, i, tl_next, parts_next);
                 asm volatile("" ::: "memory");  // the request goes out before the expansion, not after it
                 uint32_t ex[2];
                 wide_scan(mk, ex);
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
                     const int k = 2 * i + q;
-                    uint32_t step_runs = runs;
-                    if (q == 1 && crowded) {
-                        stage_out(s);
-                        request(s, ahead, i, tl_next, parts_next);
-                        asm volatile("" ::: "memory");
-                        step_runs = runs - first * 16u;
-                    }
-                    wide_reads(win[kAhead ? k & 1 : 0], step_runs, 16 * i + 4 * q, lut, ex[q], q ? mk >> 16 : mk);
+                    wide_reads(win[kAhead ? k & 1 : 0], runs, 16 * i + 4 * q, lut, ex[q], q ? mk >> 16 : mk);
                     asm volatile("" ::: "memory");
                     if (!kAhead)
                         use(k);
@@ -626,8 +536,7 @@ bool wide_plan(int n_out, int k_in, int n_strips, int k_tok, bool gated, int max
 
 template <int FMT, int TG, int SG, int W>
 static hipError_t launch_wide_t(const WideArgs& a, const WidePlan& p, hipStream_t s) {
-    constexpr size_t lds = (size_t)std::max(W * wide_wave_dw(FMT, TG, W) * 4, SG * W * TG * 1024);
-    static_assert(lds <= kWideLdsBytes, "a workgroup fits a compute unit");
+    constexpr size_t lds = (size_t)std::max(W * kWideBufDw * 4, SG * W * TG * 1024);
     static std::atomic<bool> raised{false};
     if (!raised.load(std::memory_order_acquire)) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wide_linear_kernel<FMT, TG, SG, W>),

@@ -1,5 +1,5 @@
-"""Wide linears whose workgroups take several passes over several groups of strips: the next pass's activations travel while this
-one's are used, and not across the end of a group.  Small integers: every sum is exact in fp32, results equal to the last bit."""
+"""Wide linears whose workgroups take several passes over several groups of strips, and bitmask halves around the size of their stage.
+Small integers: every sum is exact in fp32, results equal to the last bit."""
 import numpy as np
 import pytest
 

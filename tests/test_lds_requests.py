@@ -51,11 +51,11 @@ def scalar_offsets(tmp_path_factory):
 
 
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
-@pytest.mark.parametrize("kernel", ["mega_forward_kernel", "wide_linear_kernel", "lm_head_kernel"])
+@pytest.mark.parametrize("kernel", ["mega_forward_kernel", "lm_head_kernel"])
 def test_no_scalar_offset(scalar_offsets, kernel):
     assert list(scalar_offsets[kernel]) == ["0"]
 
 
 @pytest.mark.skipif(not os.path.exists(OBJDUMP), reason="no disassembler")
 def test_no_other_kernel_has_such_requests(scalar_offsets):
-    assert set(scalar_offsets) == {"mega_forward_kernel", "wide_linear_kernel", "lm_head_kernel"}
+    assert set(scalar_offsets) == {"mega_forward_kernel", "lm_head_kernel"}
