@@ -46,7 +46,8 @@ constexpr int kMiscDw = 544;                            // attention probabiliti
 constexpr int kAttHeads = 6;                            // heads (and kv heads) one workgroup may need
 constexpr int kAreaDw = 2 * kMegaWaves * kTileDw;       // two tile buffers per wavefront: one being expanded, one being filled
 constexpr size_t kMegaLds = (size_t)(kAreaDw + kXldsDw + kRedDw + kMiscDw + 4 * kPlanDw) * 4;
-constexpr int kBarWords = 8 * 32;                   // 8 group counters, one per 128-byte line
+constexpr int kBarCopies = 16;                      // of the barrier's counters (see barrier_arrive)
+constexpr int kBarWords = kBarCopies * 8 * 32;      // 8 group counters in each, one per 128-byte line
 static_assert(kAttHeads * 128 == kMegaThreads, "one thread per (head slot, dimension)");
 static_assert(4 * kMegaThreads >= kMegaMaxHidden && 2 * kMegaThreads >= kMaxB * 256, "columns per thread in the prologues");
 static_assert(kMaxBAtt * 256 <= kAttHeads * 128, "attention block fits the head slots");
@@ -230,7 +231,7 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // Grid barrier: the workgroups form 8 groups (by id mod 8), each with an arrival counter of its own in a separate
-// cache line.  Counters only grow; `gen` is the number of barriers passed, so after barrier number gen counter g
+// cache line (of every copy).  Counters only grow; `gen` is the number of barriers passed, so after barrier number gen counter g
 // holds gen * (size of group g).  Arriving is one atomic add whose result nobody waits for; waiting is eight lanes
 // of one wavefront polling the eight counters side by side, so a barrier costs about one trip to memory and back
 // after the last arrival.  Waits are bounded: on overrun *err is set and the kernel keeps going (results are then
@@ -239,23 +240,28 @@ __device__ __forceinline__ void lds_barrier() {
 // The barrier comes in two halves so that a wavefront can expand its next weight tile (which needs no
 // activations) between announcing its arrival and waiting for the release.
 //
-// Arrive: every wavefront has its stores and atomics acknowledged; thread 0 then counts the workgroup in.
+// The counters exist in sixteen copies: a workgroup counts itself in in all of them with one request (a lane per copy) and polls
+// one.  With one copy 256 workgroups poll the same eight lines, and the arrivals that everyone waits for queue behind the polls.
+// 3B shape on 5 tokens / 1.5B shape on 3 / 3B in 2:4, forward: 996 / 736 / 976 us with one copy, 987 / 721 / 963 with four, 987 / 717 /
+// 961 with eight, 986 / 712 / 955 with sixteen, 991 / 715 / 965 with 32 (more adds than polls).
+//
+// Arrive: every wavefront has its stores and atomics acknowledged; the first lanes then count the workgroup in.
 __device__ __forceinline__ void barrier_arrive(unsigned* bar, unsigned& gen) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     gen += 1;
-    if (threadIdx.x == 0) (void)__hip_atomic_fetch_add(&bar[(blockIdx.x & 7u) * 32], 1u, __ATOMIC_RELAXED, SD2_AGENT);
+    if (threadIdx.x < kBarCopies) (void)__hip_atomic_fetch_add(&bar[(threadIdx.x * 8u + (blockIdx.x & 7u)) * 32], 1u, __ATOMIC_RELAXED, SD2_AGENT);
 }
 
 // Wait: lanes 0..7 of the first wavefront poll the group counters (bounded), then the workgroup goes on together.
 __device__ __forceinline__ void barrier_wait(unsigned* bar, unsigned* err, unsigned ncu, unsigned gen, int& spin_limit) {
     if (threadIdx.x < 64) {
-        const unsigned g = threadIdx.x;
+        const unsigned g = threadIdx.x, copy = (blockIdx.x >> 3) % kBarCopies;
         const unsigned ngrp = ncu < 8u ? ncu : 8u;
         const unsigned want = g < ngrp ? gen * ((ncu - g + 7u) / 8u) : 0u;
         int spins = 0;
         for (;;) {
-            const unsigned have = g < ngrp ? __hip_atomic_load(&bar[g * 32], __ATOMIC_RELAXED, SD2_AGENT) : 0u;
+            const unsigned have = g < ngrp ? __hip_atomic_load(&bar[(copy * 8u + g) * 32], __ATOMIC_RELAXED, SD2_AGENT) : 0u;
             if (__all(have >= want)) break;  // wave-uniform exit
             __builtin_amdgcn_s_sleep(1);
             if (++spins > spin_limit) {
