@@ -42,13 +42,13 @@ constexpr int kXldsDw = kMaxB * kMegaMaxTok * kXRow / 2;  // bf16 [slab][token][
 constexpr int kMaxUnits = 24;                           // (strip, slab group) units of a block: one result slot each
 constexpr int kRedDw = kMaxUnits * kMegaMaxTok * 16;    // fp32 [strip][group][token][row]
 constexpr int kPlanDw = 16;                             // per-kind plan: s_eff b_eff strip0 slab0 | n_strips 1/grp_slabs active tiles/wave | mask_off(2) val_off(2) | grp_slabs n_grp 1/n_grp -
-constexpr int kMiscDw = 544;                            // attention probabilities, per-token scalars
-constexpr int kAttHeads = 6;                            // heads (and kv heads) one workgroup may need
+constexpr int kMiscDw = kMegaMaxTok * 12;               // sums of squares per token and wavefront
+constexpr int kAttHeads = 6;                            // heads one workgroup may need
 constexpr int kAreaDw = 2 * kMegaWaves * kTileDw;       // two tile buffers per wavefront: one being expanded, one being filled
 constexpr size_t kMegaLds = (size_t)(kAreaDw + kXldsDw + kRedDw + kMiscDw + 4 * kPlanDw) * 4;
 constexpr int kBarCopies = 16;                      // of the barrier's counters (see barrier_arrive)
 constexpr int kBarWords = kBarCopies * 8 * 32;      // 8 group counters in each, one per 128-byte line
-static_assert(kAttHeads * 128 == kMegaThreads, "one thread per (head slot, dimension)");
+static_assert(kAttHeads * 128 == kMegaThreads, "two wavefronts per head slot");
 static_assert(4 * kMegaThreads >= kMegaMaxHidden && 2 * kMegaThreads >= kMaxB * 256, "columns per thread in the prologues");
 static_assert(kMaxBAtt * 256 <= kAttHeads * 128, "attention block fits the head slots");
 
@@ -100,6 +100,30 @@ __device__ __forceinline__ void wave_sums_lane63(float (&v)[N]) {
     SD2_DPP_STAGE(0x142, 0xa);  // row_bcast:15
     SD2_DPP_STAGE(0x143, 0xc);  // row_bcast:31
 #undef SD2_DPP_STAGE
+}
+
+// Calls f with the number of token slots that the code is made for, the smallest of 1 2 3 4 5 8 that holds the tokens: straight-line
+// work on all slots (those past the last token repeat it; nobody reads their results) takes less time than a branch per token, which
+// is paid by every wavefront of every workgroup in every phase, and no token's loads wait for those of the one before it.  With this
+// and attention without meetings in LDS: 3B shape on 5 tokens 980 -> 958 us, 1.5B shape on 3 tokens 713 -> 675, 3B in 2:4 947 -> 922,
+// decode step of the 3B shape 1183 -> 1148.
+template <typename F>
+__device__ __forceinline__ void with_token_slots(int k_tok, F&& f) {
+    if (k_tok <= 2) {
+        if (k_tok == 1)
+            f(std::integral_constant<int, 1>{});
+        else
+            f(std::integral_constant<int, 2>{});
+    } else if (k_tok <= 4) {
+        if (k_tok == 3)
+            f(std::integral_constant<int, 3>{});
+        else
+            f(std::integral_constant<int, 4>{});
+    } else if (k_tok == 5) {
+        f(std::integral_constant<int, 5>{});
+    } else {
+        f(std::integral_constant<int, kMegaMaxTok>{});
+    }
 }
 
 // The argument block as it sits in the kernarg segment: indexing it with a run-time (wave-uniform) index
@@ -553,15 +577,14 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
     int cb = 0;                                                 // the one the current tile's stream is in (or on its way to)
     uint16_t* xlds = reinterpret_cast<uint16_t*>(mega_lds + kAreaDw);
     float* red = reinterpret_cast<float*>(mega_lds + kAreaDw + kXldsDw);
-    float* misc = red + kRedDw;                                 // [0,432) attention scores / probabilities
-    float* part_sums = misc + 448;                              // [token][wave] sums of squares of a wavefront's columns
-    static_assert(448 + kMegaMaxTok * kMegaWaves <= kMiscDw && (kAreaDw + kXldsDw + kRedDw + 448) % 4 == 0, "partial sums fit, 16-byte aligned");
+    float* part_sums = red + kRedDw;                            // [token][wave] sums of squares of a wavefront's columns
+    static_assert(kMegaMaxTok * kMegaWaves <= kMiscDw && (kAreaDw + kXldsDw + kRedDw) % 4 == 0, "partial sums fit, 16-byte aligned");
     if (tid < 16) lut[tid] = make_expand_selector((uint32_t)tid);
-    for (int i = tid; i < kRedDw + kMiscDw; i += kMegaThreads) red[i] = 0.f;  // accumulators, scores, sums
+    for (int i = tid; i < kRedDw + kMiscDw; i += kMegaThreads) red[i] = 0.f;  // accumulators, sums
     for (int i = tid; i < kXldsDw; i += kMegaThreads) (mega_lds + kAreaDw)[i] = 0u;  // rows of unused token slots stay zero
 
     // per-kind plans -> LDS
-    uint32_t* plans = reinterpret_cast<uint32_t*>(misc + kMiscDw);
+    uint32_t* plans = reinterpret_cast<uint32_t*>(part_sums + kMiscDw);
     if (tid < 4) {
         const int n_sblk = ka->geo[tid].n_sblk, n_bblk = ka->geo[tid].n_bblk;
         const int s_blk = ka->geo[tid].s_blk, b_blk = ka->geo[tid].b_blk;
@@ -737,113 +760,102 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
         if (kind == 0 || kind == 2) {
             // Thread i owns columns 4i..4i+3 of every token: all loads of the residual are in flight at once,
             // the squares meet in LDS, and each thread then normalises and rounds the columns it holds.
-            const int c4 = 4 * tid;
-            i32x4 hraw[kMegaMaxTok];
+            with_token_slots(k_tok, [&](auto slots) {
+                constexpr int N = decltype(slots)::value;
+                const int c4 = 4 * tid;
+                i32x4 hraw[N];
 #pragma unroll
-            for (int t = 0; t < kMegaMaxTok; ++t)
-                hraw[t] = (t < k_tok && c4 < a.hidden) ? *reinterpret_cast<const i32x4*>(h_cur + (size_t)t * a.hidden + c4) : i32x4{0, 0, 0, 0};
-            if (PROBE) {
+                for (int t = 0; t < N; ++t) hraw[t] = i32x4{0, 0, 0, 0};
+                if (c4 < a.hidden) {
+#pragma unroll
+                    for (int t = 0; t < N; ++t) hraw[t] = *reinterpret_cast<const i32x4*>(h_cur + (size_t)min(t, k_tok - 1) * a.hidden + c4);
+                }
+                if (PROBE) {
                     __builtin_amdgcn_s_waitcnt(0);
                     if (tt && tid == 0) tt[5] = __builtin_amdgcn_s_memrealtime();
-            }
-            {
-                // Sums of squares of all token slots at once (unused slots hold zeros), on the fixed-point numbers as they
-                // are: the scale is a power of two, so it can be applied to the totals without changing a bit.  Lane 63
-                // ends up with the wavefront's totals.
-                auto sums_of = [&](auto n_tag) {
-                    constexpr int N = decltype(n_tag)::value;
-                    float ss[N];
+                }
+                // Sums of squares of all token slots at once, on the fixed-point numbers as they are: the scale is a power of two, so
+                // it can be applied to the totals without changing a bit.  Lane 63 ends up with the wavefront's totals.
+                float ss[N];
+#pragma unroll
+                for (int t = 0; t < N; ++t) {
+                    const float f0 = (float)hraw[t][0], f1 = (float)hraw[t][1], f2 = (float)hraw[t][2], f3 = (float)hraw[t][3];
+                    ss[t] = f0 * f0 + f1 * f1 + f2 * f2 + f3 * f3;
+                }
+                wave_sums_lane63(ss);
+                if (lane == 63) {
+#pragma unroll
+                    for (int t = 0; t < N; ++t) part_sums[t * kMegaWaves + wave] = ss[t];  // plain stores: LDS float atomics are slow
+                }
+                lds_barrier();
+                // Every wavefront adds the twelve partial sums itself (lane t: token t, always in the same order), so the
+                // scale factors reach its lanes through scalar registers: no second trip through LDS, no second barrier.
+                float inv_t[N];
+                {
+                    float tot = 0.f;
+                    if (lane < N) {
+                        const f32x4* ps = reinterpret_cast<const f32x4*>(part_sums + lane * kMegaWaves);
+                        static_assert(kMegaWaves == 12, "three 16-byte reads hold a token's partial sums");
+                        const f32x4 p0 = ps[0], p1 = ps[1], p2 = ps[2];
+                        tot = ((((((((((p0[0] + p0[1]) + p0[2]) + p0[3]) + p1[0]) + p1[1]) + p1[2]) + p1[3]) + p2[0]) + p2[1]) + p2[2]) + p2[3];
+                    }
+                    tot *= fix_inv * fix_inv;
+                    const float r = 1.0f / sqrtf(tot / (float)a.hidden + 1e-5f);
+                    // a residual whose norm stays below the limit has every entry below it: the adds into it cannot wrap
+                    if (wave == 0 && lane < k_tok && !(tot < a.h_limit_sq)) __hip_atomic_fetch_or(a.err, 2u, __ATOMIC_RELAXED, SD2_AGENT);
+                    const float scaled = r * fix_inv;
+#pragma unroll
+                    for (int t = 0; t < N; ++t) inv_t[t] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scaled), t));
+                }
+                const int c = c4 - col_lo;
+                if (c >= 0 && c < n_col) {
+                    uint16_t* dst = xlds + ((c >> 8) * kMegaMaxTok) * kXRow + (c & 255);
 #pragma unroll
                     for (int t = 0; t < N; ++t) {
-                        const float f0 = (float)hraw[t][0], f1 = (float)hraw[t][1], f2 = (float)hraw[t][2], f3 = (float)hraw[t][3];
-                        ss[t] = f0 * f0 + f1 * f1 + f2 * f2 + f3 * f3;
-                    }
-                    wave_sums_lane63(ss);
-                    if (lane == 63) {
-#pragma unroll
-                        for (int t = 0; t < N; ++t) part_sums[t * kMegaWaves + wave] = ss[t];  // plain stores: LDS float atomics are slow
-                    }
-                };
-                // the usual draft lengths skip the work of the unused slots (their partial sums stay zero)
-                if (k_tok <= 5)
-                    sums_of(std::integral_constant<int, 5>{});
-                else
-                    sums_of(std::integral_constant<int, kMegaMaxTok>{});
-            }
-            lds_barrier();
-            // Every wavefront adds the twelve partial sums itself (lane t: token t, always in the same order), so the
-            // scale factors reach its lanes through scalar registers: no second trip through LDS, no second barrier.
-            float inv_t[kMegaMaxTok];
-            {
-                float tot = 0.f;
-                if (lane < kMegaMaxTok) {
-                    const f32x4* ps = reinterpret_cast<const f32x4*>(part_sums + lane * kMegaWaves);
-                    static_assert(kMegaWaves == 12, "three 16-byte reads hold a token's partial sums");
-                    const f32x4 p0 = ps[0], p1 = ps[1], p2 = ps[2];
-                    tot = ((((((((((p0[0] + p0[1]) + p0[2]) + p0[3]) + p1[0]) + p1[1]) + p1[2]) + p1[3]) + p2[0]) + p2[1]) + p2[2]) + p2[3];
-                }
-                tot *= fix_inv * fix_inv;
-                const float r = 1.0f / sqrtf(tot / (float)a.hidden + 1e-5f);
-                // a residual whose norm stays below the limit has every entry below it: the adds into it cannot wrap
-                if (wave == 0 && lane < k_tok && !(tot < a.h_limit_sq)) __hip_atomic_fetch_or(a.err, 2u, __ATOMIC_RELAXED, SD2_AGENT);
-                const float scaled = r * fix_inv;
-#pragma unroll
-                for (int t = 0; t < kMegaMaxTok; ++t) inv_t[t] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scaled), t));
-            }
-            const int c = c4 - col_lo;
-            if (c >= 0 && c < n_col) {
-#pragma unroll
-                for (int t = 0; t < kMegaMaxTok; ++t)
-                    if (t < k_tok) {
                         const float inv = inv_t[t];
                         const uint32_t lo = pack_bf16((float)hraw[t][0] * inv, (float)hraw[t][1] * inv);
                         const uint32_t hi = pack_bf16((float)hraw[t][2] * inv, (float)hraw[t][3] * inv);
-                        *reinterpret_cast<uint2*>(xlds + ((c >> 8) * kMegaMaxTok + t) * kXRow + (c & 255)) = make_uint2(lo, hi);
-                        if (TRACE) {
+                        *reinterpret_cast<uint2*>(dst + t * kXRow) = make_uint2(lo, hi);
+                        if (TRACE && t < k_tok) {
                             *reinterpret_cast<f32x4*>(a.trace_src + tr_s + (size_t)t * a.trace_smax + c4) =
                                 f32x4{from_fixed(hraw[t][0], fix_inv), from_fixed(hraw[t][1], fix_inv), from_fixed(hraw[t][2], fix_inv),
                                       from_fixed(hraw[t][3], fix_inv)};
                             *reinterpret_cast<uint2*>(a.trace_x + tr_x + (size_t)t * a.trace_kmax + c4) = make_uint2(lo, hi);
                         }
                     }
-            }
+                }
+            });
         } else if (kind == 3) {
             // thread i owns columns 2i, 2i+1 of the block; gate and up of every token are in flight at once
-            const int c = 2 * tid;
-            if (c < n_col) {
-                // loads of every token first, conversions afterwards: a use inside a token's own block would wait there,
-                // with the loads of the tokens after it not yet issued
-                i32x2 gr[kMegaMaxTok], ur[kMegaMaxTok];
+            with_token_slots(k_tok, [&](auto slots) {
+                constexpr int N = decltype(slots)::value;
+                const int c = 2 * tid;
+                if (c < n_col) {
+                    i32x2 gr[N], ur[N];
 #pragma unroll
-                for (int t = 0; t < kMegaMaxTok; ++t) {
-                    gr[t] = ur[t] = i32x2{0, 0};  // defined in every path: nothing is carried from the phase before
-                    if (t < k_tok) {
-                        const int* row = yg + (size_t)t * 2 * a.inter + col_lo + c;
+                    for (int t = 0; t < N; ++t) {
+                        const int* row = yg + (size_t)min(t, k_tok - 1) * 2 * a.inter + col_lo + c;
                         gr[t] = *reinterpret_cast<const i32x2*>(row);
                         ur[t] = *reinterpret_cast<const i32x2*>(row + a.inter);
                     }
-                }
-                f32x2 gv[kMegaMaxTok], uv[kMegaMaxTok];
+                    uint16_t* dst = xlds + ((c >> 8) * kMegaMaxTok) * kXRow + (c & 255);
 #pragma unroll
-                for (int t = 0; t < kMegaMaxTok; ++t) {
-                    gv[t] = f32x2{from_fixed(gr[t][0], fix_inv), from_fixed(gr[t][1], fix_inv)};
-                    uv[t] = f32x2{from_fixed(ur[t][0], fix_inv), from_fixed(ur[t][1], fix_inv)};
-                }
-#pragma unroll
-                for (int t = 0; t < kMegaMaxTok; ++t)
-                    if (t < k_tok) {
+                    for (int t = 0; t < N; ++t) {
+                        const f32x2 gv = f32x2{from_fixed(gr[t][0], fix_inv), from_fixed(gr[t][1], fix_inv)};
+                        const f32x2 uv = f32x2{from_fixed(ur[t][0], fix_inv), from_fixed(ur[t][1], fix_inv)};
                         // hardware exp2 and reciprocal: about 1e-6 relative, far inside the bf16 rounding that follows
-                        const uint32_t pk = pack_bf16(gv[t][0] * __builtin_amdgcn_rcpf(1.0f + __expf(-gv[t][0])) * uv[t][0],
-                                                      gv[t][1] * __builtin_amdgcn_rcpf(1.0f + __expf(-gv[t][1])) * uv[t][1]);
-                        *reinterpret_cast<uint32_t*>(xlds + ((c >> 8) * kMegaMaxTok + t) * kXRow + (c & 255)) = pk;
-                        if (TRACE) {
+                        const uint32_t pk = pack_bf16(gv[0] * __builtin_amdgcn_rcpf(1.0f + __expf(-gv[0])) * uv[0],
+                                                      gv[1] * __builtin_amdgcn_rcpf(1.0f + __expf(-gv[1])) * uv[1]);
+                        *reinterpret_cast<uint32_t*>(dst + t * kXRow) = pk;
+                        if (TRACE && t < k_tok) {
                             float* ts = a.trace_src + tr_s + (size_t)t * a.trace_smax + col_lo + c;
-                            *reinterpret_cast<f32x2*>(ts) = gv[t];
-                            *reinterpret_cast<f32x2*>(ts + a.inter) = uv[t];
+                            *reinterpret_cast<f32x2*>(ts) = gv;
+                            *reinterpret_cast<f32x2*>(ts + a.inter) = uv;
                             *reinterpret_cast<uint32_t*>(a.trace_x + tr_x + (size_t)t * a.trace_kmax + col_lo + c) = pk;
                         }
                     }
-            }
+                }
+            });
         } else if (KV) {
             // kind == 1 with a cache: the attention step left, per head, token and chunk, a maximum, a sum and 128
             // weighted values; thread (head slot hh, dimension d) combines the chunks of its head
@@ -886,109 +898,84 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
                     }
             }
         } else {
-            // kind == 1: causal attention among the in-flight tokens.  Thread (head slot hh, dimension d) keeps q of
-            // its head and k, v of that head's kv group for every token in registers; a score is summed over the
-            // 128 dimensions = two wavefronts (cross-lane adds, then one LDS add per wavefront).
+            // kind == 1: causal attention among the in-flight tokens.  Two wavefronts take a head, the first its earlier query rows,
+            // the second its later ones; a lane holds two dimensions.  Scores are summed across the lanes, the softmax is the
+            // same arithmetic in every lane, and nothing passes from one wavefront to another.  (With a dimension per lane, the
+            // scores of the two wavefronts met in LDS and the softmax went round lanes there: two more barriers.)
             const int D = 128;
-            const int hh = wave >> 1, d = (wave & 1) * 64 + lane;  // head slot is wave-uniform: scalar addressing
-            const int rep = a.n_heads / a.n_kv;
-            const int head = col_lo / D + hh;                 // blocks start on head boundaries (256 | col_lo)
-            const int kvh = head / rep;
-            const bool live = hh * D < n_col;
-            int qr[kMegaMaxTok], kr[kMegaMaxTok], vr[kMegaMaxTok];
+            const int hh = wave >> 1;  // head slot is wave-uniform: scalar addressing
+            if (hh * D < n_col)
+                with_token_slots(k_tok, [&](auto slots) {
+                    constexpr int N = decltype(slots)::value;
+                    constexpr int kHalf = N <= 2 ? 1 : N == 3 ? 2 : N <= 5 ? 3 : 5;  // rows of the first wavefront
+                    const int rep = a.n_heads / a.n_kv, head = col_lo / D + hh, kvh = head / rep;  // blocks start on head boundaries (256 | col_lo)
+                    i32x2 qr[N], kr[N], vr[N];
+                    const int* base = yq + 2 * lane;
 #pragma unroll
-            for (int t = 0; t < kMegaMaxTok; ++t) {
-                qr[t] = kr[t] = vr[t] = 0;
-                if (live && t < k_tok) {
-                    const int* row = yq + (size_t)t * nqkv;
-                    qr[t] = row[head * D + d];
-                    kr[t] = row[a.q_out + kvh * D + d];
-                    vr[t] = row[a.q_out + a.kv_out + kvh * D + d];
-                }
-            }
-            // the compiler would otherwise move each conversion into its token's block above, where it waits for that
-            // token's loads before the next token's are issued: eight trips to memory in a row
-#pragma unroll
-            for (int t = 0; t < kMegaMaxTok; ++t) asm volatile("" : "+v"(qr[t]), "+v"(kr[t]), "+v"(vr[t]));
-            float qv[kMegaMaxTok], kv[kMegaMaxTok], vv[kMegaMaxTok];
-#pragma unroll
-            for (int t = 0; t < kMegaMaxTok; ++t) {  // after all the loads (see the gated product above)
-                qv[t] = from_fixed(qr[t], fix_inv);
-                kv[t] = from_fixed(kr[t], fix_inv);
-                vv[t] = from_fixed(vr[t], fix_inv);
-            }
-            // scores of a head: lower triangle [i][j <= i] at i (i + 1) / 2 + j, 36 entries; two shares, one per wavefront
-            float* sp = misc + hh * 36;
-            float* sp_hi = misc + 216 + hh * 36;
-            if (live) {
-                // The triangle in batches whose sums cross the lanes together: rows 0..2 (six products), then a row at a
-                // time (four to eight products): wide enough to fill the hazard slots, without the unused half of a square.
-                float* share = (wave & 1) ? sp_hi : sp;
-                {
-                    float part[6] = {qv[0] * kv[0], qv[1] * kv[0], qv[1] * kv[1], qv[2] * kv[0], qv[2] * kv[1], qv[2] * kv[2]};
-                    wave_sums_lane63(part);  // (rows of unused token slots are zeros: nothing reads them)
-                    if (lane == 63) {
-#pragma unroll
-                        for (int e = 0; e < 6; ++e) share[e] = part[e];  // plain stores, summed below
+                    for (int t = 0; t < N; ++t) {
+                        const int* row = base + (size_t)min(t, k_tok - 1) * nqkv;
+                        qr[t] = *reinterpret_cast<const i32x2*>(row + head * D);
+                        kr[t] = *reinterpret_cast<const i32x2*>(row + a.q_out + kvh * D);
+                        vr[t] = *reinterpret_cast<const i32x2*>(row + a.q_out + a.kv_out + kvh * D);
                     }
-                }
-#define SD2_SCORE_ROW(I) \
-    if (I < k_tok) { \
-        float part[I + 1]; \
-        _Pragma("unroll") for (int j = 0; j <= I; ++j) part[j] = qv[I] * kv[j]; \
-        wave_sums_lane63(part); \
-        if (lane == 63) { \
-            _Pragma("unroll") for (int j = 0; j <= I; ++j) share[I * (I + 1) / 2 + j] = part[j]; \
-        } \
-    }
-                SD2_SCORE_ROW(3)
-                SD2_SCORE_ROW(4)
-                SD2_SCORE_ROW(5)
-                SD2_SCORE_ROW(6)
-                SD2_SCORE_ROW(7)
-#undef SD2_SCORE_ROW
-                static_assert(kMegaMaxTok == 8, "one row of scores per token slot");
-            }
-            lds_barrier();
-            // softmax: wavefront = head, lane = (row i, column j); a row's maximum and sum go round its eight lanes
-            if (wave < kAttHeads && wave * D < n_col) {
-                const int i = lane >> 3, j = lane & 7;
-                const bool on = i < k_tok && j <= i;
-                float* row = misc + wave * 36 + i * (i + 1) / 2;
-                const float scale = 1.0f / sqrtf((float)D);
-                const float sc = on ? (row[j] + row[216 + j]) * scale : -3.0e38f;
-                float mx = sc;
-                mx = fmaxf(mx, __shfl_xor(mx, 1));
-                mx = fmaxf(mx, __shfl_xor(mx, 2));
-                mx = fmaxf(mx, __shfl_xor(mx, 4));
-                const float e = on ? __expf(sc - mx) : 0.f;
-                float sum = e;
-                sum += __shfl_xor(sum, 1);
-                sum += __shfl_xor(sum, 2);
-                sum += __shfl_xor(sum, 4);
-                if (on) row[j] = e * __builtin_amdgcn_rcpf(sum);
-            }
-            lds_barrier();
-            if (live) {
-                const int cc = hh * D + d;
+                    const int cc = hh * D + 2 * lane;
+                    uint16_t* dst = xlds + ((cc >> 8) * kMegaMaxTok) * kXRow + (cc & 255);
+                    // query rows I0 .. I1 - 1: their scores cross the lanes together
+                    auto rows = [&](auto first, auto last) {
+                        constexpr int I0 = decltype(first)::value, I1 = decltype(last)::value;
+                        constexpr int kFirst = I0 * (I0 + 1) / 2, kScores = I1 * (I1 + 1) / 2 - kFirst;
+                        f32x2 k[I1], v[I1];
 #pragma unroll
-                for (int t = 0; t < kMegaMaxTok; ++t)
-                    if (t < k_tok) {
-                        float o = 0.f;
-#pragma unroll
-                        for (int j = 0; j <= t; ++j) o += sp[t * (t + 1) / 2 + j] * vv[j];
-                        const uint16_t cv = f32_to_bf16(o);
-                        xlds[((cc >> 8) * kMegaMaxTok + t) * kXRow + (cc & 255)] = cv;
-                        if (TRACE) {
-                            a.trace_x[tr_x + (size_t)t * a.trace_kmax + col_lo + cc] = cv;
-                            float* ts = a.trace_src + tr_s + (size_t)t * a.trace_smax;
-                            ts[head * D + d] = qv[t];
-                            // heads of one kv group all record the same k and v
-                            ts[a.q_out + kvh * D + d] = kv[t];
-                            ts[a.q_out + a.kv_out + kvh * D + d] = vv[t];
+                        for (int j = 0; j < I1; ++j) {
+                            k[j] = f32x2{from_fixed(kr[j][0], fix_inv), from_fixed(kr[j][1], fix_inv)};
+                            v[j] = f32x2{from_fixed(vr[j][0], fix_inv), from_fixed(vr[j][1], fix_inv)};
                         }
+                        float sc[kScores];
+#pragma unroll
+                        for (int i = I0; i < I1; ++i) {
+                            const f32x2 q = f32x2{from_fixed(qr[i][0], fix_inv), from_fixed(qr[i][1], fix_inv)};
+#pragma unroll
+                            for (int j = 0; j <= i; ++j) sc[i * (i + 1) / 2 - kFirst + j] = q[0] * k[j][0] + q[1] * k[j][1];
+                        }
+                        wave_sums_lane63(sc);
+#pragma unroll
+                        for (int i = I0; i < I1; ++i) {
+                            float e[I1], mx = -3.0e38f, sum = 0.f, o0 = 0.f, o1 = 0.f;
+#pragma unroll
+                            for (int j = 0; j <= i; ++j) {
+                                e[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(sc[i * (i + 1) / 2 - kFirst + j]), 63)) * 0.08838834764831845f;
+                                mx = fmaxf(mx, e[j]);
+                            }
+#pragma unroll
+                            for (int j = 0; j <= i; ++j) {
+                                e[j] = __expf(e[j] - mx);
+                                sum += e[j];
+                            }
+                            const float inv = __builtin_amdgcn_rcpf(sum);
+#pragma unroll
+                            for (int j = 0; j <= i; ++j) {
+                                const float w = e[j] * inv;
+                                o0 += w * v[j][0];
+                                o1 += w * v[j][1];
+                            }
+                            const uint32_t cv = pack_bf16(o0, o1);
+                            *reinterpret_cast<uint32_t*>(dst + i * kXRow) = cv;
+                            if (TRACE && i < k_tok) {
+                                *reinterpret_cast<uint32_t*>(a.trace_x + tr_x + (size_t)i * a.trace_kmax + col_lo + cc) = cv;
+                                float* ts = a.trace_src + tr_s + (size_t)i * a.trace_smax + 2 * lane;
+                                *reinterpret_cast<f32x2*>(ts + head * D) = f32x2{from_fixed(qr[i][0], fix_inv), from_fixed(qr[i][1], fix_inv)};
+                                // heads of one kv group all record the same k and v
+                                *reinterpret_cast<f32x2*>(ts + a.q_out + kvh * D) = k[i];
+                                *reinterpret_cast<f32x2*>(ts + a.q_out + a.kv_out + kvh * D) = v[i];
+                            }
+                        }
+                    };
+                    if (wave & 1) {
+                        if constexpr (N > kHalf) rows(std::integral_constant<int, kHalf>{}, std::integral_constant<int, N>{});
+                    } else {
+                        rows(std::integral_constant<int, 0>{}, std::integral_constant<int, kHalf>{});
                     }
-            }
+                });
         }
         lds_barrier();
         if (tt && tid == 0) tt[2] = __builtin_amdgcn_s_memrealtime();
