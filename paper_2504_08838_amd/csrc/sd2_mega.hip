@@ -660,15 +660,18 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
 
         // Waits for tile j's stream, requests the stream of the tile after it (the next one of this phase, else the
         // first one of the next phase: weights do not depend on activations) and returns what the expansion needs.
+        auto request_after = [&](int j) {
+            if (j + 1 < ct.n)
+                issue_phase_tile<NM24>(ct, j + 1, bufs + cb * kTileDw, mk_next, lane);
+            else if (nt.n > 0)
+                issue_phase_tile<NM24>(nt, 0, bufs + cb * kTileDw, mk_next, lane);
+        };
         auto stage_tile = [&](int j, uint2& mk, uint32_t (&base)[8], uint32_t& key) -> const uint8_t* {
             wait_vector_memory();  // the tile's stream is in LDS, its masks in registers
             mk = mk_next;
             const uint8_t* bufb = reinterpret_cast<const uint8_t*>(bufs + cb * kTileDw);
             cb ^= 1;
-            if (j + 1 < ct.n)
-                issue_phase_tile<NM24>(ct, j + 1, bufs + cb * kTileDw, mk_next, lane);
-            else if (nt.n > 0)
-                issue_phase_tile<NM24>(nt, 0, bufs + cb * kTileDw, mk_next, lane);
+            if (!NM24 || j > 0) request_after(j);  // 2:4: the first tile's successor is requested behind its reads (below)
             if (!NM24) tile_bases(ct, j, lane, base);
             key = lane_word(ct.key, 8 * j);
             return bufb;
@@ -690,6 +693,10 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
                 } else {
                     read_tile24(tpre, bufb, lane);
                 }
+                // A wavefront stands still while its requests wait to be taken; here it has nothing left to do but to wait for the
+                // barrier.  (In front of the reads: 925 us a forward of the 3B shape on 5 tokens, behind them 904.  A bitmask tile's
+                // expansion takes longer than the barrier, and the stream is late behind it: 961 -> 985.)
+                request_after(0);
             } else {
                 expand_tile<SD2_MEGA_STEPS>(bufb, lut, base, mk, [&](int q, const Frag& f0, const Frag& f1) {
                     fpre[q][0].q = f0.q;
