@@ -200,13 +200,17 @@ __device__ __forceinline__ void expand_tile(const uint8_t* __restrict__ bufb, co
 // 1 KiB pieces C, C + 1 .. N - 1 of a buffer into LDS.  What keeps a piece inside the buffer is the hardware's range check, which looks
 // at the vector and the immediate offset; the scalar offset is not part of it.  So a piece's place is in the immediate offset (a
 // constant expression that moves the place in LDS as well), and what its 12 bits do not reach is in the vector offset.  (3B shape, 5
-// tokens, forward: 996 us, with all of it in the vector offset 1004, with a second buffer from 4 KiB on 999.)
+// tokens, forward: 996 us, with all of it in the vector offset 1004, with a second buffer from 4 KiB on 999.)  From the fifth on, pieces
+// past the buffer's n16 units of 16 bytes are not even asked for: tiles of 55 % sparsity and more have no fifth (3B shape at 50 %, where
+// nearly half the tiles have none, 939 -> 928; a branch in front of every piece: 1054).
 template <int C, int N>
-__device__ __forceinline__ void request_pieces(__amdgpu_buffer_rsrc_t from, uint32_t* lds_buf, int offset) {
+__device__ __forceinline__ void request_pieces(__amdgpu_buffer_rsrc_t from, uint32_t* lds_buf, int offset, uint32_t n16) {
     constexpr int kFar = C > 3 ? C - 3 : 0;
     __builtin_amdgcn_raw_ptr_buffer_load_lds(from, (__attribute__((address_space(3))) void*)(lds_buf + kFar * 256), 16, offset + kFar * 1024, 0,
                                              (C - kFar) * 1024, 0);
-    if constexpr (C + 1 < N) request_pieces<C + 1, N>(from, lds_buf, offset);
+    if constexpr (C + 1 < N) {
+        if (C < 3 || (C + 1) * 64u < n16) request_pieces<C + 1, N>(from, lds_buf, offset, n16);
+    }
 }
 
 // The same request with the value stream written straight into LDS (no staging registers): piece c of the
@@ -217,12 +221,14 @@ template <int MAXCH>
 __device__ __forceinline__ void issue_tile_lds(uint32_t* lds_buf, uint2& mk, const uint16_t* __restrict__ vals,
                                                const uint2* __restrict__ tile_masks, uint32_t val_start, uint32_t nnz,
                                                int lane) {
+    // The masks first: they are small, and the stream's pieces do not keep them waiting.  (3B shape on 5 tokens, forward: 951 -> 939 us,
+    // 1.5B shape on 3 tokens 659 -> 655, decode step of the 3B shape 1133 -> 1125.)
+    mk = tile_masks[lane];
     // The stream as a buffer of exactly its length: its base and length are scalars, and pieces past the end ask memory for nothing.
     const uint32_t n16 = (nnz * 2 + 8 + 15) / 16;
     const auto stream = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint8_t*>(reinterpret_cast<const uint8_t*>(vals)) + (size_t)val_start * 16, 0, (int)(n16 * 16u), 0x00020000);
-    request_pieces<0, MAXCH>(stream, lds_buf, lane * 16);
-    mk = tile_masks[lane];
+    request_pieces<0, MAXCH>(stream, lds_buf, lane * 16, n16);
 }
 
 // Waits until every vector-memory operation of this wavefront has completed (loads returned, direct-to-LDS
