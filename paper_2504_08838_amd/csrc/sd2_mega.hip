@@ -323,8 +323,8 @@ __device__ __forceinline__ void read_tile24(Tile24& t, const uint8_t* bufb, int 
 // chunk c (the history is cut into att_chunks equal stretches; the last chunk also takes the call's own tokens
 // 0 .. t, whose keys and values come from this layer's q|k|v result: rotated, rounded to bf16 as the cache holds
 // them; the item of token t stores that token's row in the cache for later calls).  A cache row is read by 16
-// consecutive lanes (16 bytes each), a wavefront reads four consecutive rows, the workgroup 48 per pass, four passes
-// in flight.  Scores stay in registers; the running maximum is agreed across the workgroup per 192 rows (online
+// consecutive lanes (16 bytes each), a wavefront reads four consecutive rows, the workgroup 48 per pass, two passes
+// in flight.  Scores stay in registers; every row of lanes keeps a running maximum of its own (online
 // softmax), sums and weighted values meet in LDS at the end.  Result per head: maximum, sum of exponentials and the
 // unnormalised weighted values, which the workgroups of the next linear combine over the chunks.
 constexpr int kAttSo = 0, kAttMax = kMegaWaves * 4 * 128, kAttSum = kAttMax + kMegaWaves * 8;
@@ -363,6 +363,17 @@ __device__ __forceinline__ void rotated_piece(const int* __restrict__ head, floa
 
 __device__ __forceinline__ u32x4 pack_bf16x8(const float (&f)[8]) {
     return u32x4{pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7])};
+}
+
+// sum over the sixteen lanes of a row, in every one of them
+__device__ __forceinline__ float row_sum(float v) {
+#define SD2_ROW_ADD(ctrl) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true))
+    SD2_ROW_ADD(0x121);  // row_ror:1
+    SD2_ROW_ADD(0x122);  // row_ror:2
+    SD2_ROW_ADD(0x124);  // row_ror:4
+    SD2_ROW_ADD(0x128);  // row_ror:8
+#undef SD2_ROW_ADD
+    return v;
 }
 
 constexpr int kAttUnr = 2;                 // passes of a workgroup's cache loads in flight
@@ -465,12 +476,11 @@ __device__ __forceinline__ void attention_item(KArgs ka, int layer, const AttIte
     }
     for (int base = j_lo; base < j_hi; base += RPI * UNR) {
         if (base != j_lo) attention_loads(ka, layer, it, base, tid, kw, vw);  // the first group is already on its way
-        float sdot[REP][UNR], mx[REP];
-#pragma unroll
-        for (int r = 0; r < REP; ++r) mx[r] = -3.0e38f;
+        float sdot[REP][UNR];
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             const int j = base + u * RPI + slot;
+            asm volatile("" ::: "memory");  // the queries are read again for every pass: kept, they would cost the registers of the sums
             float kf[8];
             bf16x8_unpack((j >= pos0 && j < j_hi) ? own_k[(j - pos0) * 16 + piece] : kw[u], kf);
 #pragma unroll
@@ -479,33 +489,24 @@ __device__ __forceinline__ void attention_item(KArgs ka, int layer, const AttIte
                 float dot = 0.f;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) dot += kf[e] * q0[e] + kf[4 + e] * q1[e];
-                dot += __shfl_xor(dot, 1);
-                dot += __shfl_xor(dot, 2);
-                dot += __shfl_xor(dot, 4);
-                dot += __shfl_xor(dot, 8);
-                sdot[r][u] = j < j_hi ? dot : -3.0e38f;
-                mx[r] = fmaxf(mx[r], sdot[r][u]);
+                sdot[r][u] = row_sum(dot);
             }
         }
-#pragma unroll
-        for (int r = 0; r < REP; ++r) {
-            float m = fmaxf(mx[r], __shfl_xor(mx[r], 16));
-            m = fmaxf(m, __shfl_xor(m, 32));
-            if (lane == 0) smax[wave * 8 + r] = m;
-        }
-        lds_barrier();
+        // the sixteen lanes of a cache row keep a running maximum of their own: rows and wavefronts meet at the end only
 #pragma unroll
         for (int r = 0; r < REP; ++r) {
             float m = M[r];
-#pragma unroll 4
-            for (int ww = 0; ww < kMegaWaves; ++ww) m = fmaxf(m, smax[ww * 8 + r]);
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                if (base + u * RPI + slot >= j_hi) sdot[r][u] = -3.0e38f;
+                m = fmaxf(m, sdot[r][u]);
+            }
             const float f = __expf(M[r] - m);
             M[r] = m;
             L[r] *= f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) acc[r][e] *= f;
         }
-        lds_barrier();
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             const int j = base + u * RPI + slot;
@@ -521,35 +522,44 @@ __device__ __forceinline__ void attention_item(KArgs ka, int layer, const AttIte
         }
     }
     lds_barrier();  // the rows of the call's own tokens and the queries share LDS with the sums below
-    // the sixteen lanes of a row all counted its weight: a wavefront's total is the sum over its lanes / 16
+    // the four rows of a wavefront, each part weighted by its maximum against the common one
 #pragma unroll
     for (int r = 0; r < REP; ++r) {
-        const float l = wave_sum(L[r]) * 0.0625f;
+        float m = fmaxf(M[r], __shfl_xor(M[r], 16));
+        m = fmaxf(m, __shfl_xor(m, 32));
+        const float f = __expf(M[r] - m);
+        float l = L[r] * f;
+        l += __shfl_xor(l, 16);
+        l += __shfl_xor(l, 32);
         if (lane == 0) {
+            smax[wave * 8 + r] = m;
             ssum[wave * 8 + r] = l;
-            if (wave == 0) smax[r] = M[r];  // the same in every thread
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            float v = acc[r][e];
+            float v = acc[r][e] * f;
             v += __shfl_xor(v, 16);
             v += __shfl_xor(v, 32);
             if (lane < 16) so[(wave * 4 + r) * D + 8 * piece + e] = v;
         }
     }
     lds_barrier();
-    for (int idx = tid; idx < rep * D; idx += kMegaThreads) {
+    for (int idx = tid; idx < rep * D; idx += kMegaThreads) {  // and the wavefronts likewise
         const int r = idx >> 7, d = idx & 127;
-        float o = 0.f;
+        float m = smax[r];
+#pragma unroll
+        for (int ww = 1; ww < kMegaWaves; ++ww) m = fmaxf(m, smax[ww * 8 + r]);
+        float o = 0.f, l = 0.f;
 #pragma unroll 4
-        for (int ww = 0; ww < kMegaWaves; ++ww) o += so[(ww * 4 + r) * D + d];
+        for (int ww = 0; ww < kMegaWaves; ++ww) {
+            const float w = __expf(smax[ww * 8 + r] - m);
+            o += w * so[(ww * 4 + r) * D + d];
+            l += w * ssum[ww * 8 + r];
+        }
         float* dst = ka->att_part + ((((size_t)layer * k_tok + t) * n_heads + (size_t)g * rep + r) * C + c) * kMegaAttPartDw;
         astore(dst + 4 + d, o);
         if (d == 0) {
-            float l = 0.f;
-#pragma unroll 4
-            for (int ww = 0; ww < kMegaWaves; ++ww) l += ssum[ww * 8 + r];
-            astore(dst, smax[r]);
+            astore(dst, m);
             astore(dst + 1, l);
         }
     }
@@ -876,38 +886,37 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
             const int head = col_lo / D + hh;
             if (hh * D < n_col) {
                 const int cc = hh * D + d, C = a.att_chunks;
+#pragma unroll 1
+                for (int t = 0; t < k_tok; ++t) {  // one copy of the code: it is cold every time it comes round
+                    const float* pp = a.att_part + (((size_t)layer * k_tok + t) * a.n_heads + head) * C * kMegaAttPartDw;
+                    // eight chunks at a time: their loads are in flight together, the running maximum rescales
+                    float mx = -3.0e38f, num = 0.f, den = 0.f;
+#pragma unroll 1
+                    for (int c0 = 0; c0 < C; c0 += 8) {
+                        float pm[8], pl[8], po[8];
 #pragma unroll
-                for (int t = 0; t < kMegaMaxTok; ++t)
-                    if (t < k_tok) {
-                        const float* pp = a.att_part + (((size_t)layer * k_tok + t) * a.n_heads + head) * C * kMegaAttPartDw;
-                        // eight chunks at a time: their loads are in flight together, the running maximum rescales
-                        float mx = -3.0e38f, num = 0.f, den = 0.f;
-                        for (int c0 = 0; c0 < C; c0 += 8) {
-                            float pm[8], pl[8], po[8];
-#pragma unroll
-                            for (int i = 0; i < 8; ++i) {
-                                const float* q = pp + min(c0 + i, C - 1) * kMegaAttPartDw;
-                                pm[i] = q[0];
-                                pl[i] = q[1];
-                                po[i] = q[4 + d];
-                            }
-                            float gm = mx;
-#pragma unroll
-                            for (int i = 0; i < 8; ++i)
-                                if (c0 + i < C) gm = fmaxf(gm, pm[i]);
-                            const float f = __expf(mx - gm);
-                            num *= f;
-                            den *= f;
-                            mx = gm;
-#pragma unroll
-                            for (int i = 0; i < 8; ++i) {
-                                const float wgt = c0 + i < C ? __expf(pm[i] - mx) : 0.f;
-                                num += wgt * po[i];
-                                den += wgt * pl[i];
-                            }
+                        for (int i = 0; i < 8; ++i) {
+                            const float* q = pp + min(c0 + i, C - 1) * kMegaAttPartDw;
+                            pm[i] = q[0];
+                            pl[i] = q[1];
+                            po[i] = q[4 + d];
                         }
-                        xlds[((cc >> 8) * kMegaMaxTok + t) * kXRow + (cc & 255)] = f32_to_bf16(num * __builtin_amdgcn_rcpf(den));
+                        float gm = mx;
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) gm = fmaxf(gm, pm[i]);  // those past the last repeat it
+                        const float f = __expf(mx - gm);
+                        num *= f;
+                        den *= f;
+                        mx = gm;
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) {
+                            const float wgt = c0 + i < C ? __expf(pm[i] - mx) : 0.f;
+                            num += wgt * po[i];
+                            den += wgt * pl[i];
+                        }
                     }
+                    xlds[((cc >> 8) * kMegaMaxTok + t) * kXRow + (cc & 255)] = f32_to_bf16(num * __builtin_amdgcn_rcpf(den));
+                }
             }
         } else {
             // kind == 1: causal attention among the in-flight tokens.  Two wavefronts take a head, the first its earlier query rows,
