@@ -71,6 +71,11 @@ constexpr uint32_t kWideStaged = 2560;
 // half, 14 bytes of misalignment and 8 of slack), or a block that goes from row order to operand order.
 constexpr int kWideBufDw = (4096 + 32) / 4;
 
+// Where the wavefronts' sums meet when a group's strips are complete.  Behind the buffers no wavefront waits for the others' last
+// reads before it leaves its sums, but that needs room: four strips of four token groups take the buffers' place.
+constexpr size_t wide_sums_bytes(int sg, int tg, int w) { return (size_t)sg * w * tg * 1024; }
+constexpr bool wide_apart(int sg, int tg, int w) { return wide_sums_bytes(sg, tg, w) + (size_t)w * kWideBufDw * 4 <= 159 * 1024; }
+
 // One 64-column step of a bitmask tile between its LDS reads and their use: the windows of its four runs, their selectors and
 // byte offsets.  The reads of a step are issued before the step ahead of it is used, so that a wavefront always has LDS
 // reads in flight while it works (two wavefronts on a SIMD do not hide each other's LDS round trips).
@@ -153,7 +158,9 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
         __syncthreads();
     }
     uint32_t* buf = wide_smem + wave * kWideBufDw;
-    float* red = reinterpret_cast<float*>(wide_smem);  // [strip of the group][wk][TG][256], in place of the buffers
+    // sums of the wavefronts [strip of the group][wk][TG][256]: behind the buffers where both fit, else in their place
+    constexpr bool kApart = wide_apart(SG, TG, W);
+    float* red = reinterpret_cast<float*>(wide_smem) + (kApart ? W * kWideBufDw : 0);
 
     const int split = (int)blockIdx.x % a.n_split, sblk = (int)blockIdx.x / a.n_split;
     const int n_pass = a.n_pass, wk = a.wk, ws = W / wk;
@@ -297,7 +304,7 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
     // The strips of a group are complete: strip o of the group, wavefront kw of the contraction, token group tg has its block in
     // red[((o wk + kw) TG + tg) 256 ..]; the threads share the adding, four rows of a token each.
     auto finish = [&](int grp) SD2_INLINE {
-        barrier();
+        if (!kApart) barrier();  // the slots take the place of the buffers, which some wavefront may still be reading
 #pragma unroll
         for (int i = 0; i < SG; ++i)
 #pragma unroll
@@ -308,6 +315,14 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
         auto sum = [&](int o, int tg) SD2_INLINE {
             const float* p = red + ((size_t)o * wk * TG + tg) * 256 + lane * 4;
             f32x4 v = *reinterpret_cast<const f32x4*>(p) + *reinterpret_cast<const f32x4*>(p + TG * 256);
+            if (W == 8 && wk == W) {  // all reads in flight at once (twelve would not leave the loop its registers)
+                f32x4 q[W];
+#pragma unroll
+                for (int k = 2; k < W; ++k) q[k] = *reinterpret_cast<const f32x4*>(p + k * (TG * 256));
+#pragma unroll
+                for (int k = 2; k < W; ++k) v += q[k];
+                return v;
+            }
             for (int k = 2; k < wk; k += 2) {
                 v += *reinterpret_cast<const f32x4*>(p + (size_t)k * (TG * 256));
                 v += *reinterpret_cast<const f32x4*>(p + (size_t)(k + 1) * (TG * 256));
@@ -342,7 +357,7 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
                 }
             }
         }
-        barrier();
+        if (grp + 1 < n_grp) barrier();  // the slots are free again
     };
 
     Stage st[SG];  // each is requested for the next round as soon as it is used: a round's worth is in flight
@@ -484,8 +499,10 @@ static int wide_cu_count() {
 
 // How a wide linear is cut.  The model behind the choice is a fit to this part, in microseconds: a strip costs a pass the
 // expansion of its half tile (two or three wavefronts on a SIMD take turns), fetching a unit's activations is paid once a
-// pass and grows with the tokens, completing a group takes 1.5, and a partial result its bytes to memory and back plus,
-// where nothing adds it anyway, a launch.  Twelve wavefronts where their 168 registers hold the sums of a group.
+// pass and grows with the tokens, completing a group takes 1.5, and a partial result its bytes to memory and back plus a
+// launch where nothing adds it anyway, and where the norm does, from nine on, 1.5 for a second trip of its loads (1.5B shape on 64
+// tokens, down: five partial results and two passes in place of nine and one, a layer 67.8 -> 66.5 us).  Twelve wavefronts where
+// their 168 registers hold the sums of a group.
 bool wide_plan(int n_out, int k_in, int n_strips, int k_tok, bool gated, int max_split, bool free_add, WidePlan* out) {
     const int tg = (k_tok + 15) / 16;
     if (tg < 2 || tg > 4 || (gated && n_out % 32) || k_in > (1 << 20) || (int64_t)n_out * k_in > (1ll << 31) - (1 << 23))
@@ -499,7 +516,7 @@ bool wide_plan(int n_out, int k_in, int n_strips, int k_tok, bool gated, int max
         const int blocks = std::max(1, std::min(n_strips / step, cus / split));
         per_wg[split] = step * ((n_strips / step + blocks - 1) / blocks);
         units[split] = (n_units + split - 1) / split;
-        extra[split] = split > 1 ? (double)split * k_tok * n_out * 8.0 / 4e6 + (free_add ? 0.0 : 3.0) : 0.0;
+        extra[split] = split > 1 ? (double)split * k_tok * n_out * 8.0 / 4e6 + (!free_add ? 3.0 : split > 8 ? 1.5 : 0.0) : 0.0;
     }
     double best = -1.0;
     for (int waves = 8; waves <= 12; waves += 4)
@@ -536,7 +553,8 @@ bool wide_plan(int n_out, int k_in, int n_strips, int k_tok, bool gated, int max
 
 template <int FMT, int TG, int SG, int W>
 static hipError_t launch_wide_t(const WideArgs& a, const WidePlan& p, hipStream_t s) {
-    constexpr size_t lds = (size_t)std::max(W * kWideBufDw * 4, SG * W * TG * 1024);
+    constexpr size_t buffers = (size_t)W * kWideBufDw * 4, sums = wide_sums_bytes(SG, TG, W);
+    constexpr size_t lds = wide_apart(SG, TG, W) ? buffers + sums : std::max(buffers, sums);
     static std::atomic<bool> raised{false};
     if (!raised.load(std::memory_order_acquire)) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&wide_linear_kernel<FMT, TG, SG, W>),
