@@ -348,19 +348,24 @@ __global__ __launch_bounds__(64 * WAVES) void sparse_strip_kernel(const DirEnt* 
         return;
     }
 
+    static_assert(SPW <= 2, "the slab after a tile's is the wavefront's other one");
     // Operand B in registers: always for one token group; for two groups when the wavefront owns a single slab (its
     // activation columns then never change).  Otherwise B is fetched per 64-column step (below).
     constexpr bool kBRegs = TG == 1 || (TG == 2 && SPW == 1);
     constexpr int kBG = kBRegs ? TG : 1;
     Frag b[kBG][4][2];
     auto load_b = [&](int slab) {
+        int row = n;
+        if (SPW > 1) asm volatile("" : "+v"(row));  // made again for every slab: kept, the rows' addresses would spill
         const int col0 = slab * 256 + 16 * g;
 #pragma unroll
         for (int tg = 0; tg < kBG; ++tg)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) load_row16(x, n + 16 * tg, k_tok, col0 + 64 * q, k_in, b[tg][q][0], b[tg][q][1]);
+            for (int q = 0; q < 4; ++q) load_row16(x, row + 16 * tg, k_tok, col0 + 64 * q, k_in, b[tg][q][0], b[tg][q][1]);
     };
-    if (kBRegs && SPW == 1) load_b(wave);
+    // (the first slab's columns are requested in front of the streams; with two slabs, those of the next tile as soon as a tile is
+    // through the matrix cores)
+    if (kBRegs) load_b(wave);
 
     // two tiles' streams are in flight in registers while a third is expanded
     u32x4 st[2][MAXCH];
@@ -382,7 +387,6 @@ __global__ __launch_bounds__(64 * WAVES) void sparse_strip_kernel(const DirEnt* 
         const uint2 mk = mkn[slot];
         const DirEnt de = den[slot];
         if (kBRegs) {
-            if (SPW > 1) load_b(wave + WAVES * j);
             request(slot, f + 2);
             expand_tile<SD2_LINEAR_STEPS>(reinterpret_cast<const uint8_t*>(buf), lut, de.base, mk,
                                           [&](int q, const Frag& f0, const Frag& f1) {
@@ -392,6 +396,7 @@ __global__ __launch_bounds__(64 * WAVES) void sparse_strip_kernel(const DirEnt* 
                                                   acc[tg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f1.v, b[tg][q][1].v, acc[tg], 0, 0, 0);
                                               }
                                           });
+            if (SPW > 1 && f + 1 < n_flat) load_b(wave + WAVES * (n_mine - 1 - j));  // (at most two slabs: the other one)
         } else {
             // operand B of step q for every token group, requested one step ahead of its use
             const int col0 = (wave + WAVES * j) * 256 + 16 * g;
