@@ -314,6 +314,16 @@ struct StackGlue {
         if (!fused || next->kind != SD2_KIND_DENSE || !dense_stream_norm_ok(next->info.k_in, k_tok)) return false;
         return !gated || (gated_ok(next, k_tok, gated_cut) && dense_gated_ok(next));
     }
+    // h += W attention(q|k|v): the linear behind the in-flight attention attends by itself
+    bool attends_itself(const sd2_matrix_t* o, const sd2_model_shape_t& sh, int qkv_splits) const {
+        return fused && o->kind == SD2_KIND_DENSE && sh.head_dim == 128 && qkv_splits == 1 &&
+               dense_stream_attend_ok(sh.n_heads, o->info.n_out, k_tok);
+    }
+    hipError_t attend(const sd2_matrix_t* o, const sd2_model_shape_t& sh, uint16_t* act_out) const {
+        const hipError_t e = launch_dense_stream_attend_add(mat_args(o).w, part, sh.n_heads, sh.n_kv, o->info.n_out, k_tok, h, s);
+        if (e != hipSuccess || !act_out) return e;
+        return launch_residual_rmsnorm(h, nullptr, part, 0, k_tok, hidden, act_out, ssq, s);
+    }
     // h += the linear's results; act_out: where the norm of the sum goes, null where nobody wants it
     hipError_t close(const sd2_matrix_t* m, const uint16_t* x, LinearCut& cut, uint16_t* act_out) const {
         const bool added = fused && m->kind == SD2_KIND_DENSE && dense_stream_add_ok(m->info.n_out, m->info.k_in, k_tok);
@@ -722,11 +732,15 @@ static int forward_impl(const sd2_model_t* md, const uint16_t* h_in, int32_t k_t
         } else {
             SD2_TRY(run_linear(qkv, act, k_tok, part, s, &cuts.lin[0]));
         }
-        SD2_TRY(launch_inflight_attention(part, n_splits(qkv, k_tok, cuts.lin[0]), k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv,
-                                          sh.head_dim, act, s));
-        SD2_TRY(record(4 * l + 1, nullptr, part, n_splits(qkv, k_tok, cuts.lin[0]), sh.q_out + 2 * sh.kv_out, sh.q_out));
+        const int qkv_splits = n_splits(qkv, k_tok, cuts.lin[0]);
         self = glue.norms_itself(gu, true, cuts.gated);
-        SD2_TRY(glue.close(o, act, cuts.lin[1], self ? nullptr : act));
+        if (glue.attends_itself(o, sh, qkv_splits)) {
+            SD2_TRY(glue.attend(o, sh, self ? nullptr : act));
+        } else {
+            SD2_TRY(launch_inflight_attention(part, qkv_splits, k_tok, sh.q_out, sh.kv_out, sh.n_heads, sh.n_kv, sh.head_dim, act, s));
+            SD2_TRY(record(4 * l + 1, nullptr, part, qkv_splits, sh.q_out + 2 * sh.kv_out, sh.q_out));
+            SD2_TRY(glue.close(o, act, cuts.lin[1], self ? nullptr : act));
+        }
         SD2_TRY(record(4 * l + 2, h, nullptr, 0, sh.hidden, sh.hidden));
         if (self) {
             SD2_TRY(launch_dense_stream_gated(mat_args(gu).w, nullptr, h, gu->info.n_out, gu->info.k_in, k_tok, act, s));

@@ -75,6 +75,86 @@ __device__ __forceinline__ void wave_excl_scans(uint32_t (&x)[N]) {
 #undef SD2_SCAN_STAGE
 }
 
+// Sums over the 64 lanes of N values at once, stage by stage: the N cross-lane adds of a stage are independent, so they issue back to
+// back and fill the wait states that a chain of dependent cross-lane operations would spend idle.  Result in lane 63.
+template <int N>
+__device__ __forceinline__ void wave_sums_lane63(float (&v)[N]) {
+#define SD2_DPP_STAGE(ctrl, rmask) \
+    _Pragma("unroll") for (int i = 0; i < N; ++i) \
+        v[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[i]), ctrl, rmask, 0xf, true))
+    SD2_DPP_STAGE(0x111, 0xf);  // row_shr:1
+    SD2_DPP_STAGE(0x112, 0xf);  // row_shr:2
+    SD2_DPP_STAGE(0x114, 0xf);  // row_shr:4
+    SD2_DPP_STAGE(0x118, 0xf);  // row_shr:8
+    SD2_DPP_STAGE(0x142, 0xa);  // row_bcast:15
+    SD2_DPP_STAGE(0x143, 0xc);  // row_bcast:31
+#undef SD2_DPP_STAGE
+}
+
+// ---- causal softmax attention of one head of 128 dimensions among at most N tokens, by one wavefront: a lane holds two dimensions
+// of every token (slots past the last token repeat it), scores are summed across the lanes, and the softmax is the same arithmetic in
+// every lane, so that nothing passes between lanes or through LDS but the sums.
+template <int N>
+struct FewTokens {
+    f32x2 q[N], k[N], v[N];
+};
+
+// qkv: final values [k_tok][nqkv]; the columns are those of the head's query and of its group's key and value
+template <int N>
+__device__ __forceinline__ void load_few(FewTokens<N>& a, const float* __restrict__ qkv, int nqkv, int q_col, int k_col, int v_col, int k_tok,
+                                         int lane) {
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+        const float* row = qkv + (size_t)min(t, k_tok - 1) * nqkv + 2 * lane;
+        a.q[t] = *reinterpret_cast<const f32x2*>(row + q_col);
+        a.k[t] = *reinterpret_cast<const f32x2*>(row + k_col);
+        a.v[t] = *reinterpret_cast<const f32x2*>(row + v_col);
+    }
+}
+
+// e^x for x <= 0, an ulp or less off: the hardware's 2^t at t = x log2(e), and to first order what the product t lost.
+__device__ __forceinline__ float exp_down(float x) {
+    const float t = x * 1.44269504f;
+    const float lost = __builtin_fmaf(x, 1.92596303e-8f, __builtin_fmaf(x, 1.44269504f, -t));
+    const float e = __builtin_amdgcn_exp2f(t);
+    return e == 0.f ? e : __builtin_fmaf(e * lost, 0.693147182f, e);  // (x may be -infinity, whose product loses NaN)
+}
+
+// out(t, x, y): the lane's two dimensions of token t's context.  The order of the sums and what is fused are written out: a launch of
+// its own and a linear's prologue give the same bits.
+template <int N, typename F>
+__device__ __forceinline__ void attend_few(const FewTokens<N>& a, F&& out) {
+    float s[N * (N + 1) / 2];
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            float first = a.q[i][0] * a.k[j][0];
+            asm("" : "+v"(first));
+            s[i * (i + 1) / 2 + j] = __builtin_fmaf(a.q[i][1], a.k[j][1], first);
+        }
+    wave_sums_lane63(s);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        float e[N], mx = -3.0e38f, sum = 0.f, x = 0.f, y = 0.f;
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            e[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(s[i * (i + 1) / 2 + j]), 63)) * 0.08838834764831845f;  // 1 / sqrt(128)
+            asm("" : "+v"(e[j]));
+            mx = fmaxf(mx, e[j]);
+        }
+#pragma unroll
+        for (int j = 0; j <= i; ++j) {
+            e[j] = exp_down(e[j] - mx);
+            sum += e[j];
+            x = __builtin_fmaf(e[j], a.v[j][0], x);
+            y = __builtin_fmaf(e[j], a.v[j][1], y);
+        }
+        const float r = __builtin_amdgcn_rcpf(sum), inv = __builtin_fmaf(__builtin_fmaf(-sum, r, 1.0f), r, r);  // 1 <= sum <= N
+        out(i, x * inv, y * inv);
+    }
+}
+
 // Byte-permute selectors that spread up to four compacted bf16 values over four columns.
 // Entry [nib] = {selector for columns 0,1 ; selector for columns 2,3}; 0x0c yields a zero byte.
 __device__ __forceinline__ uint2 make_expand_selector(uint32_t nib) {

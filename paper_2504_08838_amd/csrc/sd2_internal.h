@@ -211,5 +211,18 @@ hipError_t launch_dense_stream_gated(const uint16_t* w, const uint16_t* x, const
 // h += W x, up to 4096 rows (a strip per workgroup)
 inline bool dense_stream_add_ok(int n_out, int k_in, int k_tok) { return dense_stream_ok(k_in) && n_out <= 4096 && k_tok <= 16; }
 hipError_t launch_dense_stream_add(const uint16_t* w, const uint16_t* x, int n_out, int k_in, int k_tok, float* h, hipStream_t s);
+// token slots that the attention of one head by one wavefront is made for
+constexpr int few_slots(int k_tok) { return k_tok <= 2 ? 2 : k_tok <= 5 ? 5 : 8; }
+// h += W attention(q|k|v), q|k|v final values [k_tok][(n_heads + 2 n_kv) 128], heads of 128 dimensions.  Every workgroup attends for all
+// heads, a wavefront for one in eight, and its time goes with heads times scores: where that is at most 30 a wavefront it costs
+// less than a launch.  28 dense layers, hidden 1536, 12 heads, inside / as a launch of its own: one token 923 / 975 us, five (30
+// scores a wavefront) 1057 / 1064, eight (72) 1243 / 1160; hidden 512, 4 heads, five tokens (15) 456 / 539; 8 layers, hidden 3072, 24
+// heads, five tokens (45) 437 / 429.
+inline bool dense_stream_attend_ok(int n_heads, int n_out, int k_tok) {
+    const int heads = (n_heads + 7) / 8, slots = few_slots(k_tok);
+    return k_tok <= 5 && heads <= 4 && heads * slots * (slots + 1) / 2 <= 30 && dense_stream_add_ok(n_out, 128 * n_heads, k_tok);
+}
+hipError_t launch_dense_stream_attend_add(const uint16_t* w, const float* qkv, int n_heads, int n_kv, int n_out, int k_tok, float* h,
+                                          hipStream_t s);
 
 }  // namespace sd2

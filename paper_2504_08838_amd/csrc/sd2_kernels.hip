@@ -1166,11 +1166,31 @@ __global__ __launch_bounds__(128) void inflight_attention_kernel(const float* __
     }
 }
 
+// The same for heads of 128 dimensions, up to 8 tokens and final q|k|v values: a wavefront per head (twelve heads on 5 slots 3.2 us,
+// the kernel above 6.2).
+template <int N>
+__global__ __launch_bounds__(64) void inflight_attention_few_kernel(const float* __restrict__ qkv, int k_tok, int q_out, int kv_out, int rep,
+                                                                    uint16_t* __restrict__ ctx) {
+    const int head = blockIdx.x, lane = threadIdx.x;
+    FewTokens<N> a;
+    load_few(a, qkv, q_out + 2 * kv_out, head * 128, q_out + head / rep * 128, q_out + kv_out + head / rep * 128, k_tok, lane);
+    attend_few(a, [&](int t, float x, float y) {
+        if (t < k_tok) *reinterpret_cast<uint32_t*>(ctx + (size_t)t * q_out + head * 128 + 2 * lane) = pack_bf16(x, y);
+    });
+}
+
 hipError_t launch_inflight_attention(const float* part, int n_splits, int k_tok, int q_out, int kv_out, int n_heads,
                                      int n_kv, int head_dim, uint16_t* ctx, hipStream_t s) {
     if (k_tok < 1 || k_tok > 64 || head_dim < 8 || head_dim > 256 || head_dim % 8) return hipErrorInvalidValue;
     // stacks of four layers on 9 to 16 tokens: 1 to 4 % faster than with the kernel below; eight and fewer tokens keep that kernel
     if (head_dim == 128 && k_tok > 8) return launch_inflight_attention_wide(part, n_splits, k_tok, q_out, kv_out, n_heads, n_kv, ctx, s);
+    if (head_dim == 128 && n_splits == 1) {
+        const auto fn = few_slots(k_tok) == 2   ? inflight_attention_few_kernel<2>
+                        : few_slots(k_tok) == 5 ? inflight_attention_few_kernel<5>
+                                                : inflight_attention_few_kernel<8>;
+        hipLaunchKernelGGL(fn, dim3((unsigned)n_heads), dim3(64), 0, s, part, k_tok, q_out, kv_out, n_heads / n_kv, ctx);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(inflight_attention_kernel, dim3((unsigned)n_heads, (unsigned)k_tok), dim3(128), 0, s, part, n_splits, k_tok,
                        q_out, kv_out, n_heads, n_kv, head_dim, ctx);
     return hipGetLastError();

@@ -58,7 +58,11 @@ __device__ __forceinline__ void lm_better(float& a, int32_t& ia, float b, int32_
 // it reads twice the bytes of `x` from L2, and a launch with its gap (about 4 us) goes.
 // Dense stacks of 8 layers, us, every step a launch of its own and the activations behind the stream, then now: hidden 3072 on 5 tokens
 // 498 -> 436, on 16 tokens 574 -> 519; hidden 4096 on 5 tokens 612 -> 572; MLP 2048 x 8192 on 5 tokens 28.1 -> 24.2.
-enum { kLmHead, kLmPlain, kLmGated, kLmAdd };
+//   kAtt    as kAdd, and the activations are the context of the attention among the in-flight tokens: column chunk c is head c, so a
+//           wavefront attends for the heads whose columns it multiplies, from q|k|v in `h`, and a launch goes.  Made for 2 or 5 token
+//           slots; with more scores than that a launch of its own is faster (dense_stream_attend_ok).
+enum { kLmHead, kLmPlain, kLmGated, kLmAdd, kLmAtt2, kLmAtt5 };
+constexpr int lm_att_slots(int mode) { return mode == kLmAtt2 ? 2 : mode == kLmAtt5 ? 5 : 0; }
 
 // As a linear TG = 2 takes up to 32 tokens in one pass (two sets of B operands in registers, two accumulators per strip; the partial
 // strips then share one LDS buffer and need a second barrier per strip).
@@ -67,14 +71,15 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
                                                                 const float* __restrict__ h,
                                                                 const uint16_t* __restrict__ x_all, int vocab, int hidden,
                                                                 int k_tok_all, int n_strips, LmCand* __restrict__ part,
-                                                                float* __restrict__ out_all) {
+                                                                float* __restrict__ out_all, int rep) {
     extern __shared__ __attribute__((aligned(16))) uint32_t lm_smem[];
-    constexpr bool HEAD = MODE == kLmHead;
+    constexpr bool HEAD = MODE == kLmHead, ADD = MODE >= kLmAdd;
+    constexpr int kSlots = lm_att_slots(MODE);
     // As a linear with more tokens than one pass takes, the grid's second dimension numbers the passes of 16 TG
     // tokens (the matrix is streamed once per pass); the head itself is launched with one pass.
     const int pass = HEAD ? 0 : (int)blockIdx.y;
     const int n_cols_out = MODE == kLmGated ? vocab / 2 : vocab;
-    const uint16_t* __restrict__ x = (HEAD || NORM) ? x_all : x_all + (size_t)pass * (16 * TG) * hidden;
+    const uint16_t* __restrict__ x = (HEAD || NORM || kSlots) ? x_all : x_all + (size_t)pass * (16 * TG) * hidden;
     float* __restrict__ logits = (HEAD || MODE == kLmGated) ? out_all : out_all + (size_t)pass * (16 * TG) * vocab;
     uint16_t* __restrict__ gated = reinterpret_cast<uint16_t*>(out_all) + (size_t)pass * (16 * TG) * n_cols_out;
     const int k_tok = HEAD ? k_tok_all : min(16 * TG, k_tok_all - pass * (16 * TG));
@@ -202,12 +207,21 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
         // idle until then, and nothing was requested meanwhile.  A barrier that puts every wavefront's in front of anybody's stream
         // costs more than it gives here: 55 us a layer against 52.5 (hidden 3072, 5 tokens), the stream starts later.
         f32x4 hr[NORM ? CPW : 1][4][2];
-        if (MODE == kLmAdd) {
+        FewTokens<kSlots ? kSlots : 1> heads[kSlots ? CPW : 1];
+        if (ADD) {
             const int row = (int)blockIdx.x * 16 + red_row;
             if (wave < 4 && row < vocab && red_tok < k_tok) residual = logits[(size_t)red_tok * vocab + row];
         }
+        if constexpr (kSlots > 0) {
+            const int kv_out = n_colchunks / rep * kLmChunkCols;
 #pragma unroll
-        for (int cc = 0; cc < CPW; ++cc) {
+            for (int cc = 0; cc < CPW; ++cc) {
+                const int head = min(wave + kLmWaves * cc, n_colchunks - 1), at = hidden + head / rep * kLmChunkCols;
+                load_few(heads[cc], h, hidden + 2 * kv_out, head * kLmChunkCols, at, at + kv_out, k_tok, lane);
+            }
+        }
+#pragma unroll
+        for (int cc = 0; cc < (kSlots ? 0 : CPW); ++cc) {
             const size_t col = (size_t)min(wave + kLmWaves * cc, n_colchunks - 1) * kLmChunkCols + g * 8;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -336,13 +350,28 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
                         b[0][cc][q].u[2 * e + 1] = pack_bf16(v[2] * inv, v[3] * inv);
                     }
         }
+        if constexpr (kSlots > 0) {
+            // The context goes from two dimensions a lane to operand B through the wavefront's own places in the two buffers of partial
+            // strips (tokens 0-3, 4-7): where it leaves its strips later, and nobody else does.
+            uint32_t* turn = reinterpret_cast<uint32_t*>(red) + wave * 256;
+            auto place = [&](int t) { return turn + (t >> 2) * kLmRedDw + (t & 3) * 64; };
+            static_assert(kSlots <= 8, "two buffers of four tokens");
+#pragma unroll
+            for (int cc = 0; cc < CPW; ++cc) {
+                attend_few(heads[cc], [&](int t, float x0, float x1) { place(t)[lane] = pack_bf16(x0, x1); });
+                asm volatile("" ::: "memory");
+#pragma unroll
+                for (int q = 0; q < 4; ++q) b[0][cc][q].q = *reinterpret_cast<const u32x4*>(place(tok) + q * 16 + g * 4);
+                asm volatile("" ::: "memory");
+            }
+        }
         // waited for here, where what is behind them is known: in the loop the compiler would wait for the stream, too
 #pragma unroll
         for (int tg = 0; tg < TG; ++tg)
 #pragma unroll
             for (int cc = 0; cc < CPW; ++cc)
                 asm volatile("" : "+v"(b[tg][cc][0].q), "+v"(b[tg][cc][1].q), "+v"(b[tg][cc][2].q), "+v"(b[tg][cc][3].q));
-        if (MODE == kLmAdd) asm volatile("" : "+v"(residual));
+        if (ADD) asm volatile("" : "+v"(residual));
         if (!NORM) fill_ring();
     }
 
@@ -402,7 +431,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
                         best = v;
                         best_i = row;
                     }
-                    if (!HEAD || logits) logits[(size_t)rt * vocab + row] = MODE == kLmAdd ? residual + v : v;
+                    if (!HEAD || logits) logits[(size_t)rt * vocab + row] = ADD ? residual + v : v;
                 }
             }
         }
@@ -470,7 +499,7 @@ static int lm_workgroups(int n_strips, bool head) {
 
 template <int CPW, int MODE, bool NORM, int TG = 1>
 static hipError_t launch_lm_t(const uint16_t* w, const float* h, const uint16_t* x, int vocab, int hidden, int k_tok, LmCand* part, float* out,
-                              hipStream_t s) {
+                              hipStream_t s, int rep = 1) {
     static std::atomic<bool> attr_set{false};  // more than the default 64 KiB of dynamic LDS needs opting in, once per kernel
     const size_t lds = (size_t)kLmLdsDw * 4;
     if (!attr_set.load(std::memory_order_acquire)) {
@@ -480,10 +509,10 @@ static hipError_t launch_lm_t(const uint16_t* w, const float* h, const uint16_t*
         attr_set.store(true, std::memory_order_release);
     }
     const int n_strips = (vocab + 15) / 16;
-    const int n_wg = MODE == kLmAdd ? n_strips : lm_workgroups(n_strips, MODE == kLmHead);
+    const int n_wg = MODE >= kLmAdd ? n_strips : lm_workgroups(n_strips, MODE == kLmHead);
     const int passes = MODE == kLmHead ? 1 : (k_tok + 16 * TG - 1) / (16 * TG);
     hipLaunchKernelGGL((lm_head_kernel<CPW, MODE, NORM, TG>), dim3((unsigned)n_wg, (unsigned)passes), dim3(64 * kLmWaves), lds, s, w, h, x, vocab,
-                       hidden, k_tok, n_strips, part, out);
+                       hidden, k_tok, n_strips, part, out, rep);
     return hipGetLastError();
 }
 
@@ -553,6 +582,23 @@ hipError_t launch_dense_stream_gated(const uint16_t* w, const uint16_t* x, const
 hipError_t launch_dense_stream_add(const uint16_t* w, const uint16_t* x, int n_out, int k_in, int k_tok, float* h, hipStream_t s) {
     if (k_tok < 1 || !dense_stream_add_ok(n_out, k_in, k_tok)) return hipErrorInvalidValue;
     return launch_lm_cpw<kLmAdd, false>(w, nullptr, x, n_out, k_in, k_tok, nullptr, h, s);
+}
+
+hipError_t launch_dense_stream_attend_add(const uint16_t* w, const float* qkv, int n_heads, int n_kv, int n_out, int k_tok, float* h,
+                                          hipStream_t s) {
+    const int k_in = n_heads * 128, rep = n_heads / n_kv;
+    if (k_tok < 1 || !dense_stream_attend_ok(n_heads, n_out, k_tok)) return hipErrorInvalidValue;
+#define SD2_ATT_CASE(C, M) \
+    if ((n_heads + kLmWaves - 1) / kLmWaves == C && lm_att_slots(M) == few_slots(k_tok)) \
+        return launch_lm_t<C, M, false>(w, qkv, nullptr, n_out, k_in, k_tok, nullptr, h, s, rep)
+    SD2_ATT_CASE(1, kLmAtt2);
+    SD2_ATT_CASE(2, kLmAtt2);
+    SD2_ATT_CASE(3, kLmAtt2);
+    SD2_ATT_CASE(4, kLmAtt2);
+    SD2_ATT_CASE(1, kLmAtt5);
+    SD2_ATT_CASE(2, kLmAtt5);
+#undef SD2_ATT_CASE
+    return hipErrorInvalidValue;
 }
 
 }  // namespace sd2

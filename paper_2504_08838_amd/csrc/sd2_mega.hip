@@ -86,22 +86,6 @@ __device__ __forceinline__ float wave_sum(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-// The same for N values at once, stage by stage: the N cross-lane adds of a stage are independent, so they issue back to
-// back and fill the wait states that a chain of dependent cross-lane operations would spend idle.  Result in lane 63.
-template <int N>
-__device__ __forceinline__ void wave_sums_lane63(float (&v)[N]) {
-#define SD2_DPP_STAGE(ctrl, rmask) \
-    _Pragma("unroll") for (int i = 0; i < N; ++i) \
-        v[i] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[i]), ctrl, rmask, 0xf, true))
-    SD2_DPP_STAGE(0x111, 0xf);  // row_shr:1
-    SD2_DPP_STAGE(0x112, 0xf);  // row_shr:2
-    SD2_DPP_STAGE(0x114, 0xf);  // row_shr:4
-    SD2_DPP_STAGE(0x118, 0xf);  // row_shr:8
-    SD2_DPP_STAGE(0x142, 0xa);  // row_bcast:15
-    SD2_DPP_STAGE(0x143, 0xc);  // row_bcast:31
-#undef SD2_DPP_STAGE
-}
-
 // Calls f with the number of token slots that the code is made for, the smallest of 1 2 3 4 5 8 that holds the tokens: straight-line
 // work on all slots (those past the last token repeat it; nobody reads their results) takes less time than a branch per token, which
 // is paid by every wavefront of every workgroup in every phase, and no token's loads wait for those of the one before it.  With this

@@ -176,3 +176,18 @@ def test_infinite_weight_with_five_and_seven_chunks(k):
 
 def _bits(a):
     return wl.f32_to_bf16_bits(a)
+
+
+@pytest.mark.parametrize("heads,kv", [(1, 1), (8, 2), (9, 3), (16, 4), (17, 17), (25, 5), (32, 4), (33, 11)])
+@pytest.mark.parametrize("k_tok", [1, 2, 3, 5, 6, 8, 9])
+def test_attention_inside_the_output_projection(heads, kv, k_tok):
+    """One to four heads a wavefront and wavefronts without one, every count of token slots, heads and tokens on either side of where the
+    linear attends by itself: the traced forward's attention is a launch of its own and gives the same bits."""
+    import gpu_util as gu
+    shape = _shape(256, heads, kv, 128, layers=1)
+    get, model = _model(shape, 97)
+    h = wl.gen_x(97, 0, "q", k_tok, shape.hidden)
+    out = gu.run_forward(model, h, shape.hidden)
+    assert ol.rel_l2(out, os_.drafter_forward(shape, get, h)) <= TOL
+    apart, _, _ = gu.run_forward_trace(model, h, shape)
+    assert np.array_equal(out, apart)
