@@ -64,9 +64,11 @@ __device__ __forceinline__ void lm_better(float& a, int32_t& ia, float b, int32_
 enum { kLmHead, kLmPlain, kLmGated, kLmAdd, kLmAtt2, kLmAtt5 };
 constexpr int lm_att_slots(int mode) { return mode == kLmAtt2 ? 2 : mode == kLmAtt5 ? 5 : 0; }
 
+// HALF: a strip is eight rows (kAdd and kAtt, one strip a workgroup): a chunk is two requests instead of four, the matrix instructions'
+// other eight rows are whatever the ring holds and nobody reads their results.  Twice the compute units stream.
 // As a linear TG = 2 takes up to 32 tokens in one pass (two sets of B operands in registers, two accumulators per strip; the partial
 // strips then share one LDS buffer and need a second barrier per strip).
-template <int CPW, int MODE, bool NORM, int TG>
+template <int CPW, int MODE, bool NORM, int TG, bool HALF>
 __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* __restrict__ w,
                                                                 const float* __restrict__ h,
                                                                 const uint16_t* __restrict__ x_all, int vocab, int hidden,
@@ -75,6 +77,8 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
     extern __shared__ __attribute__((aligned(16))) uint32_t lm_smem[];
     constexpr bool HEAD = MODE == kLmHead, ADD = MODE >= kLmAdd;
     constexpr int kSlots = lm_att_slots(MODE);
+    constexpr int kLoads = HALF ? 2 : 4, kRows = MODE == kLmGated || HALF ? 8 : 16;  // requests of a chunk; rows of a strip (of each half)
+    static_assert(!HALF || (ADD && TG == 1 && !NORM), "eight rows a strip where results are added to the residual");
     // As a linear with more tokens than one pass takes, the grid's second dimension numbers the passes of 16 TG
     // tokens (the matrix is streamed once per pass); the head itself is launched with one pass.
     const int pass = HEAD ? 0 : (int)blockIdx.y;
@@ -99,7 +103,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
     for (int cc = 0; cc < CPW; ++cc) n_cc += wave + kLmWaves * cc < n_colchunks ? 1 : 0;
     const int n_chunks = my_strips * n_cc;
 
-    static_assert(kLmRing == 4, "the waits below count four loads per chunk and three chunks behind the current one");
+    static_assert(kLmRing == 4, "the waits below count three chunks behind the current one");
     // The wavefront's chunks, in order: its n_cc column chunks of strip blockIdx.x, then of strip blockIdx.x + gridDim.x, ...
     // Instruction i of a chunk fills LDS rows 4i..4i+3 (16 lanes per row); lane l brings the 16-byte piece
     // (l & 15) ^ row of its row, so piece j of row r sits at LDS piece position j ^ r.
@@ -119,8 +123,8 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
         // a request for nothing must not lead to the slot that the next chunk takes while it is in flight
         uint32_t* dst = exists ? ring + (issued & (kLmRing - 1)) * kLmChunkDw : lm_smem + kLmLdsDw - kLmNowhereDw;
         const int step = exists ? 256 : 0;
-        const int row = ((int)blockIdx.x + r_strip * (int)gridDim.x) * (MODE == kLmGated ? 8 : 16);
-        const int rows = MODE == kLmGated ? 8 : min(16, vocab - row);
+        const int row = ((int)blockIdx.x + r_strip * (int)gridDim.x) * kRows;
+        const int rows = MODE == kLmGated ? 8 : min(kRows, vocab - row);
         const int bytes = exists ? ((rows - 1) * hidden + kLmChunkCols) * 2 : 0;
         const uint16_t* src = w + (size_t)row * hidden + (wave + kLmWaves * r_cc) * kLmChunkCols;
         const auto rows_lo = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src), 0, bytes, 0x00020000);
@@ -128,7 +132,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
                                  ? __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src + (size_t)n_cols_out * hidden), 0, bytes, 0x00020000)
                                  : rows_lo;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < kLoads; ++i)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(i < 2 ? rows_lo : rows_hi, (__attribute__((address_space(3))) void*)(dst + i * step), 16,
                                                      (int)piece[i], 0, 0, 0);
         issued += exists ? 1 : 0;
@@ -142,15 +146,15 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
         if (issued < n_chunks) request_chunk(true);
     };
     // Chunk ci has landed once at most the loads of the chunks issued after it are outstanding (loads return in
-    // order): up to three chunks of four loads each, fewer at the end of the wavefront's work.
+    // order): up to three chunks of kLoads loads each, fewer at the end of the wavefront's work.
     auto wait_chunk = [&](int ci) {
         const int later = min(n_chunks - 1 - ci, kLmRing - 1);
         if (later >= 3)
-            __builtin_amdgcn_s_waitcnt(0x0F70 | 12);
+            __builtin_amdgcn_s_waitcnt(0x0F70 | (3 * kLoads));
         else if (later == 2)
-            __builtin_amdgcn_s_waitcnt(0x0F70 | 8);
+            __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * kLoads));
         else if (later == 1)
-            __builtin_amdgcn_s_waitcnt(0x0F70 | 4);
+            __builtin_amdgcn_s_waitcnt(0x0F70 | kLoads);
         else
             __builtin_amdgcn_s_waitcnt(0x0F70);
         asm volatile("" ::: "memory");
@@ -209,8 +213,8 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
         f32x4 hr[NORM ? CPW : 1][4][2];
         FewTokens<kSlots ? kSlots : 1> heads[kSlots ? CPW : 1];
         if (ADD) {
-            const int row = (int)blockIdx.x * 16 + red_row;
-            if (wave < 4 && row < vocab && red_tok < k_tok) residual = logits[(size_t)red_tok * vocab + row];
+            const int row = (int)blockIdx.x * kRows + red_row;
+            if (wave < kRows / 4 && row < vocab && red_tok < k_tok) residual = logits[(size_t)red_tok * vocab + row];
         }
         if constexpr (kSlots > 0) {
             const int kv_out = n_colchunks / rep * kLmChunkCols;
@@ -410,7 +414,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the partial strip is in LDS; loads stay in flight
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (wave < (MODE == kLmGated ? 2 : 4)) {
+        if (wave < kRows / 4) {
 #pragma unroll
             for (int tg = 0; tg < TG; ++tg) {
                 const int rt = red_tok + 16 * tg;
@@ -425,7 +429,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
                         gated[(size_t)rt * n_cols_out + ((int)blockIdx.x + si * (int)gridDim.x) * 8 + red_row] = f32_to_bf16(v / (1.0f + expf(-v)) * up);
                     continue;
                 }
-                const int row = ((int)blockIdx.x + si * (int)gridDim.x) * 16 + red_row;
+                const int row = ((int)blockIdx.x + si * (int)gridDim.x) * kRows + red_row;
                 if (row < vocab && rt < k_tok) {
                     if (HEAD && v > best) {  // rows come in increasing order: '>' keeps the lowest index among equals
                         best = v;
@@ -497,38 +501,38 @@ static int lm_workgroups(int n_strips, bool head) {
     return head ? std::min(n, kLmMaxWorkgroups) : n;
 }
 
-template <int CPW, int MODE, bool NORM, int TG = 1>
+template <int CPW, int MODE, bool NORM, int TG = 1, bool HALF = false>
 static hipError_t launch_lm_t(const uint16_t* w, const float* h, const uint16_t* x, int vocab, int hidden, int k_tok, LmCand* part, float* out,
                               hipStream_t s, int rep = 1) {
     static std::atomic<bool> attr_set{false};  // more than the default 64 KiB of dynamic LDS needs opting in, once per kernel
     const size_t lds = (size_t)kLmLdsDw * 4;
     if (!attr_set.load(std::memory_order_acquire)) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lm_head_kernel<CPW, MODE, NORM, TG>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&lm_head_kernel<CPW, MODE, NORM, TG, HALF>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
         attr_set.store(true, std::memory_order_release);
     }
-    const int n_strips = (vocab + 15) / 16;
+    const int n_strips = HALF ? (vocab + 7) / 8 : (vocab + 15) / 16;
     const int n_wg = MODE >= kLmAdd ? n_strips : lm_workgroups(n_strips, MODE == kLmHead);
     const int passes = MODE == kLmHead ? 1 : (k_tok + 16 * TG - 1) / (16 * TG);
-    hipLaunchKernelGGL((lm_head_kernel<CPW, MODE, NORM, TG>), dim3((unsigned)n_wg, (unsigned)passes), dim3(64 * kLmWaves), lds, s, w, h, x, vocab,
+    hipLaunchKernelGGL((lm_head_kernel<CPW, MODE, NORM, TG, HALF>), dim3((unsigned)n_wg, (unsigned)passes), dim3(64 * kLmWaves), lds, s, w, h, x, vocab,
                        hidden, k_tok, n_strips, part, out, rep);
     return hipGetLastError();
 }
 
 // NORM is a request: up to 4096 columns (four column chunks a wavefront) the residual's columns fit the registers
-template <int MODE, bool NORM>
+template <int MODE, bool NORM, bool HALF = false>
 static hipError_t launch_lm_cpw(const uint16_t* w, const float* h, const uint16_t* x, int vocab, int hidden, int k_tok, LmCand* part, float* out,
                                 hipStream_t s) {
     constexpr bool kLong = !NORM || MODE == kLmHead;  // the head has another prologue for longer rows
     switch ((hidden / kLmChunkCols + kLmWaves - 1) / kLmWaves) {
-        case 1: return launch_lm_t<1, MODE, NORM>(w, h, x, vocab, hidden, k_tok, part, out, s);
-        case 2: return launch_lm_t<2, MODE, NORM>(w, h, x, vocab, hidden, k_tok, part, out, s);
-        case 3: return launch_lm_t<3, MODE, NORM>(w, h, x, vocab, hidden, k_tok, part, out, s);
-        case 4: return launch_lm_t<4, MODE, NORM>(w, h, x, vocab, hidden, k_tok, part, out, s);
-        case 5: case 6: if constexpr (kLong) return launch_lm_t<6, MODE, false>(w, h, x, vocab, hidden, k_tok, part, out, s); break;
-        case 7: case 8: if constexpr (kLong) return launch_lm_t<8, MODE, false>(w, h, x, vocab, hidden, k_tok, part, out, s); break;
-        case 9: if constexpr (kLong) return launch_lm_t<9, MODE, false>(w, h, x, vocab, hidden, k_tok, part, out, s); break;
+        case 1: return launch_lm_t<1, MODE, NORM, 1, HALF>(w, h, x, vocab, hidden, k_tok, part, out, s);
+        case 2: return launch_lm_t<2, MODE, NORM, 1, HALF>(w, h, x, vocab, hidden, k_tok, part, out, s);
+        case 3: return launch_lm_t<3, MODE, NORM, 1, HALF>(w, h, x, vocab, hidden, k_tok, part, out, s);
+        case 4: return launch_lm_t<4, MODE, NORM, 1, HALF>(w, h, x, vocab, hidden, k_tok, part, out, s);
+        case 5: case 6: if constexpr (kLong) return launch_lm_t<6, MODE, false, 1, HALF>(w, h, x, vocab, hidden, k_tok, part, out, s); break;
+        case 7: case 8: if constexpr (kLong) return launch_lm_t<8, MODE, false, 1, HALF>(w, h, x, vocab, hidden, k_tok, part, out, s); break;
+        case 9: if constexpr (kLong) return launch_lm_t<9, MODE, false, 1, HALF>(w, h, x, vocab, hidden, k_tok, part, out, s); break;
         default: break;
     }
     return hipErrorInvalidValue;
@@ -579,8 +583,13 @@ hipError_t launch_dense_stream_gated(const uint16_t* w, const uint16_t* x, const
     return launch_lm_cpw<kLmGated, true>(w, h, nullptr, n_out, k_in, k_tok, nullptr, out, s);
 }
 
+// Eight rows a strip where every one of them still has a compute unit: 1536 rows are 96 strips of sixteen.  28 dense layers, hidden 1536, 5
+// tokens: 1055 -> 989 us (down 11.2 -> 8.8 in the trace).
+static bool lm_half_strips(int n_out) { return (n_out + 7) / 8 <= lm_cu_count(); }
+
 hipError_t launch_dense_stream_add(const uint16_t* w, const uint16_t* x, int n_out, int k_in, int k_tok, float* h, hipStream_t s) {
     if (k_tok < 1 || !dense_stream_add_ok(n_out, k_in, k_tok)) return hipErrorInvalidValue;
+    if (lm_half_strips(n_out)) return launch_lm_cpw<kLmAdd, false, true>(w, nullptr, x, n_out, k_in, k_tok, nullptr, h, s);
     return launch_lm_cpw<kLmAdd, false>(w, nullptr, x, n_out, k_in, k_tok, nullptr, h, s);
 }
 
@@ -588,9 +597,11 @@ hipError_t launch_dense_stream_attend_add(const uint16_t* w, const float* qkv, i
                                           hipStream_t s) {
     const int k_in = n_heads * 128, rep = n_heads / n_kv;
     if (k_tok < 1 || !dense_stream_attend_ok(n_heads, n_out, k_tok)) return hipErrorInvalidValue;
+    const bool half = lm_half_strips(n_out);
 #define SD2_ATT_CASE(C, M) \
     if ((n_heads + kLmWaves - 1) / kLmWaves == C && lm_att_slots(M) == few_slots(k_tok)) \
-        return launch_lm_t<C, M, false>(w, qkv, nullptr, n_out, k_in, k_tok, nullptr, h, s, rep)
+        return half ? launch_lm_t<C, M, false, 1, true>(w, qkv, nullptr, n_out, k_in, k_tok, nullptr, h, s, rep) \
+                    : launch_lm_t<C, M, false, 1, false>(w, qkv, nullptr, n_out, k_in, k_tok, nullptr, h, s, rep)
     SD2_ATT_CASE(1, kLmAtt2);
     SD2_ATT_CASE(2, kLmAtt2);
     SD2_ATT_CASE(3, kLmAtt2);
