@@ -64,7 +64,7 @@ __device__ __forceinline__ void lm_better(float& a, int32_t& ia, float b, int32_
 enum { kLmHead, kLmPlain, kLmGated, kLmAdd, kLmAtt2, kLmAtt5 };
 constexpr int lm_att_slots(int mode) { return mode == kLmAtt2 ? 2 : mode == kLmAtt5 ? 5 : 0; }
 
-// HALF: a strip is eight rows (kAdd and kAtt, one strip a workgroup): a chunk is two requests instead of four, the matrix instructions'
+// HALF: a strip is eight rows (kPlain, kAdd and kAtt with one strip a workgroup and one pass): a chunk is two requests instead of four, the matrix instructions'
 // other eight rows are whatever the ring holds and nobody reads their results.  Twice the compute units stream.
 // As a linear TG = 2 takes up to 32 tokens in one pass (two sets of B operands in registers, two accumulators per strip; the partial
 // strips then share one LDS buffer and need a second barrier per strip).
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(64 * kLmWaves) void lm_head_kernel(const uint16_t* 
     constexpr bool HEAD = MODE == kLmHead, ADD = MODE >= kLmAdd;
     constexpr int kSlots = lm_att_slots(MODE);
     constexpr int kLoads = HALF ? 2 : 4, kRows = MODE == kLmGated || HALF ? 8 : 16;  // requests of a chunk; rows of a strip (of each half)
-    static_assert(!HALF || (ADD && TG == 1 && !NORM), "eight rows a strip where results are added to the residual");
+    static_assert(!HALF || (MODE != kLmHead && MODE != kLmGated && TG == 1), "eight rows a strip as a linear");
     // As a linear with more tokens than one pass takes, the grid's second dimension numbers the passes of 16 TG
     // tokens (the matrix is streamed once per pass); the head itself is launched with one pass.
     const int pass = HEAD ? 0 : (int)blockIdx.y;
@@ -549,6 +549,11 @@ hipError_t launch_lm_head(const uint16_t* w, const float* h, int vocab, int hidd
     return hipGetLastError();
 }
 
+// Eight rows a strip where every one of them still has a compute unit: 1536 rows are 96 strips of sixteen.  28 dense layers, hidden 1536, 5
+// tokens: 1055 -> 989 us (down 11.2 -> 8.8 in the trace), and with q|k|v 981.  A plain linear gains from 2048 columns on: 2048 x 8192 on 16
+// tokens 13.9 -> 12.1, 1536 x 8960 on 5 8.6 -> 7.9; 2048 x 2048 and smaller take the launch either way, and keep sixteen.
+static bool lm_half_strips(int n_out) { return (n_out + 7) / 8 <= lm_cu_count(); }
+
 // y[t][n] = sum_c W[n][c] x[t][c] for a dense row-major bf16 matrix and tokens [0, k_tok); every entry of y written
 // (final values: the contraction is added up inside the workgroup).  k_in a multiple of 128, <= 9216.  A pass takes 16
 // tg tokens: two groups where dense_stream_pair_ok(k_in), whose activations then fit the registers next to each other; more
@@ -566,11 +571,13 @@ hipError_t launch_dense_stream_linear(const uint16_t* w, const uint16_t* x, int 
             default: return hipErrorInvalidValue;
         }
     }
+    if (k_tok <= 16 && k_in > 2048 && lm_half_strips(n_out)) return launch_lm_cpw<kLmPlain, false, true>(w, nullptr, x, n_out, k_in, k_tok, nullptr, y, s);
     return launch_lm_cpw<kLmPlain, false>(w, nullptr, x, n_out, k_in, k_tok, nullptr, y, s);
 }
 
 hipError_t launch_dense_stream_norm(const uint16_t* w, const float* h, int n_out, int k_in, int k_tok, float* y, hipStream_t s) {
     if (k_tok < 1 || k_tok > 16 || !dense_stream_norm_ok(k_in, k_tok)) return hipErrorInvalidValue;
+    if (lm_half_strips(n_out)) return launch_lm_cpw<kLmPlain, true, true>(w, h, nullptr, n_out, k_in, k_tok, nullptr, y, s);
     return launch_lm_cpw<kLmPlain, true>(w, h, nullptr, n_out, k_in, k_tok, nullptr, y, s);
 }
 
@@ -582,10 +589,6 @@ hipError_t launch_dense_stream_gated(const uint16_t* w, const uint16_t* x, const
     if (!dense_stream_norm_ok(k_in, k_tok)) return hipErrorInvalidValue;
     return launch_lm_cpw<kLmGated, true>(w, h, nullptr, n_out, k_in, k_tok, nullptr, out, s);
 }
-
-// Eight rows a strip where every one of them still has a compute unit: 1536 rows are 96 strips of sixteen.  28 dense layers, hidden 1536, 5
-// tokens: 1055 -> 989 us (down 11.2 -> 8.8 in the trace).
-static bool lm_half_strips(int n_out) { return (n_out + 7) / 8 <= lm_cu_count(); }
 
 hipError_t launch_dense_stream_add(const uint16_t* w, const uint16_t* x, int n_out, int k_in, int k_tok, float* h, hipStream_t s) {
     if (k_tok < 1 || !dense_stream_add_ok(n_out, k_in, k_tok)) return hipErrorInvalidValue;

@@ -174,6 +174,17 @@ def test_infinite_weight_with_five_and_seven_chunks(k):
     assert np.array_equal(gu.run_linear(gu.DenseMat(_bits(w)), _bits(x), sparse=False), x @ w.T)
 
 
+@pytest.mark.parametrize("n_out", [7, 1000, 2041, 2048, 2049])
+@pytest.mark.parametrize("k", [2048, 2176, 9216])
+@pytest.mark.parametrize("k_tok", [1, 16, 17])
+def test_strips_of_eight_rows(n_out, k, k_tok):
+    """Whole numbers on either side of where strips have eight rows: rows, columns and tokens, and last strips that are not whole."""
+    import gpu_util as gu
+    rng = np.random.default_rng([101, n_out, k, k_tok])
+    w, x = (rng.integers(-4, 5, size=(n, k)).astype(np.float32) for n in (n_out, k_tok))
+    assert np.array_equal(gu.run_linear(gu.DenseMat(_bits(w)), _bits(x), sparse=False), x @ w.T)
+
+
 def _bits(a):
     return wl.f32_to_bf16_bits(a)
 
