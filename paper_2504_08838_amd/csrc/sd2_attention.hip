@@ -171,7 +171,7 @@ hipError_t launch_inflight_attention_wide(const float* part, int n_splits, int k
 // dimension; a row pitch of 288 bytes and the assignment position = 4 e + g of the eight entries to the four lane groups
 // keep the reads of an instruction in different banks.  The wavefronts' results meet in LDS at the end.
 constexpr int kCaWaves = 8;
-constexpr int kCaVRow = 288;                             // bytes
+constexpr int kCaVRow = 320;                             // bytes: the four rows that lanes read side by side fall into different banks
 constexpr int kCaPRow = 36;                              // floats
 constexpr int kCaWaveBytes = 32 * kCaVRow + 16 * kCaPRow * 4;
 constexpr int kCaORow = kAttD + 4;
@@ -194,6 +194,17 @@ __device__ __forceinline__ void split_bf16x3(const float (&x)[8], Frag (&t)[3]) 
         }
 }
 
+// maximum over the sixteen lanes of a row, in every one of them
+__device__ __forceinline__ float row_max(float v) {
+#define SD2_ROW_MAX(ctrl) v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true)))
+    SD2_ROW_MAX(0x121);  // row_ror:1
+    SD2_ROW_MAX(0x122);  // row_ror:2
+    SD2_ROW_MAX(0x124);  // row_ror:4
+    SD2_ROW_MAX(0x128);  // row_ror:8
+#undef SD2_ROW_MAX
+    return v;
+}
+
 __global__ __launch_bounds__(64 * kCaWaves) void cached_attention_wide_kernel(const float* __restrict__ q_rot, const uint16_t* __restrict__ k_cache,
                                                                              const uint16_t* __restrict__ v_cache, int max_pos, int pos0,
                                                                              int k_tok, int q_out, int rep, uint16_t* __restrict__ ctx) {
@@ -205,6 +216,22 @@ __global__ __launch_bounds__(64 * kCaWaves) void cached_attention_wide_kernel(co
     const uint16_t* kg = k_cache + (size_t)grp * max_pos * kAttD;
     const uint16_t* vg = v_cache + (size_t)grp * max_pos * kAttD;
     const int n_pos = pos0 + min(row_lo + 15, n_rows - 1) / rep + 1;  // positions any of the rows attends to
+
+    // The first tile's keys and values are requested in front of the queries, every further tile's as soon as the tile before it has left
+    // the registers (keys when its scores are there, values when they are in LDS): its trip to memory passes beside the softmax.
+    Frag kf[2][4];
+    u32x4 vr[8];
+    auto request_tile = [&](int base) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const uint16_t* src = kg + (size_t)min(base + 16 * b + n, n_pos - 1) * kAttD + 8 * g;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) kf[b][i].q = *reinterpret_cast<const u32x4*>(src + 32 * i);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) vr[i] = *reinterpret_cast<const u32x4*>(vg + (size_t)min(base + 4 * i + g, n_pos - 1) * kAttD + 8 * n);
+    };
+    request_tile(32 * wave);
 
     // operand A of the scores: row n, dimensions 32 i + 8 g + 0..7 (rows past the last repeat it; never written)
     Frag q[4][3];
@@ -263,31 +290,18 @@ __global__ __launch_bounds__(64 * kCaWaves) void cached_attention_wide_kernel(co
 #pragma unroll
     for (int d = 0; d < 8; ++d) o[d] = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int base = 32 * wave; base < n_pos; base += 32 * kCaWaves) {
-        Frag kf[2][4];
-        u32x4 vr[8];
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const uint16_t* src = kg + (size_t)min(base + 16 * b + n, n_pos - 1) * kAttD + 8 * g;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) kf[b][i].q = *reinterpret_cast<const u32x4*>(src + 32 * i);
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) vr[i] = *reinterpret_cast<const u32x4*>(vg + (size_t)min(base + 4 * i + g, n_pos - 1) * kAttD + 8 * n);
         f32x4 s[2];
 #pragma unroll
         for (int b = 0; b < 2; ++b) s[b] = scores(kf[b], base + 16 * b + n);
 #pragma unroll
         for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4*>(vbuf + (4 * i + g) * kCaVRow + 16 * n) = vr[i];
+        if (base + 32 * kCaWaves < n_pos) request_tile(base + 32 * kCaWaves);
         float p[2][4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const bool on0 = base + n <= last[v], on1 = base + 16 + n <= last[v];
             float mx = fmaxf(on0 ? s[0][v] : -3.0e38f, on1 ? s[1][v] : -3.0e38f);
-            mx = fmaxf(mx, __shfl_xor(mx, 1));
-            mx = fmaxf(mx, __shfl_xor(mx, 2));
-            mx = fmaxf(mx, __shfl_xor(mx, 4));
-            mx = fmaxf(mx, __shfl_xor(mx, 8));
-            mx = fmaxf(mx, m[v]);
+            mx = fmaxf(row_max(mx), m[v]);
             const float f = expf(m[v] - mx);
             m[v] = mx;
             p[0][v] = on0 ? expf(s[0][v] - mx) : 0.f;
@@ -308,18 +322,25 @@ __global__ __launch_bounds__(64 * kCaWaves) void cached_attention_wide_kernel(co
         *reinterpret_cast<f32x4*>(&w[4]) = *reinterpret_cast<const f32x4*>(pbuf + n * kCaPRow + 8 * g + 4);
         Frag wt[3];
         split_bf16x3(w, wt);
-        const uint8_t* vp = vbuf + g * kCaVRow + 2 * n;
+        // Two dimensions of a position per read: o[2 j] takes the even ones of dimensions 32 j .. 32 j + 31, o[2 j + 1] the odd ones
+        // (a 16-bit read per dimension and position is twice the reads, and LDS was what the tile waited for).
+        const uint8_t* vp = vbuf + g * kCaVRow + 4 * n;
 #pragma unroll
-        for (int d = 0; d < 8; ++d) {
-            Frag vf;
+        for (int j = 0; j < 4; ++j) {
+            uint32_t pair[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) pair[e] = *reinterpret_cast<const uint32_t*>(vp + 4 * e * kCaVRow + 64 * j);
+            Frag even, odd;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const uint32_t lo = *reinterpret_cast<const uint16_t*>(vp + (4 * (2 * e)) * kCaVRow + 32 * d);
-                const uint32_t hi = *reinterpret_cast<const uint16_t*>(vp + (4 * (2 * e + 1)) * kCaVRow + 32 * d);
-                vf.u[e] = lo | (hi << 16);
+                even.u[e] = __builtin_amdgcn_perm(pair[2 * e + 1], pair[2 * e], 0x05040100u);
+                odd.u[e] = __builtin_amdgcn_perm(pair[2 * e + 1], pair[2 * e], 0x07060302u);
             }
 #pragma unroll
-            for (int k = 2; k >= 0; --k) o[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[k].v, vf.v, o[d], 0, 0, 0);
+            for (int k = 2; k >= 0; --k) {
+                o[2 * j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[k].v, even.v, o[2 * j], 0, 0, 0);
+                o[2 * j + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[k].v, odd.v, o[2 * j + 1], 0, 0, 0);
+            }
         }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_wave_barrier();  // the next tile overwrites both buffers
@@ -345,10 +366,10 @@ __global__ __launch_bounds__(64 * kCaWaves) void cached_attention_wide_kernel(co
             asm volatile("" ::: "memory");
             __builtin_amdgcn_wave_barrier();
             for (int j = 0; j < n_here; ++j) {
-                const uint16_t* src = vg + (size_t)(base + j) * kAttD + n;
+                const uint16_t* src = vg + (size_t)(base + j) * kAttD + 2 * n;
 #pragma unroll
                 for (int d = 0; d < 8; ++d) {
-                    const float x = __uint_as_float((uint32_t)src[16 * d] << 16);
+                    const float x = __uint_as_float((uint32_t)src[32 * (d >> 1) + (d & 1)] << 16);
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
                         if (base + j <= last[v]) o[d][v] += pbuf[(4 * g + v) * kCaPRow + j] * x;
@@ -374,7 +395,7 @@ __global__ __launch_bounds__(64 * kCaWaves) void cached_attention_wide_kernel(co
             ll[wave * 16 + 4 * g + v] = t;
         }
 #pragma unroll
-        for (int d = 0; d < 8; ++d) om[(wave * 16 + 4 * g + v) * kCaORow + 16 * d + n] = o[d][v];
+        for (int d = 0; d < 8; ++d) om[(wave * 16 + 4 * g + v) * kCaORow + 32 * (d >> 1) + 2 * n + (d & 1)] = o[d][v];
     }
     __syncthreads();
     const int mr = tid >> 5, d4 = 4 * (tid & 31), row = row_lo + mr;  // 512 threads: 16 rows of 32 pieces
