@@ -43,3 +43,26 @@ def test_forward_blocks_and_streams(shape, k_tok, pct):
     out = gu.run_forward(model, h_in, shape.hidden)
     assert ol.rel_l2(out, ref) <= E2E_TOL
     assert np.array_equal(gu.run_forward(model, h_in, shape.hidden), out)  # integer sums: bit-identical
+
+
+@pytest.mark.parametrize("k_tok", range(1, 9))
+@pytest.mark.parametrize("fmt", [1, 3])
+def test_every_count_of_tokens(k_tok, fmt):
+    """Prologues run on 1, 2, 3, 4, 5 or 8 token slots, the smallest count that holds the tokens: slots beyond them read nothing and
+    add nothing, and attention's rows end unevenly on the wavefronts of a head."""
+    import gpu_util as gu
+    shape = _shape(384, 3, 1, 1088, layers=2)
+    table = {p: (n, k) for p, n, k in wl.layer_matrix_shapes(shape)}
+    cache = {}
+
+    def get(layer, proj):
+        if (layer, proj) not in cache:
+            cache[(layer, proj)] = wl.gen_weight(22, layer, proj, *table[proj], 50, **({"pattern": "2:4"} if fmt == 3 else {}))
+        return cache[(layer, proj)]
+
+    h_in = wl.gen_x(22, 0, "q", k_tok, shape.hidden)
+    ref = os_.drafter_forward(shape, get, h_in)
+    model = gu.build_model(shape, get, fmt=fmt)
+    out = gu.run_forward(model, h_in, shape.hidden)
+    assert out.shape[0] == k_tok and ol.rel_l2(out, ref) <= E2E_TOL
+    assert np.array_equal(gu.run_forward(model, h_in, shape.hidden), out)
