@@ -37,11 +37,11 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0  # MI355X published HBM3E bandwidth
 # HBM bytes per launch of the forward kernel (and of the gate+up sparse linear) from rocprofv3 --pmc
 # FETCH_SIZE / WRITE_SIZE runs, scaled by the plain copy kernel of --calibrate; None until measured.
-MEASURED_TRAFFIC_BYTES = 3421746968
-MEASURED_LINEAR_TRAFFIC_BYTES = 61259910
-MEASURED_LM_HEAD_TRAFFIC_BYTES = 788242141
+MEASURED_TRAFFIC_BYTES = 3451098928
+MEASURED_LINEAR_TRAFFIC_BYTES = 61260933
+MEASURED_LM_HEAD_TRAFFIC_BYTES = 788253407
 MEASURED_NM24_TRAFFIC_BYTES = 57260356
-MEASURED_DECODE_TRAFFIC_BYTES = 3344723477
+MEASURED_DECODE_TRAFFIC_BYTES = 3395561235
 CALIBRATION_BYTES = 256 << 20  # size of the plain copies launched by --calibrate
 STREAM_BYTES = 2 << 30         # the pure read stream that serves as the measured ceiling
 
