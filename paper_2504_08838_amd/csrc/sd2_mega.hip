@@ -349,13 +349,14 @@ __device__ __forceinline__ u32x4 pack_bf16x8(const float (&f)[8]) {
     return u32x4{pack_bf16(f[0], f[1]), pack_bf16(f[2], f[3]), pack_bf16(f[4], f[5]), pack_bf16(f[6], f[7])};
 }
 
-// sum over the sixteen lanes of a row, in every one of them
+// sum over the sixteen lanes of a row, the same bits in every one of them: each step adds two lanes that go on with the same sum (by
+// rotations every lane would add in an order of its own, and a head's numerator and denominator would belong to different weights)
 __device__ __forceinline__ float row_sum(float v) {
 #define SD2_ROW_ADD(ctrl) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true))
-    SD2_ROW_ADD(0x121);  // row_ror:1
-    SD2_ROW_ADD(0x122);  // row_ror:2
-    SD2_ROW_ADD(0x124);  // row_ror:4
-    SD2_ROW_ADD(0x128);  // row_ror:8
+    SD2_ROW_ADD(0xB1);   // quad_perm [1, 0, 3, 2]
+    SD2_ROW_ADD(0x4E);   // quad_perm [2, 3, 0, 1]
+    SD2_ROW_ADD(0x141);  // row_half_mirror
+    SD2_ROW_ADD(0x140);  // row_mirror
 #undef SD2_ROW_ADD
     return v;
 }

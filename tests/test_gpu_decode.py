@@ -234,3 +234,67 @@ def test_bounded_wait_gives_up_and_recovers(sd2_options):
     got = _decode(model, shape, h_bits, gu.dev(kc), gu.dev(vc), max_pos, n_hist)
     want = od.drafter_decode(shape, get, h_bits, kc, vc, n_hist, THETA)
     assert rel_l2(got, want) <= 1e-3
+
+
+def _spelled_out(rep, fmt, n_hist, k_tok, keys, seed):
+    """One layer on two key/value heads whose attention can be told in advance: h_in is 1 everywhere, so the norm's result is too; a query is 1
+    in the dimensions UNTURNED (with base 1e30 they keep it at every position) and 0 elsewhere; the call's own keys are 0; the values are
+    v0, own ones and history alike; o adds the context to the first columns of the residual and the MLP is zero.  -> (h_out - 1, the
+    caches' bits, v0 [n_kv][128]); keys(rng, n_kv, n_hist): the history's keys, and its values (None: v0)."""
+    import gpu_util as gu
+    n_kv, hidden, max_pos, rng = 2, 1536, n_hist + 16, np.random.default_rng([seed, rep, n_hist])
+    shape = SimpleNamespace(layers=1, hidden=hidden, q_out=128 * n_kv * rep, kv_out=128 * n_kv, inter=256, n_heads=n_kv * rep, n_kv=n_kv, head_dim=128)
+    v0 = rng.integers(-127, 128, (n_kv, 128)) / 64.0
+    w = {p: np.zeros(nk, dtype=np.float32) for p, nk in ((p, (n, k)) for p, n, k in wl.layer_matrix_shapes(shape))}
+    for h in range(shape.n_heads):
+        for d in UNTURNED:
+            w["q"][128 * h + d, rng.integers(hidden)] = 1.0
+    w["v"][np.arange(shape.kv_out), rng.integers(0, hidden, shape.kv_out)] = v0.reshape(-1)
+    w["o"][np.arange(shape.q_out), np.arange(shape.q_out)] = 1.0
+    model = gu.build_model(shape, lambda layer, proj: wl.f32_to_bf16_bits(w[proj]), fmt=fmt)
+    kc, vc = np.zeros((1, n_kv, max_pos, 128), dtype=np.float32), np.zeros((1, n_kv, max_pos, 128), dtype=np.float32)
+    kc[0, :, :n_hist], values = keys(rng, n_kv, n_hist)
+    vc[0, :, :n_hist] = v0[:, None] if values is None else values
+    kc, vc = wl.f32_to_bf16_bits(kc), wl.f32_to_bf16_bits(vc)
+    h = np.full((k_tok, hidden), 0x3F80, dtype=np.uint16)
+    out = _decode(model, shape, h, gu.dev(kc), gu.dev(vc), max_pos, n_hist, theta=1e30)
+    assert np.array_equal(out[:, shape.q_out:], np.ones((k_tok, hidden - shape.q_out)))
+    return out[:, :shape.q_out].reshape(k_tok, n_kv, rep, 128) - 1.0, v0
+
+
+UNTURNED = np.r_[24:64, 88:128]
+
+
+@pytest.mark.parametrize("fmt", [1, 3])
+@pytest.mark.parametrize("rep", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("n_hist,k_tok", [(37, 1), (300, 1), (700, 3), (90, 8), (200, 12)])
+def test_equal_values_are_their_own_average(n_hist, k_tok, rep, fmt, forward):
+    """Every position has the same values, so whatever the weights are, the context is those values: numerator and denominator of a head
+    have to see the same weights in every dimension.  Scores are sums of terms near 1e6 that cancel: a score added up in another order is
+    another score, by some tenths.  What is left after the division (some 2^-20) is far below half a spacing of the context's bf16."""
+    def keys(rng, n_kv, n):
+        k = np.zeros((n_kv, n, 128))
+        size = (rng.integers(128, 256, (n_kv, n, len(UNTURNED) // 2)) * 2.0 ** 16)  # 8 bits: exact in bf16
+        k[..., UNTURNED] = rng.permuted(np.concatenate([size, -size], axis=-1), axis=-1)
+        return k, None
+    got, v0 = _spelled_out(rep, fmt, n_hist, k_tok, keys, 85)
+    assert np.array_equal(got, np.broadcast_to(v0[None, :, None], got.shape))
+
+
+@pytest.mark.parametrize("fmt", [1, 3])
+@pytest.mark.parametrize("rep", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("n_hist,k_tok,at", [(300, 1, 0), (300, 1, 299), (700, 3, 350), (90, 8, 7)])
+def test_one_position_over_all_others(n_hist, k_tok, at, rep, fmt, forward):
+    """One position of the history has a score of 500 and the others 0 or, every third and all of the last two thirds, minus infinity: the
+    context is that position's values."""
+    def keys(rng, n_kv, n):
+        k, v = np.zeros((n_kv, n, 128)), rng.integers(-127, 128, (n_kv, n, 128)) / 64.0
+        k[:, n // 3:, UNTURNED[3]] = -np.inf
+        k[:, ::3, UNTURNED[-1]] = -np.inf
+        k[:, at] = 0.0
+        k[:, at, UNTURNED] = 72.0  # 80 x 72 / sqrt(128) = 509
+        chosen.append(v[:, at])
+        return k, v
+    chosen = []
+    got, _ = _spelled_out(rep, fmt, n_hist, k_tok, keys, 86)
+    assert np.array_equal(got, np.broadcast_to(chosen[0][None, :, None], got.shape))
