@@ -202,3 +202,30 @@ def test_attention_inside_the_output_projection(heads, kv, k_tok):
     assert ol.rel_l2(out, os_.drafter_forward(shape, get, h)) <= TOL
     apart, _, _ = gu.run_forward_trace(model, h, shape)
     assert np.array_equal(out, apart)
+
+
+@pytest.mark.parametrize("heads,kv,hidden", [(2, 1, 256), (9, 3, 1152), (24, 8, 3072), (33, 11, 4224)])
+@pytest.mark.parametrize("k_tok", [1, 2, 3, 5, 8])
+def test_attention_over_the_whole_range_of_values(heads, kv, hidden, k_tok):
+    """Values of 2^127 at every token average to 2^127, and token 0's weight of exp(-89.8), which has no normal fp32 number, still brings
+    its 2^127 in front of the other tokens' zeros: in the linear that attends and in a launch of its own.  Every entry of h is 1 but
+    column 0, which is -1 at token 0, and the norm's result is h."""
+    import gpu_util as gu
+    shape = _shape(hidden, heads, kv, 128, layers=1)
+    w = {p: np.zeros((n, k), dtype=np.float32) for p, n, k in wl.layer_matrix_shapes(shape)}
+    w["q"][::128, 1] = 1.0
+    w["k"][::128, 0] = 508.0                                             # scores +-508 / sqrt(128): 89.8 apart
+    w["v"][1::128, 2] = 2.0 ** 127                                       # dimension 1: the same at every token
+    w["v"][2::128, 1], w["v"][2::128, 0] = 2.0 ** 126, -(2.0 ** 126)     # dimension 2: 2^127 at token 0, else 0
+    w["o"][3, 1], w["o"][4, 128 * heads - 126] = 2.0 ** -120, 1.0        # the first head's dimension 1, the last one's dimension 2
+    w["o"][5, 2] = 2.0 ** -120
+    _, model = _model(shape, 0, make=lambda proj, n, k: _bits(w[proj]))
+    h = np.ones((k_tok, hidden))
+    h[0, 0] = -1.0
+    ref = h.copy()
+    far = np.array([2.0 ** 127] + [np.exp(-2 * 508 / np.sqrt(128.0)) * 2.0 ** 127 / t for t in range(1, k_tok)])  # 0.17 / t
+    ref[:, 3] += 128.0
+    ref[:, 4] += far
+    ref[:, 5] += far * 2.0 ** -120
+    out = gu.run_forward(model, _bits(h.astype(np.float32)), hidden)
+    assert (abs(out - ref) <= 2.0 ** -8 * abs(ref - h) + 2.0 ** -22 * abs(ref)).all()  # the context's rounding to bf16
