@@ -621,6 +621,40 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
     unsigned gen = 0;
     int spin_limit = a.spin_limit;
 
+    // Records a phase once it has arrived at the barrier, where there is time, from where its prologue read and left it: the block's
+    // activations, in LDS up to the next prologue, and what they were made of, which nobody changes any more.  The blocks of strips
+    // share the tokens.  (Recorded on the way, every token by every workgroup, straight-line work on all token slots spills 78
+    // registers: eight layers of the 3B shape on 5 tokens 421 us, so 323.)  Every source column has its own place: the residual,
+    // gate and up, or the head's query and its group's key and value, which all heads of the group record.
+    auto record = [&](int q) {
+        KArgs kr = ka;
+        int first = tid;
+        asm volatile("" : "+s"(kr), "+v"(first));  // what follows from the arguments is made again: kept over the phases, it would spill
+        const int layer = q >> 2, kind = q & 3, n_sblk = kr->geo[kind].n_sblk;
+        const uint32_t* kpl = plans + kind * kPlanDw;
+        const int col_lo = uni(kpl[3]) * 256, n_col = uni(kpl[6]) ? min(kr->geo[kind].b_blk * 256, kr->geo[kind].k_in - col_lo) : 0;
+        const int* from = kind == 1   ? kr->yqkv + (size_t)layer * kr->yqkv_stride
+                          : kind == 3 ? kr->ygu + (size_t)layer * kr->ygu_stride
+                                      : kr->hv + (size_t)(2 * layer + (kind >> 1)) * kr->h_stride;
+        const int pitch = kind == 1 ? kr->q_out + 2 * kr->kv_out : kind == 3 ? 2 * kr->inter : kr->hidden;
+#pragma unroll 1
+        for (int t = cu % n_sblk; t < k_tok; t += n_sblk) {
+            const int* row = from + (size_t)t * pitch;
+            uint16_t* to_x = kr->trace_x + ((size_t)q * k_tok + t) * kr->trace_kmax;
+            float* to = kr->trace_src + ((size_t)q * k_tok + t) * kr->trace_smax;
+#pragma unroll 1
+            for (int c = first; c < n_col; c += kMegaThreads) {
+                const int c0 = col_lo + c, key = kr->q_out + (c0 >> 7) / (kr->n_heads / kr->n_kv) * 128 + (c0 & 127);
+                const int c1 = kind == 1 ? key : kind == 3 ? c0 + kr->inter : c0, c2 = kind == 1 ? key + kr->kv_out : c0;
+                const int v0 = row[c0], v1 = row[c1], v2 = row[c2];
+                to_x[c0] = xlds[((c >> 8) * kMegaMaxTok + t) * kXRow + (c & 255)];
+                to[c0] = from_fixed(v0, kr->fix_inv);
+                to[c1] = from_fixed(v1, kr->fix_inv);
+                to[c2] = from_fixed(v2, kr->fix_inv);
+            }
+        }
+    };
+
     for (int p = 0; p < n_phases; ++p) {
         const int layer = p >> 2, kind = p & 3;
         MegaGeo ge;  // this kind's geometry, fetched with scalar loads
@@ -634,6 +668,7 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
         unsigned long long* tt = a.trace_time ? a.trace_time + ((size_t)cu * n_phases + p) * 8 : nullptr;
         if (tt && tid == 0) tt[0] = __builtin_amdgcn_s_memrealtime();
         if (p > 0) barrier_arrive(a.bar, gen);
+        if (TRACE && p > 0) record(p - 1);
 
         if (KV && kind == 1) {
             // The attention step over the cache, then a barrier of its own; the first tile of the linear is expanded
@@ -753,7 +788,6 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
         const int hv_in = 2 * layer + (kind >= 2 ? 1 : 0);  // what this phase's norm reads / what its output is added to
         const int* h_cur = a.hv + (size_t)hv_in * a.h_stride;
         int* h_nxt = a.hv + (size_t)(hv_in + 1) * a.h_stride;
-        const size_t tr_x = ((size_t)p * k_tok) * a.trace_kmax, tr_s = ((size_t)p * k_tok) * a.trace_smax;
 
         // columns past the end of a ragged last slab must read as zero
         if (n_col < ge.b_blk * 256)
@@ -823,12 +857,6 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
                         const uint32_t lo = pack_bf16((float)hraw[t][0] * inv, (float)hraw[t][1] * inv);
                         const uint32_t hi = pack_bf16((float)hraw[t][2] * inv, (float)hraw[t][3] * inv);
                         *reinterpret_cast<uint2*>(dst + t * kXRow) = make_uint2(lo, hi);
-                        if (TRACE && t < k_tok) {
-                            *reinterpret_cast<f32x4*>(a.trace_src + tr_s + (size_t)t * a.trace_smax + c4) =
-                                f32x4{from_fixed(hraw[t][0], fix_inv), from_fixed(hraw[t][1], fix_inv), from_fixed(hraw[t][2], fix_inv),
-                                      from_fixed(hraw[t][3], fix_inv)};
-                            *reinterpret_cast<uint2*>(a.trace_x + tr_x + (size_t)t * a.trace_kmax + c4) = make_uint2(lo, hi);
-                        }
                     }
                 }
             });
@@ -854,12 +882,6 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
                         const uint32_t pk = pack_bf16(gv[0] * __builtin_amdgcn_rcpf(1.0f + __expf(-gv[0])) * uv[0],
                                                       gv[1] * __builtin_amdgcn_rcpf(1.0f + __expf(-gv[1])) * uv[1]);
                         *reinterpret_cast<uint32_t*>(dst + t * kXRow) = pk;
-                        if (TRACE && t < k_tok) {
-                            float* ts = a.trace_src + tr_s + (size_t)t * a.trace_smax + col_lo + c;
-                            *reinterpret_cast<f32x2*>(ts) = gv;
-                            *reinterpret_cast<f32x2*>(ts + a.inter) = uv;
-                            *reinterpret_cast<uint32_t*>(a.trace_x + tr_x + (size_t)t * a.trace_kmax + col_lo + c) = pk;
-                        }
                     }
                 }
             });
@@ -964,16 +986,7 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
                                 o0 += w * v[j][0];
                                 o1 += w * v[j][1];
                             }
-                            const uint32_t cv = pack_bf16(o0, o1);
-                            *reinterpret_cast<uint32_t*>(dst + i * kXRow) = cv;
-                            if (TRACE && i < k_tok) {
-                                *reinterpret_cast<uint32_t*>(a.trace_x + tr_x + (size_t)i * a.trace_kmax + col_lo + cc) = cv;
-                                float* ts = a.trace_src + tr_s + (size_t)i * a.trace_smax + 2 * lane;
-                                *reinterpret_cast<f32x2*>(ts + head * D) = f32x2{from_fixed(qr[i][0], fix_inv), from_fixed(qr[i][1], fix_inv)};
-                                // heads of one kv group all record the same k and v
-                                *reinterpret_cast<f32x2*>(ts + a.q_out + kvh * D) = k[i];
-                                *reinterpret_cast<f32x2*>(ts + a.q_out + a.kv_out + kvh * D) = v[i];
-                            }
+                            *reinterpret_cast<uint32_t*>(dst + i * kXRow) = pack_bf16(o0, o1);
                         }
                     };
                     if (wave & 1) {
@@ -1114,6 +1127,7 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
     // ---------------- the last version of the residual stream as fp32
     if (n_phases > 0) {
         barrier_arrive(a.bar, gen);
+        if (TRACE) record(n_phases - 1);
         barrier_wait(a.bar, a.err, (unsigned)ncu, gen, spin_limit);
     }
     {

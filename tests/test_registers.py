@@ -1,4 +1,4 @@
-"""What the compiler's own notes in the built library say of the kernels: none but the persistent forward spills to memory."""
+"""What the compiler's own notes in the built library say of the kernels: which of them spill to memory."""
 import os
 import re
 
@@ -25,3 +25,9 @@ def scratch():
 def test_streaming_kernels_keep_everything_in_registers(scratch):
     spilled = [name for name, size in scratch.items() if size and "mega_forward_kernel" not in name]
     assert len(scratch) > 50 and not spilled
+
+
+def test_persistent_forward_without_a_cache_keeps_everything_in_registers(scratch):
+    """mega_forward_kernel<traced, probed, 2:4, 0>: a reload would wait behind the stream in flight, in every phase."""
+    plain = {name: size for name, size in scratch.items() if "mega_forward_kernel" in name and "Li0E" in name}
+    assert len(plain) == 5 and not any(plain.values())
