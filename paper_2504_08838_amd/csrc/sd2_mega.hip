@@ -57,7 +57,6 @@ static_assert(kMaxBAtt * 256 <= kAttHeads * 128, "attention block fits the head 
 // Activations cross compute units through memory: written by agent-scope stores and integer atomics, read (after a
 // grid barrier, at addresses no compute unit has read before in this launch) with ordinary loads.
 __device__ __forceinline__ void astore(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, SD2_AGENT); }
-__device__ __forceinline__ void astore_i(int* p, int v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, SD2_AGENT); }
 __device__ __forceinline__ void aadd_i(int* p, int v) { (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, SD2_AGENT); }
 
 // What crosses compute units as a sum of several workgroups' contributions (the results of a linear whose contraction
@@ -72,19 +71,6 @@ __device__ __forceinline__ void aadd_i(int* p, int v) { (void)__hip_atomic_fetch
 __device__ __forceinline__ float from_fixed(int w, float inv) { return (float)w * inv; }
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x2 __attribute__((ext_vector_type(2)));
-
-// sum over the 64 lanes (cross-lane adds on the DPP path, no LDS traffic); result in every lane
-__device__ __forceinline__ float wave_sum(float v) {
-#define SD2_DPP_ADD(ctrl, rmask) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, rmask, 0xf, true))
-    SD2_DPP_ADD(0x111, 0xf);  // row_shr:1
-    SD2_DPP_ADD(0x112, 0xf);  // row_shr:2
-    SD2_DPP_ADD(0x114, 0xf);  // row_shr:4
-    SD2_DPP_ADD(0x118, 0xf);  // row_shr:8
-    SD2_DPP_ADD(0x142, 0xa);  // row_bcast:15
-    SD2_DPP_ADD(0x143, 0xc);  // row_bcast:31
-#undef SD2_DPP_ADD
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
 
 // Calls f with the number of token slots that the code is made for, the smallest of 1 2 3 4 5 8 that holds the tokens: straight-line
 // work on all slots (those past the last token repeat it; nobody reads their results) takes less time than a branch per token, which
@@ -576,7 +562,7 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
     static_assert(kMegaMaxTok * kMegaWaves <= kMiscDw && (kAreaDw + kXldsDw + kRedDw) % 4 == 0, "partial sums fit, 16-byte aligned");
     if (tid < 16) lut[tid] = make_expand_selector((uint32_t)tid);
     for (int i = tid; i < kRedDw + kMiscDw; i += kMegaThreads) red[i] = 0.f;  // accumulators, sums
-    for (int i = tid; i < kXldsDw; i += kMegaThreads) (mega_lds + kAreaDw)[i] = 0u;  // rows of unused token slots stay zero
+    for (int i = tid; i < kXldsDw; i += kMegaThreads) (mega_lds + kAreaDw)[i] = 0u;  // (rows past the last token are operands, too; their results are read by nobody)
 
     // per-kind plans -> LDS
     uint32_t* plans = reinterpret_cast<uint32_t*>(part_sums + kMiscDw);
@@ -680,11 +666,7 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
             for (int u = 0; u < kAttUnr; ++u) kw[u] = vw[u] = u32x4{0u, 0u, 0u, 0u};
             if (has_item) attention_loads(ka, layer, it, it.j_lo, tid, kw, vw);
             barrier_wait(a.bar, a.err, (unsigned)ncu, gen, spin_limit);
-            if (has_item) {
-                attention_item<(KV > 0 ? KV : 1)>(ka, layer, it, reinterpret_cast<float*>(xlds), tid, kw, vw);
-                // the scratch was the activation area, whose rows of unused token slots must read as zero
-                for (int i = tid; i < kXldsDw; i += kMegaThreads) (mega_lds + kAreaDw)[i] = 0u;
-            }
+            if (has_item) attention_item<(KV > 0 ? KV : 1)>(ka, layer, it, reinterpret_cast<float*>(xlds), tid, kw, vw);
             barrier_arrive(a.bar, gen);
         }
 
