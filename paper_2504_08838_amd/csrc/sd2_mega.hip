@@ -389,6 +389,7 @@ template <int REP>
 __device__ __forceinline__ void attention_item(KArgs ka, int layer, const AttItem& it, float* scratch, int tid,
                                                u32x4 (&kw)[kAttUnr], u32x4 (&vw)[kAttUnr]) {
     constexpr int D = 128, RPI = kAttRpi, UNR = kAttUnr;
+    asm volatile("" : "+v"(tid));  // a thread's places are made again for every layer: kept over the phases, they would spill
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int piece = lane & 15, slot = wave * 4 + (lane >> 4);
     const int k_tok = ka->k_tok, C = ka->att_chunks, n_kv = ka->n_kv, n_heads = ka->n_heads;
@@ -781,7 +782,9 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
             // the squares meet in LDS, and each thread then normalises and rounds the columns it holds.
             with_token_slots(k_tok, [&](auto slots) {
                 constexpr int N = decltype(slots)::value;
-                const int c4 = 4 * tid;
+                int me = tid, at = lane;
+                if (KV > 0) asm volatile("" : "+v"(me), "+v"(at));  // (kept over the phases, what follows from them would spill)
+                const int c4 = 4 * me;
                 i32x4 hraw[N];
 #pragma unroll
                 for (int t = 0; t < N; ++t) hraw[t] = i32x4{0, 0, 0, 0};
@@ -812,8 +815,8 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
                 float inv_t[N];
                 {
                     float tot = 0.f;
-                    if (lane < N) {
-                        const f32x4* ps = reinterpret_cast<const f32x4*>(part_sums + lane * kMegaWaves);
+                    if (at < N) {
+                        const f32x4* ps = reinterpret_cast<const f32x4*>(part_sums + at * kMegaWaves);
                         static_assert(kMegaWaves == 12, "three 16-byte reads hold a token's partial sums");
                         const f32x4 p0 = ps[0], p1 = ps[1], p2 = ps[2];
                         tot = ((((((((((p0[0] + p0[1]) + p0[2]) + p0[3]) + p1[0]) + p1[1]) + p1[2]) + p1[3]) + p2[0]) + p2[1]) + p2[2]) + p2[3];
@@ -825,7 +828,7 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
                     const float ms = __builtin_fmaf(tot, inv_hidden, 1e-5f), r0 = __builtin_amdgcn_rsqf(ms);
                     const float r = __builtin_fmaf(0.5f * r0, __builtin_fmaf(-ms * r0, r0, 1.0f), r0);
                     // a residual whose norm stays below the limit has every entry below it: the adds into it cannot wrap
-                    if (wave == 0 && lane < k_tok && !(tot < a.h_limit_sq)) __hip_atomic_fetch_or(a.err, 2u, __ATOMIC_RELAXED, SD2_AGENT);
+                    if (wave == 0 && at < k_tok && !(tot < a.h_limit_sq)) __hip_atomic_fetch_or(a.err, 2u, __ATOMIC_RELAXED, SD2_AGENT);
                     const float scaled = r * fix_inv;
 #pragma unroll
                     for (int t = 0; t < N; ++t) inv_t[t] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(scaled), t));
