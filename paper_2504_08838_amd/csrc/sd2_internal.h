@@ -36,6 +36,9 @@ hipError_t launch_sparse_strip_linear(const MatArgs& m, const LinArgs& a, int tg
 bool sparse_strip_gated_supported(const MatArgs& m, int tg);
 hipError_t launch_sparse_strip_gated(const MatArgs& m, const uint16_t* x, int k_tok, uint16_t* m_out, int tg, hipStream_t s);
 
+// Compute units of a device (256 where it cannot be asked), asked once: launches decide by it, several times a layer.
+int device_cu_count();
+
 // Device address, on the current device, of the library's static scratch array (kStaticScratchBytes bytes, 256-byte
 // aligned): looked up once per device, no allocation.  Calls that use it on one GPU share it.
 constexpr size_t kStaticScratchBytes = (size_t)8 << 20;

@@ -496,7 +496,7 @@ __global__ __launch_bounds__(256) void dense_linear_kernel(const uint16_t* __res
 
 // ------------------------------------------------------------------ launch
 
-static int device_cu_count() {
+int device_cu_count() {
     static std::atomic<int> cached{0};  // threads that race here compute the same value
     int cus = cached.load(std::memory_order_relaxed);
     if (cus == 0) {

@@ -487,17 +487,9 @@ __global__ __launch_bounds__(1024) void lm_head_pick_kernel(const LmCand* __rest
     }
 }
 
-static int lm_cu_count() {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-        return n;
-    return 256;
-}
-
 // one per compute unit; the head's candidates have room for kLmMaxWorkgroups
 static int lm_workgroups(int n_strips, bool head) {
-    const int n = std::min(n_strips, lm_cu_count());
+    const int n = std::min(n_strips, device_cu_count());
     return head ? std::min(n, kLmMaxWorkgroups) : n;
 }
 
@@ -552,7 +544,7 @@ hipError_t launch_lm_head(const uint16_t* w, const float* h, int vocab, int hidd
 // Eight rows a strip where every one of them still has a compute unit: 1536 rows are 96 strips of sixteen.  28 dense layers, hidden 1536, 5
 // tokens: 1055 -> 989 us (down 11.2 -> 8.8 in the trace), and with q|k|v 981.  A plain linear gains from 2048 columns on: 2048 x 8192 on 16
 // tokens 13.9 -> 12.1, 1536 x 8960 on 5 8.6 -> 7.9; 2048 x 2048 and smaller take the launch either way, and keep sixteen.
-static bool lm_half_strips(int n_out) { return (n_out + 7) / 8 <= lm_cu_count(); }
+static bool lm_half_strips(int n_out) { return (n_out + 7) / 8 <= device_cu_count(); }
 
 // y[t][n] = sum_c W[n][c] x[t][c] for a dense row-major bf16 matrix and tokens [0, k_tok); every entry of y written
 // (final values: the contraction is added up inside the workgroup).  k_in a multiple of 128, <= 9216.  A pass takes 16

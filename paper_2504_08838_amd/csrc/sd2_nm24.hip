@@ -151,14 +151,6 @@ __global__ __launch_bounds__(64 * WAVES) void nm24_linear_kernel(const uint8_t* 
     }
 }
 
-static int nm24_cu_count() {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-        return n;
-    return 256;
-}
-
 template <int SPW, int WAVES>
 static hipError_t launch_nm24_t(const uint8_t* tiles, const uint16_t* x, float* y, int n_out, int k_in, int k_tok,
                                 int n_strips, int n_slabs, hipStream_t s) {
@@ -170,7 +162,7 @@ static hipError_t launch_nm24_t(const uint8_t* tiles, const uint16_t* x, float* 
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, nm24_linear_kernel<SPW, WAVES>, 64 * WAVES, 0) != hipSuccess ||
             per_cu < 1)
             per_cu = 1;
-        resident = nm24_cu_count() * per_cu;
+        resident = device_cu_count() * per_cu;
         cached.store(resident, std::memory_order_relaxed);
     }
     const int grid = std::min(n_strips, resident);

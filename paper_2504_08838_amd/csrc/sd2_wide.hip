@@ -483,20 +483,6 @@ __global__ __launch_bounds__(64 * W) void wide_linear_kernel(const WideArgs a) {
 
 // ---------------------------------------------------------------- plan and launch
 
-static int wide_cu_count() {
-    static std::atomic<int> cached{0};  // threads that race here compute the same value
-    int cus = cached.load(std::memory_order_relaxed);
-    if (cus == 0) {
-        int dev = 0, n = 0;
-        cus = (hipGetDevice(&dev) == hipSuccess &&
-               hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
-                  ? n
-                  : 256;
-        cached.store(cus, std::memory_order_relaxed);
-    }
-    return cus;
-}
-
 // How a wide linear is cut.  The model behind the choice is a fit to this part, in microseconds: a strip costs a pass the
 // expansion of its half tile (two or three wavefronts on a SIMD take turns), fetching a unit's activations is paid once a
 // pass and grows with the tokens, completing a group takes 1.5, and a partial result its bytes to memory and back plus a
@@ -508,7 +494,7 @@ bool wide_plan(int n_out, int k_in, int n_strips, int k_tok, bool gated, int max
     if (tg < 2 || tg > 4 || (gated && n_out % 32) || k_in > (1 << 20) || (int64_t)n_out * k_in > (1ll << 31) - (1 << 23))
         return false;  // 32-bit byte offsets, into the value section and over 64 rows of activations
     const int n_units = (k_in + 127) / 128;
-    const int cus = wide_cu_count(), step = gated ? 2 : 1;
+    const int cus = device_cu_count(), step = gated ? 2 : 1;
     const int max_cut = std::min(std::min(max_split, kWideMaxSplit), std::min(n_units, cus));
     int per_wg[kWideMaxSplit + 1], units[kWideMaxSplit + 1];  // strips of a workgroup, units of a split
     double extra[kWideMaxSplit + 1];
