@@ -189,19 +189,30 @@ def _bits(a):
     return wl.f32_to_bf16_bits(a)
 
 
-@pytest.mark.parametrize("heads,kv", [(1, 1), (8, 2), (9, 3), (16, 4), (17, 17), (25, 5), (32, 4), (33, 11)])
-@pytest.mark.parametrize("k_tok", [1, 2, 3, 5, 6, 8, 9])
-def test_attention_inside_the_output_projection(heads, kv, k_tok):
-    """One to four heads a wavefront and wavefronts without one, every count of token slots, heads and tokens on either side of where the
-    linear attends by itself: the traced forward's attention is a launch of its own and gives the same bits."""
+def _attends_as_apart(hidden, heads, kv, k_tok):
     import gpu_util as gu
-    shape = _shape(256, heads, kv, 128, layers=1)
+    shape = _shape(hidden, heads, kv, 128, layers=1)
     get, model = _model(shape, 97)
     h = wl.gen_x(97, 0, "q", k_tok, shape.hidden)
     out = gu.run_forward(model, h, shape.hidden)
     assert ol.rel_l2(out, os_.drafter_forward(shape, get, h)) <= TOL
     apart, _, _ = gu.run_forward_trace(model, h, shape)
     assert np.array_equal(out, apart)
+
+
+@pytest.mark.parametrize("heads,kv", [(1, 1), (8, 2), (9, 3), (16, 4), (17, 17), (25, 5), (32, 4), (33, 11)])
+@pytest.mark.parametrize("k_tok", [1, 2, 3, 5, 6, 8, 9])
+def test_attention_inside_the_output_projection(heads, kv, k_tok):
+    """One to four heads a wavefront and wavefronts without one, every count of token slots, heads and tokens on either side of where the
+    linear attends by itself: the traced forward's attention is a launch of its own and gives the same bits."""
+    _attends_as_apart(256, heads, kv, k_tok)
+
+
+@pytest.mark.parametrize("hidden,heads,kv", [(2112, 8, 8), (2112, 9, 3), (3072, 16, 4), (3072, 24, 8), (4096, 32, 8)])
+@pytest.mark.parametrize("k_tok", [1, 2, 3, 5])
+def test_attention_inside_strips_of_sixteen_rows(hidden, heads, kv, k_tok):
+    """The same on more than 2048 rows, whose strips have sixteen rows: one to four heads a wavefront on two slots, one and two on five."""
+    _attends_as_apart(hidden, heads, kv, k_tok)
 
 
 @pytest.mark.parametrize("heads,kv,hidden", [(2, 1, 256), (9, 3, 1152), (24, 8, 3072), (33, 11, 4224)])
