@@ -167,9 +167,10 @@ hipError_t launch_inflight_attention_wide(const float* part, int n_splits, int k
 // Workgroup (key/value head, 16 query rows): the rows are (token, query head of the group) pairs in that order, so a cache
 // row is read once per sixteen of them.  A wavefront takes tiles of 32 positions: scores of the sixteen rows (keys straight
 // from the cache as matrix operands), running maximum and sum per row (online softmax), weighted values.  The values of a
-// tile go through the wavefront's LDS, where an operand needs eight positions of one dimension: two-byte reads, lane =
-// dimension; a row pitch of 288 bytes and the assignment position = 4 e + g of the eight entries to the four lane groups
-// keep the reads of an instruction in different banks.  The wavefronts' results meet in LDS at the end.
+// tile go through the wavefront's LDS, where an operand needs eight positions of one dimension: four-byte reads, lane = a pair
+// of dimensions, whose even and odd ones become two operands; a row pitch of 320 bytes and the assignment position = 4 e + g of the
+// eight entries to the four lane groups put the sixty-four reads of an instruction into as many banks.  The wavefronts' results meet
+// in LDS at the end.
 constexpr int kCaWaves = 8;
 constexpr int kCaVRow = 320;                             // bytes: the four rows that lanes read side by side fall into different banks
 constexpr int kCaPRow = 36;                              // floats

@@ -1167,7 +1167,7 @@ __global__ __launch_bounds__(128) void inflight_attention_kernel(const float* __
 }
 
 // The same for heads of 128 dimensions, up to 8 tokens and final q|k|v values: a wavefront per head (twelve heads on 5 slots 3.2 us,
-// the kernel above 6.2).
+// the kernel above 6.2, which keeps other head sizes and partial sums of q|k|v).
 template <int N>
 __global__ __launch_bounds__(64) void inflight_attention_few_kernel(const float* __restrict__ qkv, int k_tok, int q_out, int kv_out, int rep,
                                                                     uint16_t* __restrict__ ctx) {
@@ -1182,7 +1182,7 @@ __global__ __launch_bounds__(64) void inflight_attention_few_kernel(const float*
 hipError_t launch_inflight_attention(const float* part, int n_splits, int k_tok, int q_out, int kv_out, int n_heads,
                                      int n_kv, int head_dim, uint16_t* ctx, hipStream_t s) {
     if (k_tok < 1 || k_tok > 64 || head_dim < 8 || head_dim > 256 || head_dim % 8) return hipErrorInvalidValue;
-    // stacks of four layers on 9 to 16 tokens: 1 to 4 % faster than with the kernel below; eight and fewer tokens keep that kernel
+    // heads of 128 dimensions on 9 to 16 tokens (stacks of four layers): 1 to 4 % faster than with the general kernel at the end
     if (head_dim == 128 && k_tok > 8) return launch_inflight_attention_wide(part, n_splits, k_tok, q_out, kv_out, n_heads, n_kv, ctx, s);
     if (head_dim == 128 && n_splits == 1) {
         const auto fn = few_slots(k_tok) == 2   ? inflight_attention_few_kernel<2>

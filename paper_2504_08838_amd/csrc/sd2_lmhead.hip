@@ -64,8 +64,9 @@ __device__ __forceinline__ void lm_better(float& a, int32_t& ia, float b, int32_
 enum { kLmHead, kLmPlain, kLmGated, kLmAdd, kLmAtt2, kLmAtt5 };
 constexpr int lm_att_slots(int mode) { return mode == kLmAtt2 ? 2 : mode == kLmAtt5 ? 5 : 0; }
 
-// HALF: a strip is eight rows (kPlain, kAdd and kAtt with one strip a workgroup and one pass): a chunk is two requests instead of four, the matrix instructions'
-// other eight rows are whatever the ring holds and nobody reads their results.  Twice the compute units stream.
+// HALF: a strip is eight rows (kPlain, kAdd and kAtt with one strip a workgroup and one pass): a chunk is two requests instead of four,
+// the matrix instructions' other eight rows are whatever the ring holds and nobody reads their results.  Twice the compute units stream.
+// A row's columns, wavefronts and order of sums are those of sixteen rows.
 // As a linear TG = 2 takes up to 32 tokens in one pass (two sets of B operands in registers, two accumulators per strip; the partial
 // strips then share one LDS buffer and need a second barrier per strip).
 template <int CPW, int MODE, bool NORM, int TG, bool HALF>
@@ -542,8 +543,8 @@ hipError_t launch_lm_head(const uint16_t* w, const float* h, int vocab, int hidd
 }
 
 // Eight rows a strip where every one of them still has a compute unit: 1536 rows are 96 strips of sixteen.  28 dense layers, hidden 1536, 5
-// tokens: 1055 -> 989 us (down 11.2 -> 8.8 in the trace), and with q|k|v 981.  A plain linear gains from 2048 columns on: 2048 x 8192 on 16
-// tokens 13.9 -> 12.1, 1536 x 8960 on 5 8.6 -> 7.9; 2048 x 2048 and smaller take the launch either way, and keep sixteen.
+// tokens: 1055 -> 989 us (down 11.2 -> 8.8 in the trace), and with q|k|v 981.  A plain linear gains on more than 2048 columns: 2048 x 8192 on
+// 16 tokens 13.9 -> 12.1, 1536 x 8960 on 5 8.6 -> 7.9; 2048 x 2048 and smaller take the launch either way, and keep sixteen.
 static bool lm_half_strips(int n_out) { return (n_out + 7) / 8 <= device_cu_count(); }
 
 // y[t][n] = sum_c W[n][c] x[t][c] for a dense row-major bf16 matrix and tokens [0, k_tok); every entry of y written
