@@ -563,7 +563,7 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
     static_assert(kMegaMaxTok * kMegaWaves <= kMiscDw && (kAreaDw + kXldsDw + kRedDw) % 4 == 0, "partial sums fit, 16-byte aligned");
     if (tid < 16) lut[tid] = make_expand_selector((uint32_t)tid);
     for (int i = tid; i < kRedDw + kMiscDw; i += kMegaThreads) red[i] = 0.f;  // accumulators, sums
-    for (int i = tid; i < kXldsDw; i += kMegaThreads) (mega_lds + kAreaDw)[i] = 0u;  // (rows past the last token are operands, too; their results are read by nobody)
+    for (int i = tid; i < kXldsDw; i += kMegaThreads) (mega_lds + kAreaDw)[i] = 0u;  // (places of empty tiles are multiplied by zeros: never infinite)
 
     // per-kind plans -> LDS
     uint32_t* plans = reinterpret_cast<uint32_t*>(part_sums + kMiscDw);
@@ -667,7 +667,12 @@ __global__ __launch_bounds__(kMegaThreads) void mega_forward_kernel(const MegaAr
             for (int u = 0; u < kAttUnr; ++u) kw[u] = vw[u] = u32x4{0u, 0u, 0u, 0u};
             if (has_item) attention_loads(ka, layer, it, it.j_lo, tid, kw, vw);
             barrier_wait(a.bar, a.err, (unsigned)ncu, gen, spin_limit);
-            if (has_item) attention_item<(KV > 0 ? KV : 1)>(ka, layer, it, reinterpret_cast<float*>(xlds), tid, kw, vw);
+            if (has_item) {
+                attention_item<(KV > 0 ? KV : 1)>(ka, layer, it, reinterpret_cast<float*>(xlds), tid, kw, vw);
+                // The scratch was the activation area, and its fp32 sums read as bf16 may be infinite or NaN: a later phase's empty tile,
+                // whose place no prologue writes, multiplies zeros by them.
+                for (int i = tid; i < kXldsDw; i += kMegaThreads) (mega_lds + kAreaDw)[i] = 0u;
+            }
             barrier_arrive(a.bar, gen);
         }
 

@@ -298,3 +298,20 @@ def test_one_position_over_all_others(n_hist, k_tok, at, rep, fmt, forward):
     chosen = []
     got, _ = _spelled_out(rep, fmt, n_hist, k_tok, keys, 86)
     assert np.array_equal(got, np.broadcast_to(chosen[0][None, :, None], got.shape))
+
+
+@pytest.mark.parametrize("hidden,inter", [(1088, 5760), (1344, 4864)])
+@pytest.mark.parametrize("n_kv", [1, 4])
+@pytest.mark.parametrize("k_tok", [1, 5])
+def test_empty_places_behind_the_attention_step(hidden, inter, n_kv, k_tok):
+    """Blocks of five and of three slabs whose slabs are multiplied in twos (six and four places): the place without a slab multiplies zeros
+    by whatever its activations are, and the attention step has used that part of LDS for sums in between."""
+    import gpu_util as gu
+    shape = SimpleNamespace(layers=2, hidden=hidden, q_out=512, kv_out=128 * n_kv, inter=inter, n_heads=4, n_kv=n_kv, head_dim=128)
+    max_pos, n_hist = 512, 450
+    get, model = _model(shape, 87)
+    kc, vc = wl.gen_kv_history(87, shape.layers, shape.n_kv, max_pos, shape.head_dim, n_hist)
+    h_bits = wl.gen_x(87, 0, "q", k_tok, shape.hidden)
+    got = _decode(model, shape, h_bits, gu.dev(kc), gu.dev(vc), max_pos, n_hist)
+    want = od.drafter_decode(shape, get, h_bits, kc, vc, n_hist, THETA)
+    assert rel_l2(got, want) <= 1e-3
