@@ -217,10 +217,10 @@ hipError_t launch_dense_stream_add(const uint16_t* w, const uint16_t* x, int n_o
 // token slots that the attention of one head by one wavefront is made for
 constexpr int few_slots(int k_tok) { return k_tok <= 2 ? 2 : k_tok <= 5 ? 5 : 8; }
 // h += W attention(q|k|v), q|k|v final values [k_tok][(n_heads + 2 n_kv) 128], heads of 128 dimensions.  Every workgroup attends for all
-// heads, a wavefront for one in eight, and its time goes with heads times scores: where that is at most 30 a wavefront it costs
-// less than a launch.  28 dense layers, hidden 1536, 12 heads, inside / as a launch of its own: one token 923 / 975 us, five (30
-// scores a wavefront) 1057 / 1064, eight (72) 1243 / 1160; hidden 512, 4 heads, five tokens (15) 456 / 539; 8 layers, hidden 3072, 24
-// heads, five tokens (45) 437 / 429.
+// heads, a wavefront for one in eight, and its time goes with heads times scores.  With two and five slots that is 3 to 12, 15, 30, 45 or
+// 60 scores a wavefront: at 30 it costs what a launch does, by 1 % more or less, from 45 on more.  8 dense layers, inside / apart, us:
+// 12 heads on one token (6) 244 / 256, three, four and five (30) 275 / 271, 279 / 278 and 279 / 281; 16 heads on three and five 254 / 254 and
+// 257 / 260; 24 heads on one (9) 385 / 396, on five (45) 431 / 422; 32 heads on five (60) 417 / 401.
 inline bool dense_stream_attend_ok(int n_heads, int n_out, int k_tok) {
     const int heads = (n_heads + 7) / 8, slots = few_slots(k_tok);
     return k_tok <= 5 && heads <= 4 && heads * slots * (slots + 1) / 2 <= 30 && dense_stream_add_ok(n_out, 128 * n_heads, k_tok);
